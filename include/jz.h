@@ -354,12 +354,13 @@ typedef struct jz_stats {
     int64_t list_entries[JZ_MAX_PLANES + 1]; /* list entries produced per level (index p = plane p, P = super) */
     int64_t leaf_pairs;              /* leaf-leaf interactions in the leaf list */
     int64_t leaf_pairs_visited;      /* of those, visited before the early exit */
-    double evaluations;              /* point-pair distance evaluations in the leaf stage */
+    double evaluations;              /* point pairs whose distance the leaf stage tested (kNN: the
+                                        pairs its matrix filter looked at) */
     double leaf_ms;                  /* leaf-stage kernel time (ms), when profiling is on */
     double total_ms;                 /* whole call, device time (ms), when profiling is on */
     int reruns;                      /* capacity reruns in the last call */
     int64_t insert_rounds;           /* kNN leaf stage: wave-level top-k insert rounds */
-    int64_t tile_steps;              /* kNN leaf stage: wave-level candidate steps */
+    int64_t tile_steps;              /* kNN leaf stage: wave-level steps that queue candidates */
     int64_t lists_sorted_long;       /* kNN leaf stage: lists longer than the 256 entries staged in
                                         LDS, put in r_low order (in the wave's LDS scratch up to
                                         1024 entries, beforehand in HBM up to sort_max) */

@@ -629,16 +629,16 @@ __device__ __forceinline__ void topk_insert(TopK<K> &b, double key) {
 
 constexpr int SB = 16;        // source leaves examined per batch
 constexpr int TILE_PTS = 256; // source points staged per batch (positions fit a byte)
+constexpr int HALF = 128;     // tile positions filtered at a time (32 blocks of 4 per lane row)
 constexpr int CQ = 32;        // queued candidate positions per lane
-constexpr int CH = 8;         // tile positions a lane scans between queue checks
+constexpr int CH = 8;         // positions queued between checks of the queue
 
-// LDS slot of tile position j: inside each chunk of 8 positions the slots are
-// permuted by the chunk's low 3 bits, so that lanes reading the same position
-// of different chunks at once spread over the LDS banks (unpermuted, every
-// chunk starts at a multiple of 128 bytes and all of them meet in one bank
-// group).
-__device__ __forceinline__ int tslot(int j) { return j ^ ((j >> 3) & 7); }
+typedef float v4f __attribute__((ext_vector_type(4)));
 
+// Relative and absolute margins of the matrix filter (see k_leaf_knn).
+constexpr float FILTER_E = 0x1p-18f;
+constexpr float FILTER_TINY = 0x1p-120f;
+constexpr float FILTER_BIG = 0x1p100f;
 
 // Keep the K smallest of two ascending key lists a and b in a (ascending).
 // With both lists padded to M = next power of two, min(a[i], b[M-1-i]) is a
@@ -737,8 +737,93 @@ __device__ __forceinline__ void merge_chunk(TopK<K> &a, const double (&ch)[C]) {
     for (int i = 0; i < K; ++i) a.set(i, c[i]);
 }
 
+// The matrix filter of k_leaf_knn over the m <= HALF tile positions from ap
+// (this lane's row and component of the first block of 16): wd[k] of a lane
+// receives the hits of its own query at positions 4 j + W h + k, W = 4 / SS,
+// bit j for position 4 j + W h + k; SS lanes per query, lane h of them.
+template <int SS, bool PER>
+__device__ __forceinline__ void filter_words(const float *ap, int m, int h, float ac, float aL,
+                                             float Lh, const float (&bq)[4], float tq,
+                                             unsigned (&wd)[4]) {
+    constexpr int W = 4 / SS;
+    // t of the queries 16 g + l % 16, from the lane rows that hold them
+    const int ti = __float_as_int(-tq);
+    int tg[4] = {ti, ti, ti, ti};
+    if constexpr (SS < 4) {
+        const auto x = __builtin_amdgcn_permlane16_swap(ti, ti, false, false);
+        tg[0] = x[0];
+        tg[1] = x[1];
+    }
+    if constexpr (SS == 1) {
+        const auto y = __builtin_amdgcn_permlane32_swap(tg[0], tg[0], false, false);
+        const auto z = __builtin_amdgcn_permlane32_swap(tg[1], tg[1], false, false);
+        tg[0] = y[0];
+        tg[1] = z[0];
+        tg[2] = y[1];
+        tg[3] = z[1];
+    }
+    v4f cq[W];
+#pragma unroll
+    for (int g = 0; g < W; ++g) {
+        const float v = __int_as_float(tg[g]);
+        cq[g] = v4f{v, v, v, v};
+    }
+    const int nblk = uni((m + 15) >> 4);
+    for (int b = 0; b < nblk; ++b) {
+        const float av = wrap_diff<PER>(ap[64 * b] - ac, aL, aL != 0.0f ? Lh : INFINITY);
+        v4f d[W];
+#pragma unroll
+        for (int g = 0; g < W; ++g)
+            d[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bq[g], cq[g], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int g = 0; g < W; ++g)
+                wd[g] = __builtin_amdgcn_alignbit(wd[g], __float_as_uint(d[g][i]), 31);
+    }
+    // rows and groups transposed
+    if constexpr (SS < 4) {
+        const auto x = __builtin_amdgcn_permlane16_swap(wd[0], wd[1], false, false);
+        wd[0] = x[0];
+        wd[1] = x[1];
+    }
+    if constexpr (SS == 1) {
+        const auto x = __builtin_amdgcn_permlane16_swap(wd[2], wd[3], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(wd[0], x[0], false, false);
+        const auto z = __builtin_amdgcn_permlane32_swap(wd[1], x[1], false, false);
+        wd[0] = y[0];
+        wd[1] = z[0];
+        wd[2] = y[1];
+        wd[3] = z[1];
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        // positions from m on hold no point of this batch
+        const int nv = max((m - (W * h + k) + 3) >> 2, 0);
+        wd[k] = __builtin_bitreverse32(wd[k] << (32 - 4 * nblk)) & (unsigned)((1ull << nv) - 1ull);
+    }
+}
+
+// The same masks from the exact distances of all positions.
+template <bool PER>
+__device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int h, const float4 &me,
+                                            float thr, float Lp, float Lh, unsigned (&wd)[4]) {
+    for (int k = W - 1; k >= 0; --k) {
+        const int r = W * h + k;
+        wd[3] = wd[2];
+        wd[2] = wd[1];
+        wd[1] = wd[0];
+        wd[0] = 0;
+        for (int j = 0; 4 * j < m; ++j) {
+            const float4 p = tp[4 * j + r];
+            const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
+            wd[0] |= (4 * j + r < m && dd <= thr) ? 1u << j : 0u;
+        }
+    }
+}
+
 // Leaf stage, one wave per receiving leaf. A leaf of at most 16 (32) points
-// gives each query 4 (2) lanes; the lanes of a query scan interleaved slices
+// gives each query 4 (2) lanes; the lanes of a query take interleaved slices
 // of every staged tile, keep their own top-k, and prune with the smallest
 // k-th distance of the group (the merged k-th can only be smaller), and their
 // lists are merged at the end.
@@ -747,9 +832,37 @@ __device__ __forceinline__ void merge_chunk(TopK<K> &a, const double (&ch)[C]) {
 // still reach (point-to-box bound <= the group's k-th distance); the points of
 // the sources some lane needs are staged together in one LDS tile. The walk
 // stops at the first source whose r_low exceeds every query's k-th distance.
-// Candidates within the k-th distance are queued as tile positions and
-// inserted into the register top-k in rounds, so insert time follows the
-// busiest lane rather than every accepted candidate of any lane.
+//
+// Which of the tile's points may belong to a query's list is decided on the
+// matrix cores: a filter on approximate distances that never drops a point
+// within the k-th distance, whose hits are then evaluated with the fixed
+// float32 expression. With q' = fl(q - c), p' = fl(p - c) (c: centre of the
+// receiving leaf's box), one v_mfma_f32_16x16x4_f32 computes, for 16 points x
+// 16 queries, D = -2 q'.p' + w - t, with w = |p'|^2 (1 - e) of the point and
+// t = kth (1 + e) - |q'|^2 (1 - e) + tiny of the query; a hit is D < 0, and
+// the hits are collected by shifting the sign bit of each result into a mask
+// (one v_alignbit per result).
+// Why a hit cannot be missed (u = 2^-24): the real |q' - p'|^2 differs from
+// the real |q - p|^2 by at most 4.2 u (|q'|^2 + |p'|^2), the fixed float32
+// dist2 from the latter by 6 u relative (and a subnormal rounding), and the
+// five-term sum D by at most 20 u (|p'|^2 + |q'|^2 + kth), whatever the order
+// and rounding direction of the matrix unit. e = 2^-18 = 64 u covers the sum
+// of these, tiny = 2^-120 covers flushed subnormal products. Magnitudes
+// beyond 2^100 (where inf - inf could appear) take the exact dense scan below.
+// In a periodic box p' is the image nearest to c, and the wrapped difference
+// carries a rounding at the scale of the period, so the k-th distance is
+// raised by 2^-19 L; the image nearest to c is also the one nearest to q as
+// long as |q'| + kth stays below half a period on every axis, else the dense
+// scan runs.
+// Against per-lane box tests and exact evaluations on the vector unit (12
+// instructions per position and wave, 30 % of the lanes in use) the filter
+// costs one matrix instruction and four shifts per 16 x 16 pairs: at 2^24
+// clustered points and k = 16 the kernel issues 4.3e9 vector instructions
+// instead of 6.1e9 and takes 9.5 ms instead of 10.6; 2^21 uniform points,
+// k = 30: 1.95 ms instead of 2.85.
+// Hits are queued as tile positions and inserted into the register top-k in
+// rounds, so insert time follows the busiest lane rather than every accepted
+// candidate of any lane.
 //
 // k > 32 takes several passes (the paper's LeafToLeaf with at most 32
 // neighbours per call, called again for the next ones): a pass with LO finds
@@ -758,7 +871,7 @@ __device__ __forceinline__ void merge_chunk(TopK<K> &a, const double (&ch)[C]) {
 // continue by index. A pass writes columns [col0, col0 + kw) of rows of
 // out_stride entries.
 template <int K, bool LO, bool PER>
-__global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
+__global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const int2 *__restrict__ seg, int2 *__restrict__ list, const Node *__restrict__ leaves,
     const float4 *__restrict__ pts, int n_leaves, const int *__restrict__ leaf_base,
     int32_t *__restrict__ out_idx, float *__restrict__ out_d2,
@@ -769,15 +882,14 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
     const unsigned long long *__restrict__ n_first, int first_len) {
     // Lp: period of the cube (PER), Lh its half
     const float Lh = 0.5f * Lp;
-    // one block per wave: the staged list (LCAP entries), the point tile,
-    // the (lo, hi) box of every 8 tile positions and the candidate queues;
-    // before the walk the whole block is the scratch in which a longer list
-    // is sorted
-    constexpr int O_TILE = LCAP, O_BOX = O_TILE + TILE_PTS * 2, O_Q = O_BOX + TILE_PTS / 8 * 4;
+    // one block per wave: the staged list (LCAP entries), the point tile
+    // (x, y, z and the filter's w), the points' indices and the candidate
+    // queues; before the walk the whole block is the scratch in which a
+    // longer list is sorted
+    constexpr int O_TILE = LCAP, O_IDX = O_TILE + TILE_PTS * 2, O_Q = O_IDX + TILE_PTS / 2;
     constexpr int RAW = O_Q + CQ * 64 / 8;
     __shared__ __align__(16) uint64_t s_raw[WPB][RAW];
     __shared__ Node s_nodes[WPB][SB];
-    __shared__ int s_offs[WPB][SB + 1];
     __shared__ int s_sc[WPB][SB];
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     // the first waves take the leaves with lists longer than first_len (in
@@ -816,24 +928,22 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
     const float4 me = pts[a.start + qpos];
     const int64_t row = (int64_t)__float_as_int(me.w) - qry_lo;
     const int base = leaf_base ? leaf_base[A] : 0;
-    // keys at or below lo (and distances below lo_d) belong to earlier passes
+    // keys at or below lo belong to earlier passes
     double lo = -1.0;
-    float lo_d = 0.0f;
     if constexpr (LO) {
         if (act) {
             const int pi = out_idx[row * out_stride + col0 - 1];
             const float pd = out_d2[row * out_stride + col0 - 1];
             lo = pi < 0 ? __builtin_bit_cast(double, PAD_KEY) : key_of(pd, pi + base);
-            lo_d = pi < 0 ? INFINITY : pd;
         }
     }
     const int2 sg = seg[A];
     int2 *gl = list + uni(sg.x);
     const int len = uni(sg.y);
     float4 *tile = reinterpret_cast<float4 *>(L + O_TILE);
-    float4 *cbox = reinterpret_cast<float4 *>(L + O_BOX);
+    const float *tilef = reinterpret_cast<const float *>(tile);
+    int *tidx = reinterpret_cast<int *>(L + O_IDX);
     Node *nb = s_nodes[w];
-    int *offs = s_offs[w];
     int *sc = s_sc[w];  // source points of each batch source
     const bool staged = stage_list(gl, len, L, min(sort_cap, prev_pow2(RAW)), presorted);
 
@@ -841,7 +951,33 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
     TopK<K> best;
 #pragma unroll
     for (int i = 0; i < K; ++i) best.set(i, pad);
-    unsigned evals = 0, visited = 0, rounds = 0, steps = 0;
+    unsigned visited = 0, rounds = 0, steps = 0;
+    unsigned long long evals = 0;
+
+    // The filter's query side. Lane l holds component l / 16 (x, y, z, 1) of
+    // query 16 g + l % 16 in bq[g] (through LDS: the tile is not in use yet).
+    const float cx = uni(0.5f * a.lo[0] + 0.5f * a.hi[0]);
+    const float cy = uni(0.5f * a.lo[1] + 0.5f * a.hi[1]);
+    const float cz = uni(0.5f * a.lo[2] + 0.5f * a.hi[2]);
+    const float mx = me.x - cx, my = me.y - cy, mz = me.z - cz;
+    const float qn2 = mx * mx + my * my + mz * mz;
+    const float nq = qn2 * (1.0f - FILTER_E);
+    const bool qbad = __ballot(act && !(qn2 < FILTER_BIG)) != 0;
+    // (periodic) farthest coordinate of a query from c
+    const float qfar = PER ? fmaxf(fmaxf(fabsf(mx), fabsf(my)), fabsf(mz)) : 0.0f;
+    if (h == 0) tile[q] = make_float4(-2.0f * mx, -2.0f * my, -2.0f * mz, 1.0f);
+    wave_lds_sync();
+    float bq[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        bq[g] = tilef[(((16 * g + (lane & 15)) & ((64 >> lgS) - 1)) << 2) + (lane >> 4)];
+    wave_lds_sync();
+    // the points' side: row m of a block of 16 tile positions reads position
+    // 4 (m % 4) + m / 4 of it, so that result i of lane row r is position
+    // 4 i + r and bit j of that row's mask position 4 j + r
+    const int arow = (((lane & 3) << 2 | ((lane >> 2) & 3)) << 2) + (lane >> 4);
+    const float ac = lane < 16 ? cx : (lane < 32 ? cy : (lane < 48 ? cz : 0.0f));
+    const float aL = lane < 48 ? Lp : 0.0f;  // (periodic) no wrap of w
     // candidate queue of this lane: positions at q0, q0 + 64, ... up to qp
     // (LDS-typed pointers: 32-bit arithmetic instead of 64-bit)
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
@@ -882,7 +1018,7 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
                 const int qv = q0[64 * slot];
                 const float4 s = tile[qv];
                 const float dd = dist2_m<PER>(me.x, me.y, me.z, s.x, s.y, s.z, Lp, Lh);
-                const double kk = key_of(dd, __float_as_int(s.w));
+                const double kk = key_of(dd, tidx[qv]);
                 ch[u] = (c + u < qn && (!LO || kk > lo)) ? kk : pad;
             }
             sort_keys<8>(ch);
@@ -934,184 +1070,117 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
                                          nb[qq].hi[0], nb[qq].hi[1], nb[qq].hi[2], Lp) <= kth)
                 needbits |= 1u << qq;
         const unsigned any = uni(wave_or(needbits));
-        // take needed sources in order while their points fit the tile; each
-        // occupies a multiple of 8 positions, one box per 8 (every lane
-        // computes the same offsets; lane 0 keeps them in LDS for the scan)
-        int take = 0, npts = 0;
-        int o_r[SB + 1];
-        o_r[0] = 0;
-        if (lane == 0) offs[0] = 0;
-#pragma unroll
-        for (int qq = 0; qq < SB; ++qq) {
-            const bool want = qq < nb_n && take == qq;
-            const int c = want && ((any >> qq) & 1u) ? (uni(sc[qq]) + 7) & -8 : 0;
-            if (want && npts + c <= TILE_PTS) {
-                npts += c;
-                take = qq + 1;
+        // take the needed sources in order while their points fit the tile,
+        // and stage them one after the other (lane f takes point f of a
+        // source: a leaf holds at most 64 points), each with its w
+        int take = nb_n, npts = 0;
+        bool bad = qbad;
+        for (unsigned rest = any; rest;) {
+            const int qq = __ffs((int)rest) - 1;
+            rest &= rest - 1u;
+            const int nsc = uni(sc[qq]);
+            if (npts + nsc > TILE_PTS) {
+                take = qq;
+                break;
             }
-            o_r[qq + 1] = npts;
-            if (lane == 0) offs[qq + 1] = npts;
-        }
-        // stage the taken sources' points (lane f takes point f of a source:
-        // a leaf holds at most 64 points) and the bounding box of every 8
-        // positions (reduced over groups of 8 lanes). Filler positions hold a
-        // point at +inf with index -1: its key is the padding key, so
-        // accepting it changes nothing; it is left out of the boxes.
-#pragma unroll
-        for (int qq = 0; qq < SB; ++qq) {
-            if (qq < take && o_r[qq + 1] > o_r[qq]) {
-                const int cnt = uni(nb[qq].count), st = uni(nb[qq].start);
-                const int nsc = uni(sc[qq]);
-                const int size = o_r[qq + 1] - o_r[qq];
-                const float4 filler = make_float4(INFINITY, INFINITY, INFINITY, __int_as_float(-1));
-                float4 p = filler;
-                bool real = lane < cnt;
-                if (real) p = pts[st + lane];
+            const int cnt = uni(nb[qq].count), st = uni(nb[qq].start);
+            if (lane < cnt) {
+                const float4 p = pts[st + lane];
+                const float dx = wrap_diff<PER>(p.x - cx, Lp, Lh);
+                const float dy = wrap_diff<PER>(p.y - cy, Lp, Lh);
+                const float dz = wrap_diff<PER>(p.z - cz, Lp, Lh);
+                const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
+                int pos = npts + lane;
+                bool real = true;
                 if (types) {
-                    // only the source points, packed at the front
-                    real = real && __float_as_int(p.w) < src_hi;
-                    const uint64_t rm = __ballot(real);
-                    if (real) tile[tslot(o_r[qq] + (int)__popcll(rm & lanemask_lt()))] = p;
-                    if (lane >= nsc && lane < size) tile[tslot(o_r[qq] + lane)] = filler;
-                    wave_lds_sync();
-                    real = lane < nsc;
-                    p = real ? tile[tslot(o_r[qq] + lane)] : filler;
-                } else if (lane < size) {
-                    tile[tslot(o_r[qq] + lane)] = p;
+                    // only the source points, packed
+                    real = __float_as_int(p.w) < src_hi;
+                    pos = npts + (int)__popcll(__ballot(real) & lanemask_lt());
                 }
-                float lx = real ? p.x : INFINITY, ly = real ? p.y : INFINITY,
-                      lz = real ? p.z : INFINITY;
-                float hx = real ? p.x : -INFINITY, hy = real ? p.y : -INFINITY,
-                      hz = real ? p.z : -INFINITY;
-                lx = group8_min(lx);
-                ly = group8_min(ly);
-                lz = group8_min(lz);
-                hx = group8_max(hx);
-                hy = group8_max(hy);
-                hz = group8_max(hz);
-                if ((lane & 7) == 0 && lane < size) {
-                    // the chunk's box, and in lo.w its number of real points
-                    float4 *bx = cbox + ((o_r[qq] + lane) >> 3) * 2;
-                    bx[0] = make_float4(lx, ly, lz, __int_as_float(min(8, max(0, nsc - lane))));
-                    bx[1] = make_float4(hx, hy, hz, 0.0f);
+                if (real) {
+                    tile[pos] = make_float4(p.x, p.y, p.z, pw);
+                    tidx[pos] = __float_as_int(p.w);
+                    bad = bad || !(pw < FILTER_BIG);
                 }
             }
+            npts += nsc;
         }
+        bad = __ballot(bad) != 0;
         // next window
         fetch(t + take, SB);
         wave_lds_sync();
-        // the S lanes of a query take positions jj + h of every S-aligned step
-        auto scan = [&](auto s_const) __attribute__((always_inline)) {
-            constexpr int SS = decltype(s_const)::value;
-            if (t == 0) {
-                // the first source (one with r_low = 0) meets an empty top-k:
-                // every point is accepted, so its points are merged in sorted
-                // chunks instead of being queued and inserted one by one
-                constexpr int C = K < 8 ? next_pow2(K) : (K <= 16 ? 8 : 16);
-                if (take == 1 && (any & 1u)) {
-                    ++visited;
-                    const int f0 = uni(offs[0]), f1 = uni(offs[1]);
-                    for (int j0 = f0; j0 < f1; j0 += C * SS) {
-                        double ch[C];
+        evals += (unsigned)npts * (unsigned)acount;
+        if (t == 0) {
+            // the first source (one with r_low = 0) meets an empty top-k:
+            // every point is accepted, so its points are merged in sorted
+            // chunks instead of being queued and inserted one by one (lane h
+            // of a query's S takes positions h, h + S, ...)
+            constexpr int C = K < 8 ? next_pow2(K) : (K <= 16 ? 8 : 16);
+            visited += (unsigned)__popc(any & 1u);
+            for (int j0 = 0; j0 < npts; j0 += C << lgS) {
+                double ch[C];
 #pragma unroll
-                        for (int u = 0; u < C; ++u) {
-                            if (j0 + u * SS < f1) {
-                                const float4 p = tile[tslot(j0 + u * SS + h)];
-                                const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
-                                const double kk = key_of(dd, __float_as_int(p.w));
-                                ch[u] = (!LO || kk > lo) ? kk : pad;
-                            } else {
-                                ch[u] = pad;
-                            }
-                        }
-                        sort_keys<C>(ch);
-                        merge_chunk<K, C>(best, ch);
-                        steps += (unsigned)((min(f1, j0 + C * SS) - j0) / SS);
-                    }
-                    const int cnt = uni(sc[0]);
-                    if (act) evals += cnt > h ? (unsigned)((cnt - h + SS - 1) / SS) : 0u;
+                for (int u = 0; u < C; ++u) {
+                    const int j = j0 + (u << lgS) + h;
+                    const int jj = min(j, TILE_PTS - 1);
+                    const float4 p = tile[jj];
+                    const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
+                    const double kk = key_of(dd, tidx[jj]);
+                    ch[u] = (j < npts && (!LO || kk > lo)) ? kk : pad;
                 }
-                return;
+                sort_keys<C>(ch);
+                merge_chunk<K, C>(best, ch);
+                steps += C;
             }
-            // Every lane marks the 8-position chunks of the tile its query can
-            // reach (chunk box within the group's k-th distance; a chunk box
-            // lies inside its source's box, so this also drops the sources the
-            // query does not need), then pops its own chunks, lowest first:
-            // the lanes work on different chunks at once, so a pass costs the
-            // largest per-lane chunk count instead of the number of chunks any
-            // lane needs. The S lanes of a query share kth and so the mask,
-            // and split each chunk's positions.
+            npts = 0;
+        } else {
             visited += (unsigned)__popc(any & ((1u << take) - 1u));
-            const int nch = uni(npts >> 3);
-            // In a periodic box the minimum-image wrap of a difference only
-            // triggers beyond half a period: for a chunk with fl(q - lo) <= h
-            // and fl(q - hi) >= -h on every axis (the rounded difference is
-            // monotone in the point), no point of it wraps for this query, and
-            // its distances and bound are the open ones, bit for bit. W marks
-            // the chunks that may wrap; the periodic forms run only where some
-            // lane has one.
-            unsigned M = 0, W = 0;
-            for (int c = 0; c < nch; ++c) {
-                const float4 *bx = cbox + c * 2;
-                const float4 blo = bx[0], bhi = bx[1];
-                bool wrap = false;
-                if constexpr (PER)
-                    wrap = !(me.x - blo.x <= Lh && me.x - bhi.x >= -Lh && me.y - blo.y <= Lh &&
-                             me.y - bhi.y >= -Lh && me.z - blo.z <= Lh && me.z - bhi.z >= -Lh);
-                const float lo2 =
-                    (PER && __ballot(act && wrap))
-                        ? point_low2_m<PER>(me.x, me.y, me.z, blo.x, blo.y, blo.z, bhi.x, bhi.y,
-                                            bhi.z, Lp)
-                        : point_low2_m<false>(me.x, me.y, me.z, blo.x, blo.y, blo.z, bhi.x, bhi.y,
-                                              bhi.z, Lp);
-                const bool need = act && lo2 <= kth;
-                M |= need ? (1u << c) : 0u;
-                W |= need && wrap ? (1u << c) : 0u;
+        }
+        for (int p0 = 0; p0 < npts; p0 += HALF) {
+            const int m = min(HALF, npts - p0);
+            unsigned wd[4] = {0, 0, 0, 0};
+            bool dense = bad;
+            float thr = kth;
+            if constexpr (PER) {
+                // the k-th distance raised by 2^-19 L
+                const float rt = __builtin_sqrtf(kth) * (1.0f + 0x1p-20f) + Lp * 0x1p-19f;
+                dense = dense || __ballot(act && !(qfar + rt < Lh * (1.0f - 0x1p-10f)));
+                thr = rt * rt;
             }
-            const int nit = uni(wave_max_i(__popc(M)));
-            for (int it = 0; it < nit; ++it) {
-                const bool has = M != 0u;
-                const int c = has ? __ffs((int)M) - 1 : 0;
-                M &= M - 1u;
-                const float thr = has ? kth : -1.0f;
-                // tslot(c * 8 + q) for q < 8 is (c * 8 | (c & 7)) ^ q, and
-                // q = u * SS + h = (u * SS) ^ h: one XOR per position
-                const int jb = (c * 8 | (c & 7)) ^ h;
-                // (the queue pointer is kept as an address, not as an offset
-                // from the lane's first slot, so no add is needed per write)
-                asm volatile("" : "+v"(qp));
-                auto eval = [&](auto per_const) __attribute__((always_inline)) {
-                    constexpr bool P = decltype(per_const)::value;
-#pragma unroll
-                    for (int u = 0; u < 8 / SS; ++u) {
-                        const int j = jb ^ (u * SS);
-                        const float4 p = tile[j];
-                        const float dd = dist2_m<P>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
-                        // written always, kept only if accepted (at most CH
-                        // positions per pop from qn <= CQ - CH: the slot exists)
-                        *qp = (uint8_t)j;
-                        qp += (dd <= thr && (!LO || dd >= lo_d)) ? 64 : 0;
+            // t of this lane's query
+            const float tq = act ? thr * (1.0f + FILTER_E) - nq + FILTER_TINY : -FILTER_BIG;
+            if (dense) dense_words<PER>(tile + p0, m, 4 >> lgS, h, me, act ? kth : -1.0f, Lp, Lh, wd);
+            else if (lgS == 0) filter_words<1, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
+            else if (lgS == 1) filter_words<2, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
+            else filter_words<4, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
+            // queue the hits word by word, lowest position first; the queue is
+            // drained when a lane's is nearly full and after the batch's last
+            // word
+            const int W = 4 >> lgS;
+            for (int k = 0; k < W; ++k) {
+                unsigned M = wd[0];
+                wd[0] = wd[1];
+                wd[1] = wd[2];
+                wd[2] = wd[3];
+                const int n = uni(wave_max_i(__popc(M)));
+                const int pb = p0 + W * h + k;
+                const bool last = k == W - 1 && p0 + HALF >= npts;
+                int it = 0;
+                do {
+                    const int e = min(n, it + CH);
+                    for (; it < e; ++it) {
+                        // (written always, kept only if there is a hit: at
+                        // most CH positions from qp <= qlim, the slot exists)
+                        *qp = (uint8_t)(pb + ((__ffs((int)M) - 1) << 2));
+                        qp += M ? 64 : 0;
+                        M &= M - 1u;
                     }
-                };
-                if (PER && __ballot(has && ((W >> c) & 1u)))
-                    eval(std::integral_constant<bool, PER>());
-                else
-                    eval(std::integral_constant<bool, false>());
-                steps += (unsigned)(8 / SS);
-                if (has) {
-                    const int r = __float_as_int(cbox[c * 2].w);
-                    evals += r > h ? (unsigned)((r - h + SS - 1) / SS) : 0u;
-                }
-                if (__ballot(qp > qlim)) {
-                    drain();
-                    kth = group_kth();
-                }
+                    if (__ballot(qp > qlim) != 0 || (last && it >= n)) drain();
+                } while (it < n);
+                steps += (unsigned)n;
             }
-        };
-        if (lgS == 2) scan(std::integral_constant<int, 4>());
-        else if (lgS == 1) scan(std::integral_constant<int, 2>());
-        else scan(std::integral_constant<int, 1>());
-        drain();
+            if (p0 + HALF < npts) kth = group_kth();
+        }
         wave_lds_sync();
         t += take;
     }
@@ -1141,10 +1210,9 @@ __global__ __launch_bounds__(64 * WPB) void k_leaf_knn(
             }
         }
     }
-    const int ev = wave_sum_i((int)evals);
     if (lane == 0) {
         unsigned long long *st = stats + (A & (STAT_SLOTS - 1));
-        atomicAdd(st + 0 * STAT_SLOTS, (unsigned long long)ev);
+        atomicAdd(st + 0 * STAT_SLOTS, evals);
         atomicAdd(st + 1 * STAT_SLOTS, (unsigned long long)visited);
         atomicAdd(st + 2 * STAT_SLOTS, (unsigned long long)rounds);
         atomicAdd(st + 3 * STAT_SLOTS, (unsigned long long)steps);

@@ -1,0 +1,69 @@
+"""GPU parity of the kNN leaf stage's matrix filter at the sizes where it can
+go wrong: leaves around the 16, 32 and 48 queries of its column groups, tiles
+around 16, 128 and 256 staged points, coordinates whose scale or offset strains
+the filter's margins, and sets where it gives way to the exact dense scan.
+Results are exact, so every comparison with the oracle is bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_05885_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def jz():
+    from paper_2604_05885_amd import api
+    return api
+
+
+def check(jz, p, k, what, period=0.0, **opts):
+    import torch
+    p = np.ascontiguousarray(p, dtype=np.float32)
+    with jz.jz_build(torch.from_numpy(p).cuda(), jz.default_opts(period=period, **opts)) as t:
+        gi, gd = t.knn(k)
+        gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
+    wi, wd = oracle.knn_bf_periodic(p, period, k) if period else oracle.knn_bf(p, k)
+    assert np.array_equal(gi, wi), what
+    assert np.array_equal(gd.view(np.uint32), wd.view(np.uint32)), what
+
+
+# one leaf of n points beside a second set of leaves: every count of queries
+# and of staged points around the filter's blocks
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 127, 128, 129,
+                               255, 256, 257, 320])
+@pytest.mark.parametrize("k", [1, 7, 16, 33])
+def test_filter_block_edges(jz, n, k):
+    check(jz, inputs.uniform(n, 100 + n), k, (n, k))
+
+
+@pytest.mark.parametrize("leaf_max", [1, 3, 16, 17, 32, 33, 48, 63])
+def test_filter_leaf_sizes(jz, leaf_max):
+    check(jz, inputs.clustered(3000, 6, 41), 16, leaf_max, leaf_max=leaf_max)
+
+
+# the spread around a far offset is a few hundred units in the last place, so
+# many distances are equal and the filter's threshold meets them exactly
+@pytest.mark.parametrize("offset,scale", [(0.0, 2.0 ** -62), (0.0, 2.0 ** -40), (1.0, 2.0 ** -16),
+                                          (1.0e4, 2.0 ** -3), (-3.0e7, 512.0), (0.0, 2.0 ** 45),
+                                          (0.0, 2.0 ** 52), (2.0 ** 58, 2.0 ** 44)])
+def test_filter_scales(jz, offset, scale):
+    p = (inputs.clustered(2500, 5, 42).astype(np.float64) * scale + offset).astype(np.float32)
+    check(jz, p, 12, (offset, scale))
+
+
+# sparse points far around a dense core: wide leaves whose centre is far from
+# most of their points
+def test_filter_wide_leaves(jz):
+    core = inputs.uniform(1500, 43) * np.float32(1e-5)
+    far = (inputs.uniform(1500, 44) - np.float32(0.5)) * np.float32(100.0)
+    for k in (5, 32):
+        check(jz, np.concatenate([core, far]), k, k)
+
+
+# few points in the cube: the k-th distance reaches past half a period
+@pytest.mark.parametrize("n,k", [(5, 5), (40, 32), (300, 32), (700, 8), (3000, 16)])
+def test_filter_periodic_reach(jz, n, k):
+    check(jz, inputs.uniform(n, 45), k, (n, k), period=1.0)
+    check(jz, inputs.clustered(n, 3, 46), k, (n, k, "clustered"), period=1.0)
