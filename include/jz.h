@@ -360,7 +360,7 @@ typedef struct jz_stats {
     double total_ms;                 /* whole call, device time (ms), when profiling is on */
     int reruns;                      /* capacity reruns in the last call */
     int64_t insert_rounds;           /* kNN leaf stage: wave-level top-k insert rounds */
-    int64_t tile_steps;              /* kNN leaf stage: wave-level steps that queue candidates */
+    int64_t tile_steps;              /* kNN leaf stage: blocks of 16 source points filtered */
     int64_t lists_sorted_long;       /* kNN leaf stage: lists longer than the 256 entries staged in
                                         LDS, put in r_low order (in the wave's LDS scratch up to
                                         1024 entries, beforehand in HBM up to sort_max) */

@@ -628,10 +628,10 @@ __device__ __forceinline__ void topk_insert(TopK<K> &b, double key) {
 }
 
 constexpr int SB = 16;        // source leaves examined per batch
-constexpr int TILE_PTS = 256; // source points staged per batch (positions fit a byte)
+constexpr int TILE_PTS = 255; // source points staged per batch (positions fit a byte)
+constexpr int FILLER = 255;   // tile position of a point at infinity with the padding index
 constexpr int HALF = 128;     // tile positions filtered at a time (32 blocks of 4 per lane row)
 constexpr int CQ = 32;        // queued candidate positions per lane
-constexpr int CH = 8;         // positions queued between checks of the queue
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -670,21 +670,24 @@ __device__ __forceinline__ void merge_topk(TopK<K> &a, const TopK<K> &b) {
     for (int i = 0; i < K; ++i) a.set(i, c[i]);
 }
 
-// Sort C keys ascending in registers (bitonic sorting network, C a power of 2).
+// Sort C keys ascending in registers (Batcher's odd-even merge sort, C a power
+// of 2: 19 compare-exchanges for 8 keys, 63 for 16, where the bitonic network
+// takes 24 and 80).
 template <int C>
 __device__ __forceinline__ void sort_keys(double (&a)[C]) {
 #pragma unroll
-    for (int k = 2; k <= C; k <<= 1) {
+    for (int p = 1; p < C; p <<= 1) {
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int k = p; k > 0; k >>= 1) {
 #pragma unroll
             for (int i = 0; i < C; ++i) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const double x = a[i], y = a[l];
-                    const double lo = __builtin_fmin(x, y), hi = __builtin_fmax(x, y);
-                    a[i] = (i & k) == 0 ? lo : hi;
-                    a[l] = (i & k) == 0 ? hi : lo;
+                // i joins i + k where i lies in the lower half of its group
+                // of 2k (counted from k mod p) and both in one block of 2p
+                if (i >= k % p && ((i - k % p) / k) % 2 == 0 && i + k < C &&
+                    i / (2 * p) == (i + k) / (2 * p)) {
+                    const double x = a[i], y = a[i + k];
+                    a[i] = __builtin_fmin(x, y);
+                    a[i + k] = __builtin_fmax(x, y);
                 }
             }
         }
@@ -886,7 +889,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     // (x, y, z and the filter's w), the points' indices and the candidate
     // queues; before the walk the whole block is the scratch in which a
     // longer list is sorted
-    constexpr int O_TILE = LCAP, O_IDX = O_TILE + TILE_PTS * 2, O_Q = O_IDX + TILE_PTS / 2;
+    constexpr int O_TILE = LCAP, O_IDX = O_TILE + (FILLER + 1) * 2, O_Q = O_IDX + (FILLER + 1) / 2;
     constexpr int RAW = O_Q + CQ * 64 / 8;
     __shared__ __align__(16) uint64_t s_raw[WPB][RAW];
     __shared__ Node s_nodes[WPB][SB];
@@ -966,6 +969,10 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     // (periodic) farthest coordinate of a query from c
     const float qfar = PER ? fmaxf(fmaxf(fabsf(mx), fabsf(my)), fabsf(mz)) : 0.0f;
     if (h == 0) tile[q] = make_float4(-2.0f * mx, -2.0f * my, -2.0f * mz, 1.0f);
+    if (lane == 0) {
+        tile[FILLER] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+        tidx[FILLER] = -1;
+    }
     wave_lds_sync();
     float bq[4];
 #pragma unroll
@@ -983,7 +990,10 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
     lds_u8 *const q0 = (lds_u8 *)(reinterpret_cast<uint8_t *>(L + O_Q) + lane);
     lds_u8 *qp = q0;
-    const lds_u8 *const qlim = q0 + 64 * (CQ - CH);
+    // every slot that holds no candidate names the filler, whose key is the
+    // padding key, so a drain takes whole rounds without looking at the count
+#pragma unroll
+    for (int i = 0; i < CQ; ++i) q0[64 * i] = FILLER;
 
     // the group's k-th distance: an upper bound of the query's final k-th
     // the walk's radius of this leaf: the k-th distance of each of its
@@ -1005,21 +1015,17 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         // a scalar trip count (a loop on a ballot compiles to a divergent
         // loop, whose exit handling copies the list every round)
         const int nr = uni(wave_max_i(qn));
-        for (int c = 0; c < nr; c += 8) {
+        for (lds_u8 *qc = q0; qc < q0 + 64 * nr; qc += 64 * 8) {
             rounds += 8;
             double ch[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                // slots are read unconditionally (branches around the reads
-                // would make the compiler copy the list)
-                // (a slot past the lane's count holds a stale byte: still a
-                // tile position, and its key is replaced by the padding key)
-                const int slot = min(c + u, CQ - 1);
-                const int qv = q0[64 * slot];
+                const int qv = qc[64 * u];
+                qc[64 * u] = FILLER;
                 const float4 s = tile[qv];
                 const float dd = dist2_m<PER>(me.x, me.y, me.z, s.x, s.y, s.z, Lp, Lh);
                 const double kk = key_of(dd, tidx[qv]);
-                ch[u] = (c + u < qn && (!LO || kk > lo)) ? kk : pad;
+                ch[u] = (!LO || kk > lo) ? kk : pad;
             }
             sort_keys<8>(ch);
             merge_chunk<K, 8>(best, ch);
@@ -1122,7 +1128,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
 #pragma unroll
                 for (int u = 0; u < C; ++u) {
                     const int j = j0 + (u << lgS) + h;
-                    const int jj = min(j, TILE_PTS - 1);
+                    const int jj = min(j, FILLER);
                     const float4 p = tile[jj];
                     const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
                     const double kk = key_of(dd, tidx[jj]);
@@ -1130,7 +1136,6 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
                 }
                 sort_keys<C>(ch);
                 merge_chunk<K, C>(best, ch);
-                steps += C;
             }
             npts = 0;
         } else {
@@ -1138,6 +1143,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         }
         for (int p0 = 0; p0 < npts; p0 += HALF) {
             const int m = min(HALF, npts - p0);
+            steps += (unsigned)((m + 15) >> 4);
             unsigned wd[4] = {0, 0, 0, 0};
             bool dense = bad;
             float thr = kth;
@@ -1154,30 +1160,23 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             else if (lgS == 1) filter_words<2, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
             else filter_words<4, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
             // queue the hits word by word, lowest position first; the queue is
-            // drained when a lane's is nearly full and after the batch's last
-            // word
+            // drained before a word that would overflow some lane's, and
+            // after the batch's last word
             const int W = 4 >> lgS;
-            for (int k = 0; k < W; ++k) {
+            for (int k = 0; k <= W; ++k) {
                 unsigned M = wd[0];
                 wd[0] = wd[1];
                 wd[1] = wd[2];
                 wd[2] = wd[3];
-                const int n = uni(wave_max_i(__popc(M)));
+                wd[3] = 0;
+                const bool full = __ballot(qp + 64 * __popc(M) > q0 + 64 * CQ) != 0;
+                if (full || (k == W && p0 + HALF >= npts)) drain();
                 const int pb = p0 + W * h + k;
-                const bool last = k == W - 1 && p0 + HALF >= npts;
-                int it = 0;
-                do {
-                    const int e = min(n, it + CH);
-                    for (; it < e; ++it) {
-                        // (written always, kept only if there is a hit: at
-                        // most CH positions from qp <= qlim, the slot exists)
-                        *qp = (uint8_t)(pb + ((__ffs((int)M) - 1) << 2));
-                        qp += M ? 64 : 0;
-                        M &= M - 1u;
-                    }
-                    if (__ballot(qp > qlim) != 0 || (last && it >= n)) drain();
-                } while (it < n);
-                steps += (unsigned)n;
+                while (M) {
+                    *qp = (uint8_t)(pb + ((__ffs((int)M) - 1) << 2));
+                    qp += 64;
+                    M &= M - 1u;
+                }
             }
             if (p0 + HALF < npts) kth = group_kth();
         }
