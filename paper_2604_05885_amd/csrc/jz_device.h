@@ -213,6 +213,8 @@ constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1, 0, 3, 2]
 constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2, 3, 0, 1]
 constexpr int DPP_HALF_MIRROR = 0x141; // lane i <-> 7 - i inside each 8
 constexpr int DPP_MIRROR = 0x140;      // lane i <-> 15 - i inside each 16
+constexpr int DPP_MIRROR4 = 0x1B;      // quad_perm [3, 2, 1, 0]
+constexpr int DPP_XOR8 = 0x128;        // row_ror:8
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v) {
     return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);

@@ -40,11 +40,8 @@ __device__ __forceinline__ uint64_t list_key(int2 e) {
     return ((uint64_t)(uint32_t)e.y << 32) | (uint32_t)e.x;  // r_low >= 0: bits order as floats
 }
 
-// Stage a receiver's list in LDS and sort it ascending by (r_low, source).
-__device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L) {
-    int M = 1;
-    while (M < len) M <<= 1;
-    for (int i = lane_id(); i < M; i += 64) L[i] = i < len ? list_key(src[i]) : ~0ull;
+// Sort the M keys (a power of 2) of L ascending.
+__device__ void sort_lds(uint64_t *L, int M) {
     wave_lds_sync();
     for (int k = 2; k <= M; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -61,6 +58,14 @@ __device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L)
             wave_lds_sync();
         }
     }
+}
+
+// Stage a receiver's list in LDS and sort it ascending by (r_low, source).
+__device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L) {
+    int M = 1;
+    while (M < len) M <<= 1;
+    for (int i = lane_id(); i < M; i += 64) L[i] = i < len ? list_key(src[i]) : ~0ull;
+    sort_lds(L, M);
 }
 
 // Order a receiver's list by (r_low, source). A list of at most LCAP entries
@@ -608,6 +613,66 @@ struct TopK {
     __device__ __forceinline__ void set(int i, double x) { v[i / W][i % W] = x; }
 };
 
+// key of the lane at distance J (xor, a power of 2 below 64)
+template <int J>
+__device__ __forceinline__ double lane_xor_d(double v) {
+    if constexpr (J == 32) return swap32_d(v);
+    if constexpr (J == 16) return swap16_d(v);
+    const uint64_t b = bits_of(v);
+    int lo = (int)(uint32_t)b, hi = (int)(b >> 32);
+    if constexpr (J == 1) {
+        lo = dpp_i<DPP_XOR1>(lo);
+        hi = dpp_i<DPP_XOR1>(hi);
+    } else if constexpr (J == 2) {
+        lo = dpp_i<DPP_XOR2>(lo);
+        hi = dpp_i<DPP_XOR2>(hi);
+    } else if constexpr (J == 4) {
+        // the mirror inside 8 lanes of the mirror inside 4
+        lo = dpp_i<DPP_HALF_MIRROR>(dpp_i<DPP_MIRROR4>(lo));
+        hi = dpp_i<DPP_HALF_MIRROR>(dpp_i<DPP_MIRROR4>(hi));
+    } else {
+        lo = dpp_i<DPP_XOR8>(lo);
+        hi = dpp_i<DPP_XOR8>(hi);
+    }
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// One step of a bitonic sort of NR * 64 keys, element r * 64 + lane in x[r]:
+// pairs at distance J < 64 ordered by bit KK of the element's index.
+template <int NR, int KK, int J>
+__device__ __forceinline__ void lane_step(double (&x)[NR]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const double y = lane_xor_d<J>(x[r]);
+        const bool up = KK < 64 ? (lane & KK) == 0 : ((r * 64) & KK) == 0;
+        const bool take_min = ((lane & J) == 0) == up;
+        x[r] = (x[r] < y) == take_min ? x[r] : y;
+    }
+}
+template <int NR, int KK, int J>
+__device__ __forceinline__ void lane_merge(double (&x)[NR]) {
+    lane_step<NR, KK, J>(x);
+    if constexpr (J > 1) lane_merge<NR, KK, J / 2>(x);
+}
+// NR * 64 keys (NR = 1 or 2) sorted ascending across the wave: 21 or 28 steps
+// of register exchanges, no LDS round trip between them
+template <int NR>
+__device__ __forceinline__ void lane_sort(double (&x)[NR]) {
+    lane_merge<NR, 2, 1>(x);
+    lane_merge<NR, 4, 2>(x);
+    lane_merge<NR, 8, 4>(x);
+    lane_merge<NR, 16, 8>(x);
+    lane_merge<NR, 32, 16>(x);
+    lane_merge<NR, 64, 32>(x);
+    if constexpr (NR == 2) {
+        const double lo = __builtin_fmin(x[0], x[1]), hi = __builtin_fmax(x[0], x[1]);
+        x[0] = lo;
+        x[1] = hi;
+        lane_merge<NR, 128, 32>(x);
+    }
+}
+
 // Insert key into the ascending list b (the largest entry falls off).
 // Inserting the padding key leaves b unchanged, so callers insert
 // unconditionally instead of branching. Each slot computes the carried
@@ -911,10 +976,10 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const Node a = leaves[A];
     uint64_t *L = s_raw[w];
     // The leaf's query points: all its points, or, with separate point types
-    // (qry_lo > 0), those with index >= qry_lo; query j sits at leaf
+    // (scnt0 given), those with index >= qry_lo; query j sits at leaf
     // position sel[j] (selected through the LDS queue area, unused so far).
     int acount = uni(a.count);
-    const bool types = qry_lo > 0;
+    const bool types = scnt0 != nullptr;
     const uint8_t *sel = reinterpret_cast<const uint8_t *>(L + O_Q);
     if (types) {
         const bool isq = lane < acount && __float_as_int(pts[a.start + lane].w) >= qry_lo;
@@ -948,7 +1013,6 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     int *tidx = reinterpret_cast<int *>(L + O_IDX);
     Node *nb = s_nodes[w];
     int *sc = s_sc[w];  // source points of each batch source
-    const bool staged = stage_list(gl, len, L, min(sort_cap, prev_pow2(RAW)), presorted);
 
     const double pad = __builtin_bit_cast(double, PAD_KEY);
     TopK<K> best;
@@ -969,10 +1033,6 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     // (periodic) farthest coordinate of a query from c
     const float qfar = PER ? fmaxf(fmaxf(fabsf(mx), fabsf(my)), fabsf(mz)) : 0.0f;
     if (h == 0) tile[q] = make_float4(-2.0f * mx, -2.0f * my, -2.0f * mz, 1.0f);
-    if (lane == 0) {
-        tile[FILLER] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-        tidx[FILLER] = -1;
-    }
     wave_lds_sync();
     float bq[4];
 #pragma unroll
@@ -990,10 +1050,6 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
     lds_u8 *const q0 = (lds_u8 *)(reinterpret_cast<uint8_t *>(L + O_Q) + lane);
     lds_u8 *qp = q0;
-    // every slot that holds no candidate names the filler, whose key is the
-    // padding key, so a drain takes whole rounds without looking at the count
-#pragma unroll
-    for (int i = 0; i < CQ; ++i) q0[64 * i] = FILLER;
 
     // the group's k-th distance: an upper bound of the query's final k-th
     // the walk's radius of this leaf: the k-th distance of each of its
@@ -1033,6 +1089,101 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         qp = q0;
     };
 
+    // The receiving leaf itself comes first (its r_low is 0): its source
+    // points meet an empty top-k, where every point is accepted, so they are
+    // merged in sorted chunks instead of being queued (lane h of a query's S
+    // takes positions h, h + S, ...).
+    int own = acount;
+    if (types) {
+        const float4 p = pts[a.start + min(lane, uni(a.count) - 1)];
+        const bool real = lane < a.count && __float_as_int(p.w) < src_hi;
+        const uint64_t rm = __ballot(real);
+        own = uni((int)__popcll(rm));
+        if (real) {
+            const int pos = (int)__popcll(rm & lanemask_lt());
+            tile[pos] = p;
+            tidx[pos] = __float_as_int(p.w);
+        }
+    } else if (act && h == 0) {
+        tile[q] = me;
+        tidx[q] = __float_as_int(me.w);
+    }
+    wave_lds_sync();
+    {
+        constexpr int C = K < 8 ? next_pow2(K) : (K <= 16 ? 8 : 16);
+        for (int j0 = 0; j0 < own; j0 += C << lgS) {
+            double ch[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const int j = j0 + (u << lgS) + h;
+                const float4 p = tile[j];
+                const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
+                const double kk = key_of(dd, tidx[j]);
+                ch[u] = (j < own && (!LO || kk > lo)) ? kk : pad;
+            }
+            sort_keys<C>(ch);
+            merge_chunk<K, C>(best, ch);
+        }
+        evals += (unsigned)own * (unsigned)acount;
+        visited += own > 0;
+    }
+    wave_lds_sync();
+
+    // The rest of the list: the entries some query still reaches with the
+    // radii that the own leaf left, put in r_low order in L (at 2^24 clustered
+    // points and k = 16 a fifth of the walk's 155 entries per leaf, so one or
+    // two keys per lane, sorted in registers). Where more than LCAP are left,
+    // the whole list is ordered (stage_list) or read as it is.
+    int nl = 0;
+    bool staged = true;
+    {
+        const float Rw = uni(wave_max_f(act ? group_kth() : -INFINITY));
+        const bool sorted = len > sort_cap && len <= presorted;
+        int2 e = make_int2(0, 0);
+        if (lane < len) e = gl[lane];
+        for (int i0 = 0; i0 < len; i0 += 64) {
+            const int2 x = e;
+            if (i0 + 64 + lane < len) e = gl[i0 + 64 + lane];
+            const bool keep = i0 + lane < len && x.x != A && __int_as_float(x.y) <= Rw;
+            const uint64_t m = __ballot(keep);
+            const int c = (int)__popcll(m);
+            if (nl + c > LCAP) {
+                nl = LCAP + 1;
+                break;
+            }
+            if (keep) L[nl + __popcll(m & lanemask_lt())] = list_key(x);
+            nl += c;
+            if (sorted && c == 0 && i0 > 0) break;
+        }
+    }
+    wave_lds_sync();
+    if (nl > LCAP) {
+        nl = len;
+        staged = stage_list(gl, len, L, min(sort_cap, prev_pow2(RAW)), presorted);
+    } else if (nl <= 64) {
+        double x[1] = {lane < nl ? __builtin_bit_cast(double, L[lane]) : pad};
+        lane_sort<1>(x);
+        L[lane] = bits_of(x[0]);
+    } else if (nl <= 128) {
+        double x[2] = {__builtin_bit_cast(double, L[lane]),
+                       lane + 64 < nl ? __builtin_bit_cast(double, L[lane + 64]) : pad};
+        lane_sort<2>(x);
+        L[lane] = bits_of(x[0]);
+        L[lane + 64] = bits_of(x[1]);
+    } else {
+        for (int i = nl + lane; i < LCAP; i += 64) L[i] = ~0ull;
+        sort_lds(L, LCAP);
+    }
+    // every slot that holds no candidate names the filler, whose key is the
+    // padding key, so a drain takes whole rounds without looking at the count
+#pragma unroll
+    for (int i = 0; i < CQ; ++i) q0[64 * i] = FILLER;
+    if (lane == 0) {
+        tile[FILLER] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+        tidx[FILLER] = -1;
+    }
+    wave_lds_sync();
+
     // The list entries of the next batch window and their Node records are
     // fetched one batch ahead (into registers of lanes 0..SB-1), so the Node
     // loads overlap the current batch's work.
@@ -1040,8 +1191,8 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     float pf_rl = INFINITY;
     bool pf_ok = false;
     float4 pf_lo = make_float4(0, 0, 0, 0), pf_hi = pf_lo;  // the Node record's two halves
-    auto fetch = [&](int t0, int cnt) __attribute__((always_inline)) {
-        pf_ok = lane < cnt && t0 + lane < len;
+    auto fetch = [&](int t0) __attribute__((always_inline)) {
+        pf_ok = lane < SB && t0 + lane < nl;
         if (pf_ok) {
             list_entry(staged, L, gl, t0 + lane, pf_src, pf_rl);
             const float4 *rec = reinterpret_cast<const float4 *>(leaves + pf_src);
@@ -1050,11 +1201,9 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             pf_sc = scnt0 ? scnt0[pf_src] : __float_as_int(pf_hi.w);
         }
     };
-    // the first batch is one source, so that the top-k fills from the
-    // nearest leaf before anything else is filtered against it
-    fetch(0, 1);
+    fetch(0);
     int t = 0;
-    while (t < len) {
+    while (t < nl) {
         float kth = group_kth();
         const float Rw = uni(wave_max_f(act ? kth : -INFINITY));
         // sources t .. t + nb_n - 1 of this batch: the window's entries with
@@ -1075,7 +1224,8 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             if (act && point_low2_m<PER>(me.x, me.y, me.z, nb[qq].lo[0], nb[qq].lo[1], nb[qq].lo[2],
                                          nb[qq].hi[0], nb[qq].hi[1], nb[qq].hi[2], Lp) <= kth)
                 needbits |= 1u << qq;
-        const unsigned any = uni(wave_or(needbits));
+        const unsigned own_bit = (unsigned)__ballot(lane < nb_n && pf_src == A);
+        const unsigned any = uni(wave_or(needbits)) & ~own_bit;
         // take the needed sources in order while their points fit the tile,
         // and stage them one after the other (lane f takes point f of a
         // source: a leaf holds at most 64 points), each with its w
@@ -1113,34 +1263,10 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         }
         bad = __ballot(bad) != 0;
         // next window
-        fetch(t + take, SB);
+        fetch(t + take);
         wave_lds_sync();
         evals += (unsigned)npts * (unsigned)acount;
-        if (t == 0) {
-            // the first source (one with r_low = 0) meets an empty top-k:
-            // every point is accepted, so its points are merged in sorted
-            // chunks instead of being queued and inserted one by one (lane h
-            // of a query's S takes positions h, h + S, ...)
-            constexpr int C = K < 8 ? next_pow2(K) : (K <= 16 ? 8 : 16);
-            visited += (unsigned)__popc(any & 1u);
-            for (int j0 = 0; j0 < npts; j0 += C << lgS) {
-                double ch[C];
-#pragma unroll
-                for (int u = 0; u < C; ++u) {
-                    const int j = j0 + (u << lgS) + h;
-                    const int jj = min(j, FILLER);
-                    const float4 p = tile[jj];
-                    const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, Lp, Lh);
-                    const double kk = key_of(dd, tidx[jj]);
-                    ch[u] = (j < npts && (!LO || kk > lo)) ? kk : pad;
-                }
-                sort_keys<C>(ch);
-                merge_chunk<K, C>(best, ch);
-            }
-            npts = 0;
-        } else {
-            visited += (unsigned)__popc(any & ((1u << take) - 1u));
-        }
+        visited += (unsigned)__popc(any & ((1u << take) - 1u));
         for (int p0 = 0; p0 < npts; p0 += HALF) {
             const int m = min(HALF, npts - p0);
             steps += (unsigned)((m + 15) >> 4);
@@ -1215,7 +1341,8 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         atomicAdd(st + 1 * STAT_SLOTS, (unsigned long long)visited);
         atomicAdd(st + 2 * STAT_SLOTS, (unsigned long long)rounds);
         atomicAdd(st + 3 * STAT_SLOTS, (unsigned long long)steps);
-        if (len > LCAP) atomicAdd(st + (staged ? 4 : 5) * STAT_SLOTS, 1ull);
+        if (len > LCAP)
+            atomicAdd(st + (len <= max(sort_cap, presorted) ? 4 : 5) * STAT_SLOTS, 1ull);
     }
 }
 
