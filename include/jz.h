@@ -361,15 +361,15 @@ typedef struct jz_stats {
     int reruns;                      /* capacity reruns in the last call */
     int64_t insert_rounds;           /* kNN leaf stage: wave-level top-k insert rounds */
     int64_t tile_steps;              /* kNN leaf stage: blocks of 16 source points filtered */
-    int64_t lists_sorted_long;       /* kNN leaf stage: lists longer than the 256 entries staged in
-                                        LDS, put in r_low order (in the wave's LDS scratch up to
-                                        1024 entries, beforehand in HBM up to sort_max) */
-    int64_t lists_unordered;         /* kNN leaf stage: lists longer than sort_max, read unordered */
+    int64_t lists_sorted_long;       /* kNN leaf stage: lists of more than 256 entries, up to
+                                        sort_max (from 2048 on put in r_low order beforehand) */
+    int64_t lists_unordered;         /* kNN leaf stage: lists longer than sort_max, whose slices of
+                                        up to 256 entries are taken as they come */
     /* kNN lists put in r_low order in HBM before they are walked, by the sorter
      * for lists of up to 1024 entries ([0]) and by the one for longer lists, up
      * to sort_max ([1]); index p < JZ_MAX_PLANES: the lists of plane p + 1 read
      * by walk level p; index JZ_MAX_PLANES: the leaf lists read by the leaf
-     * stage (only those longer than it sorts itself, 1024 entries). */
+     * stage (only those longer than 2048 entries). */
     int64_t lists_presorted[JZ_MAX_PLANES + 1][2];
 } jz_stats;
 

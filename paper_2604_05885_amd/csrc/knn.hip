@@ -40,8 +40,11 @@ __device__ __forceinline__ uint64_t list_key(int2 e) {
     return ((uint64_t)(uint32_t)e.y << 32) | (uint32_t)e.x;  // r_low >= 0: bits order as floats
 }
 
-// Sort the M keys (a power of 2) of L ascending.
-__device__ void sort_lds(uint64_t *L, int M) {
+// Stage a receiver's list in LDS and sort it ascending by (r_low, source).
+__device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L) {
+    int M = 1;
+    while (M < len) M <<= 1;
+    for (int i = lane_id(); i < M; i += 64) L[i] = i < len ? list_key(src[i]) : ~0ull;
     wave_lds_sync();
     for (int k = 2; k <= M; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -58,14 +61,6 @@ __device__ void sort_lds(uint64_t *L, int M) {
             wave_lds_sync();
         }
     }
-}
-
-// Stage a receiver's list in LDS and sort it ascending by (r_low, source).
-__device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L) {
-    int M = 1;
-    while (M < len) M <<= 1;
-    for (int i = lane_id(); i < M; i += 64) L[i] = i < len ? list_key(src[i]) : ~0ull;
-    sort_lds(L, M);
 }
 
 // Order a receiver's list by (r_low, source). A list of at most LCAP entries
@@ -638,39 +633,56 @@ __device__ __forceinline__ double lane_xor_d(double v) {
 }
 
 // One step of a bitonic sort of NR * 64 keys, element r * 64 + lane in x[r]:
-// pairs at distance J < 64 ordered by bit KK of the element's index.
+// pairs at distance J ordered by bit KK of the element's index.
 template <int NR, int KK, int J>
-__device__ __forceinline__ void lane_step(double (&x)[NR]) {
-    const int lane = lane_id();
+__device__ __forceinline__ void lane_step(double (&x)[NR], int lane) {
+    if constexpr (J >= 64) {
+        constexpr int D = J / 64;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const double y = lane_xor_d<J>(x[r]);
-        const bool up = KK < 64 ? (lane & KK) == 0 : ((r * 64) & KK) == 0;
-        const bool take_min = ((lane & J) == 0) == up;
-        x[r] = (x[r] < y) == take_min ? x[r] : y;
+        for (int r = 0; r < NR; ++r) {
+            if (r & D) continue;
+            const bool up = ((r * 64) & KK) == 0;
+            const double lo = __builtin_fmin(x[r], x[r + D]), hi = __builtin_fmax(x[r], x[r + D]);
+            x[r] = up ? lo : hi;
+            x[r + D] = up ? hi : lo;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const double y = lane_xor_d<J>(x[r]);
+            const bool up = KK < 64 ? (lane & KK) == 0 : ((r * 64) & KK) == 0;
+            const bool take_min = ((lane & J) == 0) == up;
+            x[r] = (x[r] < y) == take_min ? x[r] : y;
+        }
     }
 }
 template <int NR, int KK, int J>
-__device__ __forceinline__ void lane_merge(double (&x)[NR]) {
-    lane_step<NR, KK, J>(x);
-    if constexpr (J > 1) lane_merge<NR, KK, J / 2>(x);
+__device__ __forceinline__ void lane_merge(double (&x)[NR], int lane) {
+    lane_step<NR, KK, J>(x, lane);
+    if constexpr (J > 1) lane_merge<NR, KK, J / 2>(x, lane);
 }
-// NR * 64 keys (NR = 1 or 2) sorted ascending across the wave: 21 or 28 steps
-// of register exchanges, no LDS round trip between them
+// NR * 64 keys of L (the entries from n on taken as padding) sorted ascending
+// across the wave: 21, 28 or 36 steps of register exchanges for NR = 1, 2, 4,
+// with no LDS round trip between them
 template <int NR>
-__device__ __forceinline__ void lane_sort(double (&x)[NR]) {
-    lane_merge<NR, 2, 1>(x);
-    lane_merge<NR, 4, 2>(x);
-    lane_merge<NR, 8, 4>(x);
-    lane_merge<NR, 16, 8>(x);
-    lane_merge<NR, 32, 16>(x);
-    lane_merge<NR, 64, 32>(x);
-    if constexpr (NR == 2) {
-        const double lo = __builtin_fmin(x[0], x[1]), hi = __builtin_fmax(x[0], x[1]);
-        x[0] = lo;
-        x[1] = hi;
-        lane_merge<NR, 128, 32>(x);
-    }
+__device__ __forceinline__ void lane_sort(uint64_t *L, int n) {
+    // (opaque, so that the steps' lane masks are not kept in registers)
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));
+    double x[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        x[r] = __builtin_bit_cast(double, r * 64 + lane < n ? L[r * 64 + lane] : PAD_KEY);
+    lane_merge<NR, 2, 1>(x, lane);
+    lane_merge<NR, 4, 2>(x, lane);
+    lane_merge<NR, 8, 4>(x, lane);
+    lane_merge<NR, 16, 8>(x, lane);
+    lane_merge<NR, 32, 16>(x, lane);
+    lane_merge<NR, 64, 32>(x, lane);
+    if constexpr (NR >= 2) lane_merge<NR, 128, 64>(x, lane);
+    if constexpr (NR >= 4) lane_merge<NR, 256, 128>(x, lane);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) L[r * 64 + lane] = bits_of(x[r]);
 }
 
 // Insert key into the ascending list b (the largest entry falls off).
@@ -692,7 +704,9 @@ __device__ __forceinline__ void topk_insert(TopK<K> &b, double key) {
     }
 }
 
-constexpr int SB = 16;        // source leaves examined per batch
+// Leaf lists longer than this (and up to sort_max) are put in r_low order in
+// HBM before the leaf stage; shorter ones it orders itself, as far as needed.
+constexpr int LEAF_PRESORT = 2048;
 constexpr int TILE_PTS = 255; // source points staged per batch (positions fit a byte)
 constexpr int FILLER = 255;   // tile position of a point at infinity with the padding index
 constexpr int HALF = 128;     // tile positions filtered at a time (32 blocks of 4 per lane row)
@@ -895,11 +909,18 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // of every staged tile, keep their own top-k, and prune with the smallest
 // k-th distance of the group (the merged k-th can only be smaller), and their
 // lists are merged at the end.
-// Source leaves are taken in r_low order, in batches: the Node records of up
-// to SB sources are read together; each lane marks the sources its query can
-// still reach (point-to-box bound <= the group's k-th distance); the points of
-// the sources some lane needs are staged together in one LDS tile. The walk
-// stops at the first source whose r_low exceeds every query's k-th distance.
+// The leaf's own points come first; then the list's entries within the largest
+// radius that is left, in r_low order, their points staged in one LDS tile in
+// batches of what fits it. After the first batch every entry's box is tested
+// against all queries (point-to-box bound <= the group's k-th distance), and
+// the entries that no query needs are dropped. The walk stops at the first
+// source whose r_low exceeds every query's k-th distance.
+// The tests run with one entry per lane and the queries broadcast: with one
+// query per lane and the entries broadcast in windows of 16, each window waited
+// for its Node records and retested what the tile had no room for, and single
+// waves with 8300 reachable boxes and no needed one took the whole 1.4 ms of
+// the kernel at 10^6 clustered points, k = 8 (now 0.67 ms; 2^24 points, k = 16:
+// 7.48 -> 7.42 ms; 2^21 uniform points, k = 30: 1.69 -> 1.58 ms).
 //
 // Which of the tile's points may belong to a query's list is decided on the
 // matrix cores: a filter on approximate distances that never drops a point
@@ -940,8 +961,9 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // out_stride entries.
 template <int K, bool LO, bool PER>
 __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
-    const int2 *__restrict__ seg, int2 *__restrict__ list, const Node *__restrict__ leaves,
-    const float4 *__restrict__ pts, int n_leaves, const int *__restrict__ leaf_base,
+    const int2 *__restrict__ seg, const int2 *__restrict__ list,
+    const Node *__restrict__ leaves, const float4 *__restrict__ pts, int n_leaves,
+    const int *__restrict__ leaf_base,
     int32_t *__restrict__ out_idx, float *__restrict__ out_d2,
     unsigned long long *__restrict__ stats, const unsigned long long *__restrict__ overflow,
     int sort_cap, int presorted, int out_stride, int col0, int kw,
@@ -957,8 +979,6 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     constexpr int O_TILE = LCAP, O_IDX = O_TILE + (FILLER + 1) * 2, O_Q = O_IDX + (FILLER + 1) / 2;
     constexpr int RAW = O_Q + CQ * 64 / 8;
     __shared__ __align__(16) uint64_t s_raw[WPB][RAW];
-    __shared__ Node s_nodes[WPB][SB];
-    __shared__ int s_sc[WPB][SB];
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     // the first waves take the leaves with lists longer than first_len (in
     // `first`), the others every leaf in order except those
@@ -1006,13 +1026,11 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         }
     }
     const int2 sg = seg[A];
-    int2 *gl = list + uni(sg.x);
+    const int2 *gl = list + uni(sg.x);
     const int len = uni(sg.y);
     float4 *tile = reinterpret_cast<float4 *>(L + O_TILE);
     const float *tilef = reinterpret_cast<const float *>(tile);
     int *tidx = reinterpret_cast<int *>(L + O_IDX);
-    Node *nb = s_nodes[w];
-    int *sc = s_sc[w];  // source points of each batch source
 
     const double pad = __builtin_bit_cast(double, PAD_KEY);
     TopK<K> best;
@@ -1129,144 +1147,134 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     }
     wave_lds_sync();
 
-    // The rest of the list: the entries some query still reaches with the
-    // radii that the own leaf left, put in r_low order in L (at 2^24 clustered
-    // points and k = 16 a fifth of the walk's 155 entries per leaf, so one or
-    // two keys per lane, sorted in registers). Where more than LCAP are left,
-    // the whole list is ordered (stage_list) or read as it is.
-    int nl = 0;
-    bool staged = true;
-    {
-        const float Rw = uni(wave_max_f(act ? group_kth() : -INFINITY));
-        const bool sorted = len > sort_cap && len <= presorted;
-        int2 e = make_int2(0, 0);
-        if (lane < len) e = gl[lane];
-        for (int i0 = 0; i0 < len; i0 += 64) {
-            const int2 x = e;
-            if (i0 + 64 + lane < len) e = gl[i0 + 64 + lane];
-            const bool keep = i0 + lane < len && x.x != A && __int_as_float(x.y) <= Rw;
-            const uint64_t m = __ballot(keep);
-            const int c = (int)__popcll(m);
-            if (nl + c > LCAP) {
-                nl = LCAP + 1;
-                break;
+    // The rest of the list, in slices of at most LCAP entries within the
+    // largest radius the queries have left (after the own leaf, 47 of the 155
+    // entries of an average leaf at k = 16), each put in r_low order in L.
+    // Almost every leaf has one slice, sorted in registers.
+    const bool sorted = len > LEAF_PRESORT && len <= presorted;
+    bool fresh = true;  // no batch has run yet
+    for (int i0 = 0; i0 < len;) {
+        int nl = 0;
+        {
+            const float Rw = uni(wave_max_f(act ? group_kth() : -INFINITY));
+            int2 e = make_int2(0, 0);
+            if (i0 + lane < len) e = gl[i0 + lane];
+            while (i0 < len && nl <= LCAP - 64) {
+                const int2 x = e;
+                if (i0 + 64 + lane < len) e = gl[i0 + 64 + lane];
+                const bool keep = i0 + lane < len && x.x != A && __int_as_float(x.y) <= Rw;
+                const uint64_t m = __ballot(keep);
+                if (keep) L[nl + __popcll(m & lanemask_lt())] = list_key(x);
+                nl += (int)__popcll(m);
+                // (in r_low order, and not just the own leaf: nothing follows)
+                if (sorted && i0 > 0 && m == 0) i0 = len;
+                i0 += 64;
             }
-            if (keep) L[nl + __popcll(m & lanemask_lt())] = list_key(x);
-            nl += c;
-            if (sorted && c == 0 && i0 > 0) break;
-        }
-    }
-    wave_lds_sync();
-    if (nl > LCAP) {
-        nl = len;
-        staged = stage_list(gl, len, L, min(sort_cap, prev_pow2(RAW)), presorted);
-    } else if (nl <= 64) {
-        double x[1] = {lane < nl ? __builtin_bit_cast(double, L[lane]) : pad};
-        lane_sort<1>(x);
-        L[lane] = bits_of(x[0]);
-    } else if (nl <= 128) {
-        double x[2] = {__builtin_bit_cast(double, L[lane]),
-                       lane + 64 < nl ? __builtin_bit_cast(double, L[lane + 64]) : pad};
-        lane_sort<2>(x);
-        L[lane] = bits_of(x[0]);
-        L[lane + 64] = bits_of(x[1]);
-    } else {
-        for (int i = nl + lane; i < LCAP; i += 64) L[i] = ~0ull;
-        sort_lds(L, LCAP);
-    }
-    // every slot that holds no candidate names the filler, whose key is the
-    // padding key, so a drain takes whole rounds without looking at the count
-#pragma unroll
-    for (int i = 0; i < CQ; ++i) q0[64 * i] = FILLER;
-    if (lane == 0) {
-        tile[FILLER] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-        tidx[FILLER] = -1;
-    }
-    wave_lds_sync();
-
-    // The list entries of the next batch window and their Node records are
-    // fetched one batch ahead (into registers of lanes 0..SB-1), so the Node
-    // loads overlap the current batch's work.
-    int pf_src = 0, pf_sc = 0;
-    float pf_rl = INFINITY;
-    bool pf_ok = false;
-    float4 pf_lo = make_float4(0, 0, 0, 0), pf_hi = pf_lo;  // the Node record's two halves
-    auto fetch = [&](int t0) __attribute__((always_inline)) {
-        pf_ok = lane < SB && t0 + lane < nl;
-        if (pf_ok) {
-            list_entry(staged, L, gl, t0 + lane, pf_src, pf_rl);
-            const float4 *rec = reinterpret_cast<const float4 *>(leaves + pf_src);
-            pf_lo = rec[0];
-            pf_hi = rec[1];
-            pf_sc = scnt0 ? scnt0[pf_src] : __float_as_int(pf_hi.w);
-        }
-    };
-    fetch(0);
-    int t = 0;
-    while (t < nl) {
-        float kth = group_kth();
-        const float Rw = uni(wave_max_f(act ? kth : -INFINITY));
-        // sources t .. t + nb_n - 1 of this batch: the window's entries with
-        // r_low <= Rw (a prefix, the list being sorted by r_low)
-        const bool inb = pf_ok && (!staged || pf_rl <= Rw);
-        const uint64_t inmask = __ballot(inb);
-        const int nb_n = __ffsll((unsigned long long)(~inmask)) - 1;
-        if (nb_n == 0) break;
-        if (lane < nb_n) {
-            float4 *rec = reinterpret_cast<float4 *>(nb + lane);
-            rec[0] = pf_lo;
-            rec[1] = pf_hi;
-            sc[lane] = pf_sc;
         }
         wave_lds_sync();
-        unsigned needbits = 0;
-        for (int qq = 0; qq < nb_n; ++qq)
-            if (act && point_low2_m<PER>(me.x, me.y, me.z, nb[qq].lo[0], nb[qq].lo[1], nb[qq].lo[2],
-                                         nb[qq].hi[0], nb[qq].hi[1], nb[qq].hi[2], Lp) <= kth)
-                needbits |= 1u << qq;
-        const unsigned own_bit = (unsigned)__ballot(lane < nb_n && pf_src == A);
-        const unsigned any = uni(wave_or(needbits)) & ~own_bit;
-        // take the needed sources in order while their points fit the tile,
-        // and stage them one after the other (lane f takes point f of a
-        // source: a leaf holds at most 64 points), each with its w
-        int take = nb_n, npts = 0;
+        if (nl <= 64) lane_sort<1>(L, nl);
+        else if (nl <= 128) lane_sort<2>(L, nl);
+        else lane_sort<4>(L, nl);
+        // every queue slot that holds no candidate names the filler, whose key
+        // is the padding key, so a drain takes whole rounds without looking at
+        // the count
+#pragma unroll
+        for (int i = 0; i < CQ; ++i) q0[64 * i] = FILLER;
+        if (lane == 0) {
+            tile[FILLER] = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
+            tidx[FILLER] = -1;
+        }
+        wave_lds_sync();
+    // The slice in chunks of 64 entries, one per lane, each staged in batches
+    // of what fits the tile. The nearest batch runs unseen; before the others,
+    // with the radii it leaves, every lane tests its entry's box against all
+    // queries, and the entries that no query reaches are dropped.
+    for (int c0 = 0; c0 < nl; c0 += 64) {
+        uint64_t pend = nl - c0 >= 64 ? ~0ull : (1ull << (nl - c0)) - 1ull;
+        float4 n_lo = make_float4(0, 0, 0, 0), n_hi = n_lo;  // the entry's Node record
+        float e_rl = INFINITY;
+        int e_sc = 0;
+        if (lane < nl - c0) {
+            const uint64_t e = L[c0 + lane];
+            const int src = (int)(uint32_t)e;
+            e_rl = __uint_as_float((uint32_t)(e >> 32));
+            const float4 *rec = reinterpret_cast<const float4 *>(leaves + src);
+            n_lo = rec[0];
+            n_hi = rec[1];
+            e_sc = types ? scnt0[src] : __float_as_int(n_hi.w);
+        }
+        bool tested = false;
+        while (pend) {
+        float kth = group_kth();
+        pend &= __ballot(e_rl <= uni(wave_max_f(act ? kth : -INFINITY)));
+        if (!fresh && !tested && pend) {
+            if (h == 0) tile[q] = make_float4(me.x, me.y, me.z, act ? kth : -1.0f);
+            wave_lds_sync();
+            bool need = false;
+#pragma unroll 4
+            for (int i = 0; i < acount; ++i) {
+                const float4 p = tile[i];
+                need |= point_low2_m<PER>(p.x, p.y, p.z, n_lo.x, n_lo.y, n_lo.z, n_hi.x, n_hi.y,
+                                          n_hi.z, Lp) <= p.w;
+            }
+            pend &= __ballot(need);
+            tested = true;
+            wave_lds_sync();
+        }
+        fresh = false;
+        // take entries in order while their points fit the tile: position f
+        // of the tile is point f + delta, delta changing with the source
+        // (several loads per lane in flight; separate point types need the
+        // packing of each leaf's source points and go source by source)
+        int npts = 0;
         bool bad = qbad;
-        for (unsigned rest = any; rest;) {
-            const int qq = __ffs((int)rest) - 1;
-            rest &= rest - 1u;
-            const int nsc = uni(sc[qq]);
-            if (npts + nsc > TILE_PTS) {
-                take = qq;
-                break;
-            }
-            const int cnt = uni(nb[qq].count), st = uni(nb[qq].start);
-            if (lane < cnt) {
-                const float4 p = pts[st + lane];
-                const float dx = wrap_diff<PER>(p.x - cx, Lp, Lh);
-                const float dy = wrap_diff<PER>(p.y - cy, Lp, Lh);
-                const float dz = wrap_diff<PER>(p.z - cz, Lp, Lh);
-                const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
-                int pos = npts + lane;
-                bool real = true;
-                if (types) {
-                    // only the source points, packed
-                    real = __float_as_int(p.w) < src_hi;
-                    pos = npts + (int)__popcll(__ballot(real) & lanemask_lt());
+        auto stage = [&](const float4 &p, int pos) __attribute__((always_inline)) {
+            const float dx = wrap_diff<PER>(p.x - cx, Lp, Lh);
+            const float dy = wrap_diff<PER>(p.y - cy, Lp, Lh);
+            const float dz = wrap_diff<PER>(p.z - cz, Lp, Lh);
+            const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
+            tile[pos] = make_float4(p.x, p.y, p.z, pw);
+            tidx[pos] = __float_as_int(p.w);
+            bad = bad || !(pw < FILTER_BIG);
+        };
+        const int e_st = __float_as_int(n_lo.w);
+        int at[4] = {0, 0, 0, 0};
+        while (pend) {
+            const int qq = __ffsll((unsigned long long)pend) - 1;
+            const int c = __builtin_amdgcn_readlane(e_sc, qq);
+            if (npts + c > TILE_PTS) break;
+            pend &= pend - 1ull;
+            ++visited;
+            const int st = __builtin_amdgcn_readlane(e_st, qq);
+            if (types) {
+                if (lane < __builtin_amdgcn_readlane(__float_as_int(n_hi.w), qq)) {
+                    const float4 p = pts[st + lane];
+                    const bool real = __float_as_int(p.w) < src_hi;
+                    const int pos = npts + (int)__popcll(__ballot(real) & lanemask_lt());
+                    if (real) stage(p, pos);
                 }
-                if (real) {
-                    tile[pos] = make_float4(p.x, p.y, p.z, pw);
-                    tidx[pos] = __float_as_int(p.w);
-                    bad = bad || !(pw < FILTER_BIG);
-                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (u * 64 + lane >= npts) at[u] = st - npts;
             }
-            npts += nsc;
+            npts += c;
+        }
+        if (!types) {
+#pragma unroll
+            for (int v = 0; v < 4; v += 2) {
+                float4 p[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if ((v + u) * 64 + lane < npts) p[u] = pts[at[v + u] + (v + u) * 64 + lane];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if ((v + u) * 64 + lane < npts) stage(p[u], (v + u) * 64 + lane);
+            }
         }
         bad = __ballot(bad) != 0;
-        // next window
-        fetch(t + take);
         wave_lds_sync();
         evals += (unsigned)npts * (unsigned)acount;
-        visited += (unsigned)__popc(any & ((1u << take) - 1u));
         for (int p0 = 0; p0 < npts; p0 += HALF) {
             const int m = min(HALF, npts - p0);
             steps += (unsigned)((m + 15) >> 4);
@@ -1307,7 +1315,8 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             if (p0 + HALF < npts) kth = group_kth();
         }
         wave_lds_sync();
-        t += take;
+        }
+    }
     }
     // merge the partial lists of a query's lanes
     if (lgS >= 1) {
@@ -1346,7 +1355,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     }
 }
 
-typedef void (*leaf_fn)(const int2 *, int2 *, const Node *, const float4 *, int, const int *,
+typedef void (*leaf_fn)(const int2 *, const int2 *, const Node *, const float4 *, int, const int *,
                         int32_t *, float *, unsigned long long *, const unsigned long long *, int,
                         int, int, int, int, const int *, int, int, float, const float *,
                         const int *, const unsigned long long *, int);
@@ -1510,7 +1519,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                 joint ? t->src_cnt[p].as<int>() : nullptr, period,
                 p == 0 ? d_rleaf.as<float>() : nullptr);
         }
-        presort(lists[0].as<int2>(), segs[0].as<int2>(), t->L[0], leaf_cap,
+        presort(lists[0].as<int2>(), segs[0].as<int2>(), t->L[0], LEAF_PRESORT,
                 ctr + c_long + 2 * JZ_MAX_PLANES);
         k_long_first<<<(unsigned)((t->L[0] + 63) / 64), 64, 0, s>>>(
             segs[0].as<int2>(), (int)t->L[0], leaf_cap, d_first.as<int>(), ctr + c_first);
