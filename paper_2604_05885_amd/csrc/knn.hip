@@ -969,7 +969,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     int sort_cap, int presorted, int out_stride, int col0, int kw,
     const int *__restrict__ scnt0, int src_hi, int qry_lo, float Lp,
     const float *__restrict__ rleaf, const int *__restrict__ first,
-    const unsigned long long *__restrict__ n_first, int first_len) {
+    const unsigned long long *__restrict__ n_first, int first_len, int row_align) {
     // Lp: period of the cube (PER), Lh its half
     const float Lh = 0.5f * Lp;
     // one block per wave: the staged list (LCAP entries), the point tile
@@ -1334,6 +1334,30 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     if (act && h == 0) {
         int32_t *oi = out_idx + row * out_stride + col0;
         float *od = out_d2 + row * out_stride + col0;
+        // in words of V entries where the buffers and the row length allow
+        // (row_align: bytes every row start is a multiple of): a row is a
+        // place of its own in memory, so every store passes over 64 lines,
+        // and 32 four-byte ones per query took 7.46 ms of kernel where 8 of
+        // 16 bytes take 7.21 (2^24 points, k = 16)
+        constexpr int V = K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1);
+        if (V > 1 && kw == K && row_align >= 4 * V) {
+            typedef int vi __attribute__((ext_vector_type(V)));
+            typedef float vf __attribute__((ext_vector_type(V)));
+#pragma unroll
+            for (int r = 0; r < K; r += V) {
+                vi wi;
+                vf wf;
+#pragma unroll
+                for (int u = 0; u < V; ++u) {
+                    const uint64_t e = bits_of(best.get(r + u));
+                    const bool none = e == PAD_KEY;
+                    wi[u] = none ? -1 : (int)(uint32_t)e - base;
+                    wf[u] = none ? INFINITY : __uint_as_float((uint32_t)(e >> 32));
+                }
+                *reinterpret_cast<vi *>(oi + r) = wi;
+                *reinterpret_cast<vf *>(od + r) = wf;
+            }
+        } else
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             if (r < kw) {
@@ -1358,7 +1382,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
 typedef void (*leaf_fn)(const int2 *, const int2 *, const Node *, const float4 *, int, const int *,
                         int32_t *, float *, unsigned long long *, const unsigned long long *, int,
                         int, int, int, int, const int *, int, int, float, const float *,
-                        const int *, const unsigned long long *, int);
+                        const int *, const unsigned long long *, int, int);
 
 template <int K, bool LO, bool PER>
 leaf_fn leaf_ptr() {
@@ -1530,6 +1554,8 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
         if (ev.on) JZ_HIP(hipEventRecord(ev[1], s));
         // k <= 32: one pass; larger k: passes of 32 neighbours, each after
         // the last key of the one before
+        const uintptr_t places = (uintptr_t)idx | (uintptr_t)dist2 | 4 * (uintptr_t)k;
+        const int row_align = places & 4 ? 4 : (places & 8 ? 8 : 16);
         for (int col = 0; col < k; col += 32) {
             const leaf_fn fn = leaf_kernel(k, col, per);
             fn<<<blocks_for(n_waves, WPB), 64 * WPB, 0, s>>>(
@@ -1538,7 +1564,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                 idx, dist2, ctr + CTR_STATS, ctr + CTR_FLAG, leaf_cap, sort_max, k, col,
                 std::min(32, k - col), joint ? t->src_cnt[0].as<int>() : nullptr,
                 joint ? (int)t->n_src : INT_MAX, joint ? (int)t->n_src : 0, period,
-                d_rleaf.as<float>(), d_first.as<int>(), ctr + c_first, leaf_cap);
+                d_rleaf.as<float>(), d_first.as<int>(), ctr + c_first, leaf_cap, row_align);
             JZ_HIP(hipGetLastError());
         }
         if (ev.on) JZ_HIP(hipEventRecord(ev[2], s));
