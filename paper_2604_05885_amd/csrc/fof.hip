@@ -205,244 +205,313 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_step(
     }
 }
 
-constexpr int FSB = 8;          // source leaves per batch
-constexpr int FTILE = 128;      // source points staged per batch
+// The matrix filter over the c <= 64 points of one staged source: the lane's
+// own query's pairs as a mask over the source's points. Row m of a block of 16
+// reads point Q (m / 4) + 4 b + m % 4 (Q: a quarter of the points, rounded up
+// to 4), so that a lane row's results are one run of Q points and the four
+// rows' masks join by shifts. NG: groups of 16 queries.
+template <int NG, bool PER>
+__device__ __forceinline__ uint64_t pair_mask(const float *tilef, int c, float ac, float aL,
+                                              float Lh, const float (&bq)[4],
+                                              const float (&tg)[4]) {
+    const int lane = lane_id();
+    const int nblk = uni((c + 15) >> 4), Q = 4 * nblk;
+    const float *ap = tilef + 4 * (Q * ((lane >> 2) & 3) + (lane & 3)) + (lane >> 4);
+    unsigned wd[4] = {0, 0, 0, 0};
+    for (int b = 0; b < nblk; ++b) {
+        const float av = wrap_diff<PER>(ap[16 * b] - ac, aL, aL != 0.0f ? Lh : INFINITY);
+        v4f d[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const v4f cg = {tg[g], tg[g], tg[g], tg[g]};
+            d[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bq[g], cg, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                wd[g] = __builtin_amdgcn_alignbit(wd[g], __float_as_uint(d[g][i]), 31);
+    }
+    // rows and groups transposed: word r holds row r's bits of this lane's query
+    const auto x = __builtin_amdgcn_permlane16_swap(wd[0], wd[1], false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(wd[2], wd[3], false, false);
+    const auto u = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+    const auto v = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    const uint64_t m = (((((uint64_t)u[0] << Q | v[0]) << Q) | u[1]) << Q) | v[1];
+    return __builtin_bitreverse64(m << (64 - 4 * Q)) & (~0ull >> (64 - c));
+}
 
-// LDS slot of tile position j: permuted inside each chunk of 8 by the chunk's
-// low 3 bits (lanes reading the same position of different chunks spread
-// over the LDS banks)
-__device__ __forceinline__ int fslot(int j) { return j ^ ((j >> 3) & 7); }
-
-// Leaf stage: one wave per receiving leaf A, lanes over its points. Sources
-// (leaves B >= A) are read in batches of FSB Node records. A source is
-// skipped when A and B are both whole and already one group; a lane skips a
-// source its point cannot reach (point-to-box bound > b^2); the points of the
-// sources some lane needs are staged together in LDS, each source padded to
-// a multiple of 8 positions, with the bounding box of every 8 positions; 8
-// positions no lane can reach are skipped. Per source, every lane first
-// records which of its points link to its own point (no atomics); only if
-// some lane links are the roots of the source's points looked up, in
-// parallel, and unions made where the roots differ (a lane's own root is
-// cached; groups only ever merge, so equal roots, even looked up at different
-// times, mean already connected). Two whole leaves need only one link.
+// The links of a leaf's points to one source's (lm: a mask per lane, which may
+// hold pairs just beyond b), united where they join two groups; see k_leaf_fof.
 template <bool PER>
-__global__ __launch_bounds__(64 * WPB) void k_leaf_fof(
+__device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b0, int my,
+                                            const float4 &me, const float4 *tile, int *rootT,
+                                            int *uf, float bb, float L, float Lh, int &ra) {
+    const int lane = lane_id();
+    uint64_t linking = __ballot(lm != 0);
+    if (!linking) return;
+    auto linked = [&](int f) __attribute__((always_inline)) {
+        const float4 p = tile[f];
+        return dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, L, Lh) <= bb;
+    };
+    if (wA && wB) {
+        // both leaves are whole: a single link joins them
+        const int l0 = __ffsll((unsigned long long)linking) - 1;
+        if (uf_find_c(uf, __builtin_amdgcn_readlane(my, l0)) == uf_find_c(uf, b0)) return;
+        while (linking) {
+            const int f = lm ? __ffsll((unsigned long long)lm) - 1 : 0;
+            const uint64_t ok = __ballot(lm != 0 && linked(f));
+            if (ok) {
+                if (lane == __ffsll((unsigned long long)ok) - 1) uf_union_c(uf, my, b0 + f);
+                return;
+            }
+            lm &= lm - 1ull;
+            linking = __ballot(lm != 0);
+        }
+        return;
+    }
+    // roots of the source's points that some lane links to
+    const uint64_t want = (uint64_t)uni(wave_or((unsigned)(lm >> 32))) << 32 |
+                          uni(wave_or((unsigned)lm));
+    int rt = -1;
+    if ((want >> lane) & 1ull) rt = uf_find_c(uf, wB ? b0 : b0 + lane);
+    rootT[lane] = rt;
+    wave_lds_sync();
+    const int r0 = __builtin_amdgcn_readlane(rt, __ffsll((unsigned long long)want) - 1);
+    const uint64_t eq = __ballot(rt == r0);
+    if (lm && ra < 0) ra = uf_find_c(uf, my);
+    uint64_t com = ra == r0 ? 0ull : lm & eq, rest = lm & ~eq;
+    int last = -1;  // the last root this lane's group was joined with
+    while (__ballot((com | rest) != 0)) {
+        // each lane's next link to a group it has not joined
+        int f = 0, rj = -1;
+        if (com) {
+            f = __ffsll((unsigned long long)com) - 1;
+            com &= com - 1ull;
+            rj = r0;
+        } else {
+            while (rest) {
+                f = __ffsll((unsigned long long)rest) - 1;
+                rest &= rest - 1ull;
+                const int r = rootT[f];
+                if (r != ra && r != last) {
+                    rj = r;
+                    break;
+                }
+            }
+        }
+        if (rj >= 0 && !linked(f)) rj = -1;
+        // one lane per pair of groups joins them
+        bool first = false;
+        for (uint64_t left = __ballot(rj >= 0); left;) {
+            const int l0 = __ffsll((unsigned long long)left) - 1;
+            const int a0 = __builtin_amdgcn_readlane(ra, l0), j0 = __builtin_amdgcn_readlane(rj, l0);
+            left &= ~__ballot(rj == j0 && ra == a0);
+            first = first || lane == l0;
+        }
+        if (first) uf_union_c(uf, my, b0 + f);
+        if (rj >= 0) {
+            ra = uf_find_c(uf, min(ra, rj));
+            if (rj == r0) com = 0;
+            last = rj;
+        }
+    }
+    wave_lds_sync();
+}
+
+// Leaf stage: one wave per receiving leaf A, lanes over its points, sources
+// B >= A (a point links to the later points of a pair only).
+//
+// The leaf's own points come first: their links are a mask per lane, its
+// components are closed in registers, and one union per point joins them; a
+// leaf whose points are all connected becomes "whole" for the other waves too.
+// Then source by source (skipped when A and B are both whole and already one
+// group, or when no lane's point reaches the source's box): the next source's
+// points are loaded while the current one is worked on; a matrix filter gives
+// each lane the points its own may link to, and only a pair that would join two
+// groups is evaluated with the fixed float32 expression. Two whole leaves need
+// one link. Otherwise the roots of the source's linked points are looked up, in
+// parallel; the points under the first one's root count as one (in a dense
+// region they all are), and of the lanes that would join the same two groups
+// only one does. Groups only ever merge, so equal roots, even looked up at
+// different times, mean already connected.
+// With box tests and distances on the vector unit, and every lane walking its
+// own links (a dense source cost a lane up to 64 steps and as many lanes the
+// same compare-and-swap), the kernel took 3.63 ms at 2^24 clustered points and
+// alpha = 0.2, now 2.02; 1.03 ms at 10^6, now 0.34; 0.58 at 3 10^5, now 0.235.
+template <bool PER>
+__global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
     const int2 *__restrict__ seg, const int2 *__restrict__ list, const Node *__restrict__ leaves,
     const float4 *__restrict__ pts, int n_leaves, float b2, const float *__restrict__ b2n,
-    const int *__restrict__ whole, int *__restrict__ uf, unsigned long long *__restrict__ stats,
+    int *__restrict__ whole, int *__restrict__ uf, unsigned long long *__restrict__ stats,
     const unsigned long long *__restrict__ overflow, float L) {
     const float Lh = 0.5f * L;
-    __shared__ float4 s_tile[WPB][FTILE];
-    __shared__ float4 s_box[WPB][FTILE / 8 * 2];  // (lo, hi) of every 8 tile positions
-    __shared__ Node s_nodes[WPB][FSB];
-    __shared__ int s_offs[WPB][FSB + 1];
+    __shared__ float4 s_tile[WPB][64];
     __shared__ int s_root[WPB][64];
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     const int A = xcd_block(blk_x(), nblk_x()) * WPB + w;
     // a level of this attempt overflowed (it is rerun): nothing to do
     if (A >= n_leaves || *overflow) return;
     const Node a = leaves[A];
-    const int astart = uni(a.start);
-    const bool act = lane < uni(a.count);
+    const int astart = uni(a.start), acount = uni(a.count);
+    const bool act = lane < acount;
     const int my = astart + (act ? lane : 0);
     const float4 me = pts[my];
     const float bb = b2n ? b2n[A] : b2;
-    const int wA = uni(whole[A]);
+    bool wA = uni(ld_cached(whole + A)) != 0;
     const int2 sg = seg[A];
     const int2 *gl = list + uni(sg.x);
     const int len = uni(sg.y);
     float4 *tile = s_tile[w];
-    float4 *cbox = s_box[w];
-    Node *nb = s_nodes[w];
-    int *offs = s_offs[w];
+    const float *tilef = reinterpret_cast<const float *>(tile);
     int *rootT = s_root[w];
-    int ra = -1;  // cached root of this lane's point
-    unsigned evals = 0;
-    for (int t = 0; t < len;) {
-        const int nb_n = min(FSB, len - t);
-        const int rA = wA ? uni(uf_find_c(uf, astart)) : -1;
-        bool skip = false;
-        int wB = 0;
-        if (lane < nb_n) {
-            const int B = gl[t + lane].x;
-            const Node b = leaves[B];
-            nb[lane] = b;
-            wB = whole[B];
-            skip = wA && wB && uf_find_c(uf, b.start) == rA;
+    int ra = -1;  // this lane's point's root, as last looked up
+    unsigned long long evals = 0;
+
+    tile[lane] = me;
+    wave_lds_sync();
+    if (!wA) {
+        // the leaf's own links, exactly (both directions, as masks of lanes)
+        uint64_t adj = 0;
+        for (int f = 0; f < acount; ++f) {
+            const float4 p = tile[f];
+            const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, L, Lh);
+            adj |= dd <= bb ? 1ull << f : 0ull;
         }
-        const unsigned skipmask = (unsigned)__ballot(skip);
-        const unsigned wholemask = (unsigned)__ballot(lane < nb_n && wB);
-        wave_lds_sync();
-        unsigned needbits = 0;
-        for (int q = 0; q < nb_n; ++q)
-            if (!((skipmask >> q) & 1u) && act &&
-                point_low2_m<PER>(me.x, me.y, me.z, nb[q].lo[0], nb[q].lo[1], nb[q].lo[2],
-                                  nb[q].hi[0], nb[q].hi[1], nb[q].hi[2], L) <= bb)
-                needbits |= 1u << q;
-        const unsigned any = uni(wave_or(needbits));
-        // take needed sources in order while their (8-padded) points fit
-        int take = 0, npts = 0;
-        int o_r[FSB + 1];
-        o_r[0] = 0;
-        if (lane == 0) offs[0] = 0;
-#pragma unroll
-        for (int q = 0; q < FSB; ++q) {
-            const bool want = q < nb_n && take == q;
-            const int c = want && ((any >> q) & 1u) ? (uni(nb[q].count) + 7) & -8 : 0;
-            if (want && npts + c <= FTILE) {
-                npts += c;
-                take = q + 1;
+        if (!act) adj = 0;
+        evals += (unsigned)acount * (unsigned)acount;
+        // components: from the lowest point not yet in one, the links of all
+        // its members are added until nothing changes
+        uint64_t todo = __ballot((adj & ~(1ull << lane)) != 0);
+        int lead = lane;
+        while (todo) {
+            const int s = __ffsll((unsigned long long)todo) - 1;
+            uint64_t reach = 1ull << s, prev = 0;
+            while (reach != prev) {
+                prev = reach;
+                const uint64_t add = (reach >> lane) & 1ull ? adj : 0ull;
+                reach |= (uint64_t)uni(wave_or((unsigned)(add >> 32))) << 32 |
+                         uni(wave_or((unsigned)add));
             }
-            o_r[q + 1] = npts;
-            if (lane == 0) offs[q + 1] = npts;
+            if ((reach >> lane) & 1ull) lead = s;
+            todo &= ~reach;
+            if (reach == (acount == 64 ? ~0ull : (1ull << acount) - 1ull)) wA = true;
         }
-        // stage points (lane f takes point f of a source) and 8-position
-        // boxes; fillers lie at +inf (never within b) and stay out of boxes
-#pragma unroll
-        for (int q = 0; q < FSB; ++q) {
-            if (q < take && o_r[q + 1] > o_r[q]) {
-                const int cnt = uni(nb[q].count), st = uni(nb[q].start);
-                const int size = o_r[q + 1] - o_r[q];
-                const bool real = lane < cnt;
-                float4 p = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-                if (real) p = pts[st + lane];
-                if (lane < size) tile[fslot(o_r[q] + lane)] = p;
-                const float lx = group8_min(real ? p.x : INFINITY);
-                const float ly = group8_min(real ? p.y : INFINITY);
-                const float lz = group8_min(real ? p.z : INFINITY);
-                const float hx = group8_max(real ? p.x : -INFINITY);
-                const float hy = group8_max(real ? p.y : -INFINITY);
-                const float hz = group8_max(real ? p.z : -INFINITY);
-                if ((lane & 7) == 0 && lane < size) {
-                    // the chunk's box; lo.w: its number of real points, hi.w:
-                    // the z-index of its first position
-                    float4 *bx = cbox + ((o_r[q] + lane) >> 3) * 2;
-                    bx[0] = make_float4(lx, ly, lz, __int_as_float(min(8, max(0, cnt - lane))));
-                    bx[1] = make_float4(hx, hy, hz, __int_as_float(st + lane));
-                }
-            }
-        }
-        wave_lds_sync();
-        // 1: which tile positions link to this lane's point (a point links to
-        // the later points of a pair only). Every lane marks the chunks its
-        // point can reach (chunk box within b; a chunk box lies inside its
-        // source's box) and pops its own chunks, so a pass costs the largest
-        // per-lane chunk count, not the number of chunks any lane needs.
-        const int nch = uni(npts >> 3);
-        // periodic box: a chunk whose rounded differences to this point stay
-        // within half a period on every axis (fl(q - lo) <= h, fl(q - hi) >=
-        // -h; the rounded difference is monotone) never wraps, and its bound
-        // and distances are the open ones bit for bit; W marks the others,
-        // and the periodic forms run only where some lane has one
-        unsigned M = 0, W = 0;
-        for (int c = 0; c < nch; ++c) {
-            const float4 *bx = cbox + c * 2;
-            const float4 blo = bx[0], bhi = bx[1];
-            bool wrap = false;
-            if constexpr (PER)
-                wrap = !(me.x - blo.x <= Lh && me.x - bhi.x >= -Lh && me.y - blo.y <= Lh &&
-                         me.y - bhi.y >= -Lh && me.z - blo.z <= Lh && me.z - bhi.z >= -Lh);
-            const float lo2 =
-                (PER && __ballot(act && wrap))
-                    ? point_low2_m<PER>(me.x, me.y, me.z, blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z, L)
-                    : point_low2_m<false>(me.x, me.y, me.z, blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z,
-                                          L);
-            const bool need = act && lo2 <= bb;
-            M |= need ? (1u << c) : 0u;
-            W |= need && wrap ? (1u << c) : 0u;
-        }
-        uint64_t lk[FTILE / 64] = {};
-        const int nit = uni(wave_max_i(__popc(M)));
-        for (int it = 0; it < nit; ++it) {
-            const bool has = M != 0u;
-            const int c = has ? __ffs((int)M) - 1 : 0;
-            M &= M - 1u;
-            const int real = has ? __float_as_int(cbox[c * 2].w) : 0;
-            const int cfirst = __float_as_int(cbox[c * 2 + 1].w);
-            // the positions u that count, as a mask: u < real (a real point)
-            // and cfirst + u > my (a pair is taken from its lower point)
-            const unsigned okm = (0xffu >> (8 - real)) &
-                                 (0xffu << min(max(my - cfirst + 1, 0), 8));
-            // fslot(c * 8 + u) for u < 8 is (c * 8 | (c & 7)) ^ u
-            const int jb = c * 8 | (c & 7);
-            unsigned m8 = 0;
-            auto eval = [&](auto per_const) __attribute__((always_inline)) {
-                constexpr bool P = decltype(per_const)::value;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float4 s = tile[jb ^ u];
-                    const float dd = dist2_m<P>(me.x, me.y, me.z, s.x, s.y, s.z, L, Lh);
-                    m8 |= dd <= bb ? (1u << u) : 0u;
-                }
-            };
-            if (PER && __ballot(has && ((W >> c) & 1u)))
-                eval(std::integral_constant<bool, PER>());
-            else
-                eval(std::integral_constant<bool, false>());
-            m8 &= okm;
-#pragma unroll
-            for (int h = 0; h < FTILE / 64; ++h)
-                lk[h] |= (c >> 3) == h ? (uint64_t)m8 << ((c & 7) * 8) : 0ull;
-            evals += (unsigned)real;
-        }
-        for (int q = 0; q < take; ++q) {
-            if (!((any >> q) & 1u)) continue;
-            const bool wB = (wholemask >> q) & 1u;
-            const int f0 = uni(offs[q]), f1 = uni(offs[q + 1]);
-            const int b0 = uni(nb[q].start);
-            // this source's positions [f0, f1) of the tile link mask (f0 is a
-            // multiple of 8 and a source spans at most 64 positions)
-            const int h0 = f0 >> 6, sh = f0 & 63;
-            uint64_t lm = 0;
-#pragma unroll
-            for (int h = 0; h < FTILE / 64; ++h) {
-                if (h == h0) lm |= lk[h] >> sh;
-                if (h == h0 + 1 && sh) lm |= lk[h] << (64 - sh);
-            }
-            if (f1 - f0 < 64) lm &= (1ull << (f1 - f0)) - 1ull;
-            const uint64_t linking = __ballot(lm != 0);
-            if (!linking) continue;
-            if (wA && wB) {
-                // both leaves are whole: a single link joins them
-                const int leader = __ffsll((unsigned long long)linking) - 1;
-                if (lane == leader) uf_union_c(uf, my, b0 + __ffsll((unsigned long long)lm) - 1);
-                continue;
-            }
-            // 2: roots of the source's points that some lane links to,
-            // looked up in parallel
-            int rB = -1;
-            if (wB) {
-                rB = uf_find_c(uf, b0);
-            } else {
-                const uint64_t want = ((uint64_t)wave_or((unsigned)(lm >> 32)) << 32) |
-                                      wave_or((unsigned)lm);
-                if ((want >> lane) & 1ull) rootT[lane] = uf_find_c(uf, b0 + lane);
-            }
-            wave_lds_sync();
-            // 3: unite where the roots differ. Groups only merge, so a point
-            // whose looked-up root is one this lane has just united with is
-            // connected already.
-            if (lm) {
-                if (ra < 0) ra = uf_find_c(uf, my);
-                int last = -1;
-                while (lm) {
-                    const int f = __ffsll((unsigned long long)lm) - 1;
-                    lm &= lm - 1;
-                    const int rj = wB ? rB : rootT[f];
-                    if (rj != ra && rj != last) {
-                        uf_union_c(uf, my, b0 + f);
-                        ra = uf_find_c(uf, my);
-                        last = rj;
-                    }
-                }
-            }
-            wave_lds_sync();
-        }
-        wave_lds_sync();
-        t += take;
+        if (act && lead != lane) uf_union_c(uf, astart + lead, my);
+        if (acount == 1) wA = true;
+        // (its points' unions are done)
+        if (wA && lane == 0) st_rel(whole + A, 1);
     }
-    const int ev = wave_sum_i((int)evals);
-    if (lane == 0) atomicAdd(stats + (A & (STAT_SLOTS - 1)), (unsigned long long)ev);
+
+    // the filter's query side: lane l holds component l / 16 (x, y, z, 1) of
+    // query 16 g + l % 16 in bq[g], and minus that query's t in tg[g]
+    const float cx = uni(0.5f * a.lo[0] + 0.5f * a.hi[0]);
+    const float cy = uni(0.5f * a.lo[1] + 0.5f * a.hi[1]);
+    const float cz = uni(0.5f * a.lo[2] + 0.5f * a.hi[2]);
+    const float ac = lane < 16 ? cx : (lane < 32 ? cy : (lane < 48 ? cz : 0.0f));
+    const float aL = lane < 48 ? L : 0.0f;  // (periodic) no wrap of w
+    bool dense;
+    float bq[4], tg[4];
+    {
+        const float mx = me.x - cx, my_ = me.y - cy, mz = me.z - cz;
+        const float qn2 = mx * mx + my_ * my_ + mz * mz;
+        float thr = bb;
+        bool bad = !(qn2 < FILTER_BIG) || !(bb < FILTER_BIG);
+        if constexpr (PER) {
+            const float rt = __builtin_sqrtf(bb) * (1.0f + 0x1p-20f) + L * 0x1p-19f;
+            const float qfar = fmaxf(fmaxf(fabsf(mx), fabsf(my_)), fabsf(mz));
+            bad = bad || !(qfar + rt < Lh * (1.0f - 0x1p-10f));
+            thr = rt * rt;
+        }
+        dense = __ballot(act && bad) != 0;
+        const float t = thr * (1.0f + FILTER_E) - qn2 * (1.0f - FILTER_E) + FILTER_TINY;
+        wave_lds_sync();
+        tile[lane] = make_float4(-2.0f * mx, -2.0f * my_, -2.0f * mz, 1.0f);
+        rootT[lane] = __float_as_int(act ? -t : FILTER_BIG);
+        wave_lds_sync();
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int qq = 16 * g + (lane & 15);
+            bq[g] = tilef[4 * qq + (lane >> 4)];
+            tg[g] = __int_as_float(rootT[qq]);
+        }
+        wave_lds_sync();
+    }
+
+    for (int t0 = 0; t0 < len; t0 += 64) {
+        // up to 64 sources, one per lane
+        int e_st = 0, e_ct = 0, e_wh = 0;
+        float4 e_lo = make_float4(0, 0, 0, 0), e_hi = e_lo;
+        bool keep = false;
+        if (t0 + lane < len) {
+            const int B = gl[t0 + lane].x;
+            const float4 *rec = reinterpret_cast<const float4 *>(leaves + B);
+            e_lo = rec[0];
+            e_hi = rec[1];
+            e_st = __float_as_int(e_lo.w);
+            e_ct = __float_as_int(e_hi.w);
+            e_wh = ld_cached(whole + B);
+            keep = B != A && !(wA && e_wh && uf_find_c(uf, e_st) == uf_find_c(uf, astart));
+        }
+        uint64_t pend = __ballot(keep);
+        const uint64_t wholes = __ballot(e_wh != 0);
+        int cur = -1;
+        for (;;) {
+            // the next source some lane's point reaches, its points loading
+            int nxt = -1;
+            float4 pn = make_float4(0, 0, 0, 0);
+            while (pend) {
+                const int qq = __ffsll((unsigned long long)pend) - 1;
+                pend &= pend - 1ull;
+                auto rl = [&](float v) __attribute__((always_inline)) {
+                    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), qq));
+                };
+                const bool need = act && point_low2_m<PER>(me.x, me.y, me.z, rl(e_lo.x), rl(e_lo.y),
+                                                           rl(e_lo.z), rl(e_hi.x), rl(e_hi.y),
+                                                           rl(e_hi.z), L) <= bb;
+                if (__ballot(need)) {
+                    nxt = qq;
+                    const int st = __builtin_amdgcn_readlane(e_st, qq);
+                    if (lane < __builtin_amdgcn_readlane(e_ct, qq)) pn = pts[st + lane];
+                    break;
+                }
+            }
+            if (cur >= 0) {
+                const int b0 = __builtin_amdgcn_readlane(e_st, cur);
+                const int c = __builtin_amdgcn_readlane(e_ct, cur);
+                const bool wB = (wholes >> cur) & 1ull;
+                uint64_t lm = 0;  // the source's points this lane's may link to
+                evals += (unsigned)acount * (unsigned)c;
+                if (dense) {
+                    for (int f = 0; f < c; ++f) {
+                        const float4 p = tile[f];
+                        const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, L, Lh);
+                        lm |= dd <= bb ? 1ull << f : 0ull;
+                    }
+                    if (!act) lm = 0;
+                } else if (acount > 48) lm = pair_mask<4, PER>(tilef, c, ac, aL, Lh, bq, tg);
+                else if (acount > 32) lm = pair_mask<3, PER>(tilef, c, ac, aL, Lh, bq, tg);
+                else if (acount > 16) lm = pair_mask<2, PER>(tilef, c, ac, aL, Lh, bq, tg);
+                else lm = pair_mask<1, PER>(tilef, c, ac, aL, Lh, bq, tg);
+                link_source<PER>(lm, wA, wB, b0, my, me, tile, rootT, uf, bb, L, Lh, ra);
+            }
+            if (nxt < 0) break;
+            wave_lds_sync();
+            {
+                // the point and its w (in .w; the index is not needed)
+                const float dx = wrap_diff<PER>(pn.x - cx, L, Lh);
+                const float dy = wrap_diff<PER>(pn.y - cy, L, Lh);
+                const float dz = wrap_diff<PER>(pn.z - cz, L, Lh);
+                const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
+                tile[lane] = make_float4(pn.x, pn.y, pn.z, pw);
+                const bool far = lane < __builtin_amdgcn_readlane(e_ct, nxt) && !(pw < FILTER_BIG);
+                if (__ballot(far)) dense = true;
+            }
+            wave_lds_sync();
+            cur = nxt;
+        }
+    }
+    if (lane == 0) atomicAdd(stats + (A & (STAT_SLOTS - 1)), evals);
 }
 
 // Root of every point (a read-only find: no other thread writes uf[i] now)

@@ -157,6 +157,31 @@ __device__ __forceinline__ float point_low2_m(float qx, float qy, float qz, floa
 }
 
 // ---------------------------------------------------------------------------
+// The leaf stages' matrix filter: which pairs (q, p) of a query and a source
+// point may have dist2 <= T, for 16 points x 16 queries per
+// v_mfma_f32_16x16x4_f32. With q' = fl(q - c), p' = fl(p - c) for a common
+// point c, the product gives D = -2 q'.p' + w - t with w = |p'|^2 (1 - e) of
+// the point and t = T (1 + e) - |q'|^2 (1 - e) + tiny of the query, and a pair
+// is taken if D < 0.
+// Why no pair within T is missed (u = 2^-24): the real |q' - p'|^2 differs from
+// the real |q - p|^2 by at most 4.2 u (|q'|^2 + |p'|^2), the fixed float32
+// dist2 from the latter by 6 u relative (and a subnormal rounding), and the
+// five-term sum D by at most 20 u (|p'|^2 + |q'|^2 + T), whatever the order and
+// rounding direction of the matrix unit. e = 2^-18 = 64 u covers the sum of
+// these, tiny = 2^-120 covers flushed subnormal products. Squares beyond 2^100
+// (where inf - inf could appear) are left to an exact scan.
+// In a periodic box p' is the image nearest to c, and the wrapped difference
+// carries a rounding at the scale of the period, so the bound T is raised to
+// (sqrt(T) + 2^-19 L)^2; the image nearest to c is also the one nearest to q as
+// long as |q'| + sqrt(T) stays below half a period on every axis, else the
+// exact scan runs.
+constexpr float FILTER_E = 0x1p-18f;
+constexpr float FILTER_TINY = 0x1p-120f;
+constexpr float FILTER_BIG = 0x1p100f;
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
 // Work-group and work-item indices read straight from the hardware registers
 // and the dispatch packet. The device library's accessors behind blockIdx,
 // threadIdx, gridDim and blockDim are not inlined into code built with a

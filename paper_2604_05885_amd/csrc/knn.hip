@@ -712,13 +712,6 @@ constexpr int FILLER = 255;   // tile position of a point at infinity with the p
 constexpr int HALF = 128;     // tile positions filtered at a time (32 blocks of 4 per lane row)
 constexpr int CQ = 32;        // queued candidate positions per lane
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-// Relative and absolute margins of the matrix filter (see k_leaf_knn).
-constexpr float FILTER_E = 0x1p-18f;
-constexpr float FILTER_TINY = 0x1p-120f;
-constexpr float FILTER_BIG = 0x1p100f;
-
 // Keep the K smallest of two ascending key lists a and b in a (ascending).
 // With both lists padded to M = next power of two, min(a[i], b[M-1-i]) is a
 // bitonic sequence holding the M smallest of the padded union (so the K
@@ -931,18 +924,8 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // t = kth (1 + e) - |q'|^2 (1 - e) + tiny of the query; a hit is D < 0, and
 // the hits are collected by shifting the sign bit of each result into a mask
 // (one v_alignbit per result).
-// Why a hit cannot be missed (u = 2^-24): the real |q' - p'|^2 differs from
-// the real |q - p|^2 by at most 4.2 u (|q'|^2 + |p'|^2), the fixed float32
-// dist2 from the latter by 6 u relative (and a subnormal rounding), and the
-// five-term sum D by at most 20 u (|p'|^2 + |q'|^2 + kth), whatever the order
-// and rounding direction of the matrix unit. e = 2^-18 = 64 u covers the sum
-// of these, tiny = 2^-120 covers flushed subnormal products. Magnitudes
-// beyond 2^100 (where inf - inf could appear) take the exact dense scan below.
-// In a periodic box p' is the image nearest to c, and the wrapped difference
-// carries a rounding at the scale of the period, so the k-th distance is
-// raised by 2^-19 L; the image nearest to c is also the one nearest to q as
-// long as |q'| + kth stays below half a period on every axis, else the dense
-// scan runs.
+// (jz_device.h states why no point within the k-th distance is missed; the
+// coordinates that the filter does not cover take the exact dense scan below.)
 // Against per-lane box tests and exact evaluations on the vector unit (12
 // instructions per position and wave, 30 % of the lanes in use) the filter
 // costs one matrix instruction and four shifts per 16 x 16 pairs: at 2^24

@@ -67,3 +67,44 @@ def test_filter_wide_leaves(jz):
 def test_filter_periodic_reach(jz, n, k):
     check(jz, inputs.uniform(n, 45), k, (n, k), period=1.0)
     check(jz, inputs.clustered(n, 3, 46), k, (n, k, "clustered"), period=1.0)
+
+
+def check_fof(jz, p, b, what, period=0.0, **opts):
+    import torch
+    p = np.ascontiguousarray(p, dtype=np.float32)
+    with jz.jz_build(torch.from_numpy(p).cuda(), jz.default_opts(period=period, **opts)) as t:
+        lab = t.fof(b).cpu().numpy()
+    want = oracle.fof_bf_periodic(p, period, b) if period else oracle.fof_bf(p, b)
+    assert np.array_equal(lab, want), what
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 128, 129, 320])
+def test_fof_block_edges(jz, n):
+    p = inputs.uniform(n, 200 + n)
+    for alpha in (0.3, 0.8, 1.0, 1.2, 3.0):
+        check_fof(jz, p, inputs.linking_length(n, alpha), (n, alpha))
+        check_fof(jz, p, inputs.linking_length(n, alpha), (n, alpha, "periodic"), period=1.0)
+
+
+@pytest.mark.parametrize("leaf_max", [1, 3, 16, 17, 33, 49, 64])
+def test_fof_leaf_sizes_and_chains(jz, leaf_max):
+    """Dense clumps (leaves that become whole), percolating uniform sets, and
+    a chain of points each within b of the next only (leaves whose components
+    close over many steps)."""
+    for p, alpha in ((inputs.clustered(3000, 3, 61), 0.2), (inputs.uniform(3000, 62), 0.85),
+                     (inputs.uniform(3000, 62), 0.95)):
+        check_fof(jz, p, inputs.linking_length(len(p), alpha), (leaf_max, alpha), leaf_max=leaf_max)
+    s = np.arange(600)
+    chain = np.stack([s, (s * 7) % 3, (s * 5) % 2], 1).astype(np.float32) * np.float32(2.0 ** -10)
+    for b in (2.0 ** -10, 2.0 ** -10 * 1.42, 2.0 ** -10 * 2.3):
+        check_fof(jz, chain, b, (leaf_max, b), leaf_max=leaf_max)
+
+
+@pytest.mark.parametrize("offset,scale", [(0.0, 2.0 ** -62), (1.0, 2.0 ** -16), (-3.0e7, 512.0),
+                                          (0.0, 2.0 ** 45), (0.0, 2.0 ** 52), (2.0 ** 58, 2.0 ** 44)])
+def test_fof_scales(jz, offset, scale):
+    q = inputs.clustered(2500, 5, 42)
+    p = (q.astype(np.float64) * scale + offset).astype(np.float32)
+    for alpha in (0.1, 0.5):
+        check_fof(jz, p, float(np.float32(inputs.linking_length(2500, alpha) * scale)),
+                  (offset, scale, alpha))
