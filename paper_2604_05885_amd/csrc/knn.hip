@@ -1,21 +1,20 @@
 // Exact kNN by a dual walk over the tree planes (paper: kNN section, Alg. 1-3,
 // Eq. 14-16, and the implementation-details subsection on r_low ordering).
 //
-// Level step (one wave per work item: a receiving parent and up to 8 of its
-// children; lanes = those children):
-//   pass 1  FindRmax: register heap of (d_up^2, count); R = smallest radius
-//           whose cumulative count reaches k (Alg. 3)
-//   pass 2  count children pairs with d_low^2 <= R
-//   pass 3  insert them (with r_low = d_low^2) into the next list, at an
-//           offset reserved with one atomic per wave
+// Level step (one wave per work item: a receiving parent and up to 4 of its
+// children in scalar registers; lanes = the children of the parent's sources):
+//   FindRmax: R = smallest radius whose cumulative count reaches k (Alg. 3)
+//   count children pairs with d_low^2 <= R
+//   insert them (with r_low = d_low^2) into the next list, at an offset
+//   reserved with one atomic per wave
 // The paper's separate Count / prefix-sum / Insert launches become one kernel.
-// Each receiver's source list is read in r_low order (sorted in LDS when
-// short, in HBM before the level when long) so that the early exit
-// "r_low > max over lanes of R" can drop the rest of the list.
+// Only the sources within the radii that the parent's own children give are
+// expanded; a long list, put in r_low order in HBM before the level, is left
+// at the first entries beyond them.
 //
-// Leaf stage (one wave per receiving leaf; lanes = its query points): source
-// leaves in r_low order, each staged in LDS as float4 (x, y, z, index); every
-// lane keeps its top-k as packed (dist2 bits, index) u64 keys in registers.
+// Leaf stage (one wave per receiving leaf; lanes = its query points): the own
+// leaf, then source leaves in r_low order, staged in LDS as float4; every lane
+// keeps its top-k as packed (dist2 bits, index) u64 keys in registers.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,66 +37,6 @@ constexpr uint64_t PAD_KEY = (0x7f800000ull << 32) | 0xffffffffull;  // (+inf, n
 
 __device__ __forceinline__ uint64_t list_key(int2 e) {
     return ((uint64_t)(uint32_t)e.y << 32) | (uint32_t)e.x;  // r_low >= 0: bits order as floats
-}
-
-// Stage a receiver's list in LDS and sort it ascending by (r_low, source).
-__device__ void stage_sorted(const int2 *__restrict__ src, int len, uint64_t *L) {
-    int M = 1;
-    while (M < len) M <<= 1;
-    for (int i = lane_id(); i < M; i += 64) L[i] = i < len ? list_key(src[i]) : ~0ull;
-    wave_lds_sync();
-    for (int k = 2; k <= M; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = lane_id(); i < (M >> 1); i += 64) {
-                const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                const int b = a + j;
-                const uint64_t x = L[a], y = L[b];
-                const bool up = (a & k) == 0;
-                if ((x > y) == up) {
-                    L[a] = y;
-                    L[b] = x;
-                }
-            }
-            wave_lds_sync();
-        }
-    }
-}
-
-// Order a receiver's list by (r_low, source). A list of at most LCAP entries
-// is staged in L. A longer one, of at most scap entries, is sorted in the
-// LDS scratch that begins with L (the wave's other buffers, not yet in use)
-// and written back whole, in order, over its segment in HBM (the segment
-// belongs to this receiver alone); its first LCAP entries stay in L. The
-// segment stays a permutation of the list, so a level that is run again
-// after a capacity overflow reads the same list. A list of at most
-// presorted entries was already put in order in HBM (k_sort_lists): only its
-// first LCAP entries are staged. Either way the list then reads in r_low
-// order and the walk can stop at the first entry beyond its radius. Returns
-// false (list left as it is, read unordered) for a longer list.
-__device__ bool stage_list(int2 *__restrict__ gl, int len, uint64_t *S, int scap,
-                           int presorted) {
-    if (len > scap) {
-        if (len > presorted) return false;
-        for (int i = lane_id(); i < LCAP; i += 64) S[i] = list_key(gl[i]);
-        wave_lds_sync();
-        return true;
-    }
-    stage_sorted(gl, len, S);
-    if (len > LCAP) {
-        for (int i = lane_id(); i < len; i += 64) {
-            const uint64_t e = S[i];
-            gl[i] = make_int2((int)(uint32_t)e, (int)(uint32_t)(e >> 32));
-        }
-        // the wave reads entries from LCAP on back later, from other lanes:
-        // wait until the stores have reached L2 (the wave's own, so this
-        // CU's L2) and drop this CU's vector L1, which may still hold the
-        // lines as they were loaded above. (A workgroup-scope fence compiles
-        // to nothing in a one-wave workgroup; an agent-scope one would also
-        // write back and invalidate L2, which the other XCDs never read.)
-        __asm__ volatile("s_waitcnt vmcnt(0)\n\tbuffer_inv sc0" ::: "memory");
-    }
-    wave_lds_sync();
-    return true;
 }
 
 // Lists longer than a wave can sort in its LDS scratch are put in order in
@@ -206,187 +145,13 @@ __global__ __launch_bounds__(64 * NW) void k_sort_lists(int2 *__restrict__ list,
     }
 }
 
-// Entry t of a receiver's list: from LDS for the first LCAP entries of an
-// ordered list, else from HBM.
-__device__ __forceinline__ void list_entry(bool staged, const uint64_t *L, const int2 *g, int t,
-                                           int &src, float &rl) {
-    if (staged && t < LCAP) {
-        const uint64_t e = L[t];
-        src = (int)(uint32_t)e;
-        rl = __uint_as_float((uint32_t)(e >> 32));
-    } else {
-        const int2 e = g[t];
-        src = e.x;
-        rl = __int_as_float(e.y);
-    }
-}
-
-// Register heap of (radius, count), sorted by radius. Inserting pushes the
-// largest entry out; its count is merged into the last slot at its (larger)
-// radius, which keeps "at least C points within radius r" true for every
-// prefix.
-template <int NR>
-__device__ __forceinline__ void heap_insert(float (&hr)[NR], int (&hc)[NR], float r, int c) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        const bool sw = r < hr[i];
-        const float tr = sw ? hr[i] : r;
-        const int tc = sw ? hc[i] : c;
-        hr[i] = sw ? r : hr[i];
-        hc[i] = sw ? c : hc[i];
-        r = tr;
-        c = tc;
-    }
-    if (c > 0) {
-        hr[NR - 1] = r;
-        hc[NR - 1] += c;
-    }
-}
-
-// smallest radius whose cumulative count reaches k (+inf if the total is < k)
-template <int NR>
-__device__ __forceinline__ float radius_of_count(const float (&hr)[NR], const int (&hc)[NR],
-                                                 int k) {
-    int acc = 0;
-    float R = INFINITY;
-    bool found = false;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        acc += hc[i];
-        if (!found && acc >= k) {
-            R = hr[i];
-            found = true;
-        }
-    }
-    return R;
-}
-
-constexpr int NR_HEAP = 8;
-constexpr int FCAP = 128;  // source children staged per batch
-
-// Walk the (r_low-sorted) source list of one receiving parent in batches: the
-// children of consecutive sources are copied into one LDS buffer (their node
-// records in F, their indices in FI) until FCAP children; a source with more
-// children than FCAP is split over several batches. Sources whose r_low
-// exceeds rw() end the walk. fn(nF, fi) then processes the nF staged children
-// (fi: their indices).
-// The walk is pipelined one batch deep: the next batch is chosen, its indices
-// written to the other half of FI and its node records loaded into registers
-// before fn runs on the current one, and copied into F after it, so that the
-// record loads overlap fn instead of stalling every batch. The next batch is
-// chosen with rw() as it was before fn; where rw() shrinks during fn (the
-// FindRmax pass) that may take sources a later check would have dropped, which
-// only adds candidates to an upper bound. The list entries (and children
-// ranges) of the batch after that are loaded meanwhile too.
-// With separate query and source points (scnt != nullptr), a staged record's
-// count is replaced by its number of source points.
-template <class RW, class FN>
-__device__ __forceinline__ void for_source_batches(bool staged, const uint64_t *L,
-                                                   const int2 *gl, int len,
-                                                   const int *__restrict__ par_spl,
-                                                   const Node *__restrict__ nodes,
-                                                   const int *__restrict__ scnt, Node *F, int *FI,
-                                                   RW &&rw, FN &&fn) {
-    static_assert(FCAP == 128, "two node records per lane");
-    const int lane = lane_id();
-    int t = 0, skip = 0;
-    // entry t + lane of the list: its r_low and the range of its children
-    bool valid = false;
-    int s0 = 0, cnt = 0;
-    float rl = 0.0f;
-    auto load = [&](int t0) {
-        valid = t0 + lane < len;
-        if (valid) {
-            int src;
-            list_entry(staged, L, gl, t0 + lane, src, rl);
-            s0 = par_spl[src];
-            cnt = par_spl[src + 1] - s0;
-        }
-    };
-    // the prepared batch: nN children (0: the walk ends), indices in FI half
-    // `half`, the records of positions lane and lane + 64 as two halves each
-    int nN = 0, half = 0;
-    float4 r0a = make_float4(0, 0, 0, 0), r0b = r0a, r1a = r0a, r1b = r0a;
-    auto fetch_rec = [&](int x, float4 &ra, float4 &rb) {
-        const float4 *rec = reinterpret_cast<const float4 *>(nodes + x);
-        ra = rec[0];
-        rb = rec[1];
-        if (scnt) rb.w = __int_as_float(scnt[x]);  // Node.count is the last word
-    };
-    auto prepare = [&](float Rw) {
-        int *fi = FI + half * FCAP;
-        nN = 0;
-        if (t >= len) return;
-        const int b0 = s0 + (lane == 0 ? skip : 0);
-        const int c_all = cnt - (lane == 0 ? skip : 0);
-        const bool ok = valid && (!staged || rl <= Rw);
-        const uint64_t okm = __ballot(ok);  // sorted by r_low: a prefix of the lanes
-        const int nok = ~okm ? __ffsll((unsigned long long)~okm) - 1 : 64;
-        if (nok == 0) {
-            t = len;
-            return;
-        }
-        const int c = lane < nok ? c_all : 0;
-        const int incl = wave_incl_scan(c);
-        const int ntake = __popcll(__ballot(lane < nok && incl <= FCAP));
-        if (ntake == 0) {
-            // the first source alone overflows the buffer: take FCAP of its
-            // children (the loaded entries stay those of position t)
-            const int f0 = uni(__shfl(b0, 0, 64));
-            for (int f = lane; f < FCAP; f += 64) fi[f] = f0 + f;
-            nN = FCAP;
-            skip += FCAP;
-        } else {
-            // lane q < ntake lists the indices of its source's children
-            if (lane < ntake) {
-                const int off = incl - c;
-                for (int q = 0; q < c; ++q) fi[off + q] = b0 + q;
-            }
-            nN = uni(__shfl(incl, ntake - 1, 64));
-            t += ntake;
-            skip = 0;
-        }
-        wave_lds_sync();
-        // every lane loads records lane and lane + 64 (independent loads
-        // instead of one chain per source)
-        if (lane < nN) fetch_rec(fi[lane], r0a, r0b);
-        if (lane + 64 < nN) fetch_rec(fi[lane + 64], r1a, r1b);
-        if (ntake != 0) load(t);
-    };
-    auto commit = [&]() {
-        float4 *f4 = reinterpret_cast<float4 *>(F);
-        if (lane < nN) {
-            f4[2 * lane] = r0a;
-            f4[2 * lane + 1] = r0b;
-        }
-        if (lane + 64 < nN) {
-            f4[2 * lane + 128] = r1a;
-            f4[2 * lane + 129] = r1b;
-        }
-    };
-    load(0);
-    prepare(uni(rw()));
-    commit();
-    wave_lds_sync();
-    while (nN > 0) {
-        const int nF = nN;
-        const int *fcur = FI + half * FCAP;
-        half ^= 1;
-        prepare(uni(rw()));
-        fn(nF, fcur);
-        wave_lds_sync();
-        commit();
-        wave_lds_sync();
-    }
-}
-
 // The walk's work items: a receiving parent with more than cb children is
 // split into items of cb children (each a wave of its own, reading the
 // parent's list), so that the few parents with many children and long lists
 // do not leave one wave running long after the rest of the level, and so
 // that the upper levels, with few parents, still fill the device. cb is at
 // most WALK_CB.
-constexpr int WALK_CB = 8;
+constexpr int WALK_CB = 4;
 constexpr int WALK_CB_UP = 2;
 // A parent whose list is longer than WALK_LONG entries takes items of at most
 // WALK_CB_LONG children: such items run many times longer than the rest and
@@ -418,30 +183,39 @@ __global__ __launch_bounds__(64) void k_walk_items(const int *__restrict__ par_s
         items[base + (unsigned long long)(incl - nb + b)] = make_int2(P, c0 + b * cbe);
 }
 
-// Level step of the kNN walk: one wave per work item (a receiving parent and
-// up to WALK_CB of its children). The children are spread over the lanes with G = 64 / (children, rounded up to a power of 2)
-// lanes per child; the G lanes of a child split the staged source children
-// between them (slice sl takes f = sl, sl + G, ...).
-//   pass 1  FindRmax: a register heap of (d_up^2, count) per lane; the G
-//           heaps of a child are then merged exactly in LDS (R = smallest
-//           radius whose cumulative count over all entries reaches k)
-//   pass 2  count pairs with d_low^2 <= R
-//   pass 3  insert them (with r_low = d_low^2) at offsets reserved with one
-//           atomic per wave; a child's entries are contiguous.
+constexpr int FCAP = 1024;  // source children listed in LDS at a time
+
+// Level step of the kNN walk: one wave per work item, a receiving parent P and
+// up to WALK_CB of its children. The children's boxes sit in scalar registers;
+// the source children go through the lanes, 64 node records at a time.
+//   phase 0  FindRmax: every lane keeps, per receiving child, the two smallest
+//            (d_up^2, count) it has met; the smallest of them over the wave are
+//            added up until the count reaches k (Alg. 3; leaving any out keeps
+//            the radius an upper bound). P's own children come first: with the
+//            radii they give, most of P's list is not expanded at all
+//   phase 1  count pairs with d_low^2 <= R: a compare per 64 pairs
+//   phase 2  insert them (with r_low = d_low^2) at offsets reserved with one
+//            atomic per wave; a child's entries are contiguous
+// The indices of the listed sources' children are expanded into LDS, FCAP at a
+// time (nearly always once for all phases), each batch's records loaded while
+// the one before is worked on.
+// With the receiving children in the lanes and the source records staged
+// through LDS, the level spent its time waiting for a chain of loads and LDS
+// steps per batch of 128, and merging heaps: 0.20 + 0.27 + 0.46 + 2.21 ms from
+// the top to the leaf level at 2^24 clustered points, k = 16, now 0.04 + 0.06 +
+// 0.20 + 1.03 (8 children per item instead of 4: 0.05 + 0.07 + 0.27 + 0.92, and
+// 0.11 ms instead of 0.07 for the one level of 5 10^4 points); 0.37 + 0.27 ms
+// at 10^6 uniform points, now 0.09 + 0.07.
 template <bool PER>
 __global__ __launch_bounds__(64 * WPB) void k_knn_step(
     const int2 *__restrict__ items, const unsigned long long *__restrict__ n_items, int cb,
-    const int2 *__restrict__ seg_in, int2 *__restrict__ list_in,
+    const int2 *__restrict__ seg_in, const int2 *__restrict__ list_in,
     const int *__restrict__ par_spl, const Node *__restrict__ nodes, int k,
     int2 *__restrict__ seg_out, int2 *__restrict__ list_out,
     unsigned long long *__restrict__ ctr, long long cap, unsigned long long *overflow,
-    int sort_cap, int presorted, const int *__restrict__ scnt, float Lp,
+    int sorted_min, int sorted_max, const int *__restrict__ scnt, float Lp,
     float *__restrict__ rout) {
-    // one block per wave: the staged list (LCAP entries), then the staged
-    // source children (FCAP records, and their indices for two batches); before the walk the
-    // whole block is the scratch in which a longer list is sorted
-    constexpr int RAW = LCAP + FCAP * (int)(sizeof(Node) / 8) + FCAP;
-    __shared__ __align__(16) uint64_t s_raw[WPB][RAW];
+    __shared__ int s_fi[WPB][FCAP];
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     // work item I: receiving parent it.x, its children from it.y (at most
     // item_cb(cb, list length) of them)
@@ -450,126 +224,214 @@ __global__ __launch_bounds__(64 * WPB) void k_knn_step(
     const int2 it = items[I];
     const int P = uni(it.x);
     const int2 sg = seg_in[P];
-    int2 *gl = list_in + uni(sg.x);
+    const int2 *gl = list_in + uni(sg.x);
     const int len = uni(sg.y);
-    const int c0 = uni(it.y), c1 = uni(min(par_spl[P + 1], it.y + item_cb(cb, len)));
-    uint64_t *L = s_raw[w];
-    Node *F = reinterpret_cast<Node *>(L + LCAP);
-    int *FI = reinterpret_cast<int *>(L + LCAP + FCAP * (int)(sizeof(Node) / 8));
-    const bool staged = stage_list(gl, len, L, min(sort_cap, prev_pow2(RAW)), presorted);
+    // (a list of these lengths is in r_low order: the walk stops at the first
+    // 64 entries that hold none within its radius)
+    const bool sorted = len > sorted_min && len <= sorted_max;
+    const int p0 = uni(par_spl[P]), p1 = uni(par_spl[P + 1]);
+    const int c0 = uni(it.y), nc = uni(min(p1, it.y + item_cb(cb, len))) - c0;
+    int *FI = s_fi[w];
 
-    for (int cb = c0; cb < c1; cb += 64) {
-        const int nc = min(64, c1 - cb);
-        // G = largest power of two with nc * G <= 64
-        int lg = 0;
-        while ((nc << (lg + 1)) <= 64) ++lg;
-        const int G = 1 << lg;
-        const int ci = lane >> lg, sl = lane & (G - 1);
-        const int c = cb + (ci < nc ? ci : 0);
-        const Node me = nodes[c];
+    Node me[WALK_CB];
+    bool act[WALK_CB];   // (uniform) receives anything
+    float R[WALK_CB];    // (uniform) radius
+    int cnt[WALK_CB];    // (uniform) entries, then insert position
+    float r0[WALK_CB], r1[WALK_CB];
+    int n0[WALK_CB], n1[WALK_CB];
+#pragma unroll
+    for (int j = 0; j < WALK_CB; ++j) {
+        const int c = c0 + min(j, nc - 1);
+        me[j] = nodes[c];
         // with separate point types, a child without query points receives
         // nothing
-        const bool act = ci < nc && (!scnt || me.count > scnt[c]);
-        float hr[NR_HEAP];
-        int hc[NR_HEAP];
+        act[j] = j < nc && (!scnt || uni(me[j].count) > uni(scnt[c]));
+        R[j] = INFINITY;
+        cnt[j] = 0;
+        r0[j] = r1[j] = INFINITY;
+        n0[j] = n1[j] = 0;
+    }
+    float Rw = INFINITY;  // largest radius of the receiving children
+    // radii from what the lanes have kept
+    auto radii = [&]() __attribute__((always_inline)) {
+        Rw = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < NR_HEAP; ++i) {
-            hr[i] = INFINITY;
-            hc[i] = 0;
-        }
-        float R = INFINITY;
-        // pass 1: FindRmax over this lane's slice
-        for_source_batches(
-            staged, L, gl, len, par_spl, nodes, scnt, F, FI,
-            [&]() { return wave_max_f(act ? R : -INFINITY); },
-            [&](int nF, const int *) {
-                for (int f = sl; f < nF; f += G) {
-                    const Node o = F[f];
-                    const float r = box_up2_m<PER>(me, o, Lp);
-                    if (act && r < R && o.count > 0) {
-                        heap_insert<NR_HEAP>(hr, hc, r, o.count);
-                        R = fminf(R, radius_of_count<NR_HEAP>(hr, hc, k));
-                    }
+        for (int j = 0; j < WALK_CB; ++j) {
+            if (!act[j]) continue;
+            float a = r0[j], b = r1[j];
+            int na = n0[j], nb = n1[j], acc = 0;
+            for (;;) {
+                const float m = uni(wave_min(a));
+                if (!(m < R[j])) break;
+                const int l = __ffsll((unsigned long long)__ballot(a == m)) - 1;
+                acc += __builtin_amdgcn_readlane(na, l);
+                if (acc >= k) {
+                    R[j] = m;
+                    break;
                 }
-                // each lane's radius already bounds its child (k points of its
-                // slice lie within it), so the child's lanes share the smallest
-                R = group_min_f(R, G);
-            });
-        if (G > 1) {
-            // exact merge of the G heaps of each child (LDS scratch: F's buffer)
-            float *mr = reinterpret_cast<float *>(F);
-            int *mc = reinterpret_cast<int *>(F) + NR_HEAP * 64;
+                const bool mine = lane == l;
+                a = mine ? b : a;
+                na = mine ? nb : na;
+                b = mine ? INFINITY : b;
+            }
+            Rw = fmaxf(Rw, R[j]);
+        }
+    };
+
+    // the stream of source children: P's own, then those of the listed sources
+    // within Rw, in the order of the list
+    int own = 0, t = 0, skip = 0, nN = 0;
+    auto fill_own = [&]() __attribute__((always_inline)) {
+        const int c = min(FCAP - nN, p1 - p0 - own);
+        for (int f = lane; f < c; f += 64) FI[nN + f] = p0 + own + f;
+        own += c;
+        nN += c;
+    };
+    auto fill_list = [&]() __attribute__((always_inline)) {
+        while (t < len && nN < FCAP) {
+            int2 e = make_int2(0, 0);
+            if (t + lane < len) e = gl[t + lane];
+            const bool in = t + lane < len && __int_as_float(e.y) <= Rw;
+            const bool keep = in && e.x != P;
+            int s0 = 0, c = 0;
+            if (keep) {
+                s0 = par_spl[e.x];
+                c = par_spl[e.x + 1] - s0;
+                if (lane == 0) {
+                    s0 += skip;
+                    c -= skip;
+                }
+            }
+            if (sorted && !__ballot(in)) {
+                t = len;
+                break;
+            }
+            const int incl = wave_incl_scan(c);
+            const int take = (int)__popcll(__ballot(nN + incl <= FCAP));  // a prefix of the lanes
+            if (take == 0) {
+                // more children than there is room for
+                if (nN > 0) break;
+                const int f0 = __builtin_amdgcn_readlane(s0, 0);
+                for (int f = lane; f < FCAP; f += 64) FI[f] = f0 + f;
+                nN = FCAP;
+                skip += FCAP;
+                return;
+            }
+            if (lane < take)
+                for (int q = 0; q < c; ++q) FI[nN + incl - c + q] = s0 + q;
+            nN += __builtin_amdgcn_readlane(incl, take - 1);
+            t += take;
+            skip = 0;
+            if (take < 64 && t < len) break;
+        }
+    };
+    long long base = 0;
+    bool single = true;  // the whole stream fits FI
+    for (int phase = 0; phase < 3; ++phase) {
+        if (phase == 1) {
+            // the leaf level keeps each child's radius for the leaf stage: k
+            // points lie within R of every point of the child
 #pragma unroll
-            for (int i = 0; i < NR_HEAP; ++i) {
-                mr[i * 64 + lane] = hr[i];
-                mc[i * 64 + lane] = hc[i];
+            for (int j = 0; j < WALK_CB; ++j)
+                if (rout && act[j] && lane == 0) rout[c0 + j] = R[j];
+        }
+        if (phase == 2) {
+            int total = 0;
+#pragma unroll
+            for (int j = 0; j < WALK_CB; ++j) total += cnt[j];
+            // segment in arena I % LIST_ARENAS (cap entries each)
+            const int ar = I & (LIST_ARENAS - 1);
+            unsigned long long lb = 0;
+            if (lane == 0) lb = atomicAdd(ctr + ar, (unsigned long long)total);
+            lb = uni(lb);
+            base = (long long)((unsigned long long)ar * (unsigned long long)cap + lb);
+            const bool ok = (long long)lb + total <= cap;
+            // an overflowing level makes every list below it incomplete: flag
+            // it, so that the leaf stage of this attempt exits at once
+            if (!ok && lane == 0) *overflow = 1;
+            int off = 0;
+#pragma unroll
+            for (int j = 0; j < WALK_CB; ++j) {
+                if (j < nc && lane == 0)
+                    seg_out[c0 + j] = ok ? make_int2((int)(base + off), cnt[j]) : make_int2(0, 0);
+                const int c = cnt[j];
+                cnt[j] = off;
+                off += c;
+            }
+            if (!ok || total == 0) break;
+        }
+        int b0 = 0;
+        bool first = phase == 0;  // P's own children alone, then the list
+        if (phase == 0 || !single) own = t = skip = nN = 0;
+        for (;;) {
+            if (phase == 0 || !single) {
+                if (own < p1 - p0) fill_own();
+                if (!first && own == p1 - p0) fill_list();
             }
             wave_lds_sync();
-            float best = INFINITY;
-            const int g0 = ci << lg;
-            if (act) {
-                for (int e = sl; e < G * NR_HEAP; e += G) {
-                    const float re = mr[(e % NR_HEAP) * 64 + g0 + e / NR_HEAP];
-                    if (!(re < best)) continue;
-                    int acc = 0;
-                    for (int g = 0; g < G; ++g)
-                        for (int i = 0; i < NR_HEAP; ++i)
-                            if (mr[i * 64 + g0 + g] <= re) acc += mc[i * 64 + g0 + g];
-                    if (acc >= k) best = re;
+            // node records of positions b + lane, loaded one batch ahead
+            int x = 0, nx = 0;
+            float4 ra = make_float4(0, 0, 0, 0), rb = ra, na = ra, nb = ra;
+            auto load = [&](int b) __attribute__((always_inline)) {
+                if (b + lane < nN) {
+                    nx = FI[b + lane];
+                    const float4 *rec = reinterpret_cast<const float4 *>(nodes + nx);
+                    na = rec[0];
+                    nb = rec[1];
+                    if (scnt) nb.w = __int_as_float(scnt[nx]);  // Node.count is the last word
                 }
-            }
-            best = group_min_f(best, G);
-            R = fminf(best, R);
-            wave_lds_sync();
-        }
-        // the leaf level keeps each child's radius for the leaf stage: k
-        // points lie within R of every point of the child
-        if (rout && act && sl == 0) rout[c] = R;
-        const float Rw = uni(wave_max_f(act ? R : -INFINITY));
-        // pass 2: count
-        int cnt = 0;
-        for_source_batches(
-            staged, L, gl, len, par_spl, nodes, scnt, F, FI, [&]() { return Rw; },
-            [&](int nF, const int *) {
-                for (int f = sl; f < nF; f += G) {
-                    const Node o = F[f];
-                    cnt += (act && o.count > 0 && box_low2_m<PER>(me, o, Lp) <= R) ? 1 : 0;
-                }
-            });
-        // reserve: lanes are child-major, so a wave scan gives contiguous segments
-        const int incl = wave_incl_scan(cnt);
-        const int total = uni(__shfl(incl, 63, 64));
-        // segment in arena I % LIST_ARENAS (cap entries each)
-        const int ar = I & (LIST_ARENAS - 1);
-        unsigned long long lb = 0;
-        if (lane == 0) lb = atomicAdd(ctr + ar, (unsigned long long)total);
-        lb = uni((unsigned long long)__shfl(lb, 0, 64));
-        const unsigned long long base = (unsigned long long)ar * (unsigned long long)cap + lb;
-        const bool ok = (long long)lb + total <= cap;
-        // an overflowing level makes every list below it incomplete: flag it,
-        // so that the leaf stage of this attempt exits at once
-        if (!ok && lane == 0) *overflow = 1;
-        const int gfirst = (ci << lg), glast = gfirst + G - 1;
-        const int gstart = __shfl(incl - cnt, gfirst & 63, 64);
-        const int gend = __shfl(incl, glast & 63, 64);
-        if (ci < nc && sl == 0)
-            seg_out[c] = ok ? make_int2((int)((long long)base + gstart), gend - gstart)
-                            : make_int2(0, 0);
-        if (!ok) continue;
-        // pass 3: insert
-        long long wp = (long long)base + (incl - cnt);
-        for_source_batches(
-            staged, L, gl, len, par_spl, nodes, scnt, F, FI, [&]() { return Rw; },
-            [&](int nF, const int *fi) {
-                for (int f = sl; f < nF; f += G) {
-                    const Node o = F[f];
-                    const float lo = box_low2_m<PER>(me, o, Lp);
-                    if (act && o.count > 0 && lo <= R) {
-                        list_out[wp] = make_int2(fi[f], __float_as_int(lo));
-                        ++wp;
+            };
+            load(b0);
+            for (int b = b0; b < nN; b += 64) {
+                x = nx;
+                ra = na;
+                rb = nb;
+                load(b + 64);
+                Node o;
+                o.lo[0] = ra.x; o.lo[1] = ra.y; o.lo[2] = ra.z;
+                o.hi[0] = rb.x; o.hi[1] = rb.y; o.hi[2] = rb.z;
+                o.start = 0;
+                o.count = b + lane < nN ? __float_as_int(rb.w) : 0;
+#pragma unroll
+                for (int j = 0; j < WALK_CB; ++j) {
+                    if (!act[j]) continue;
+                    if (phase == 0) {
+                        float r = box_up2_m<PER>(me[j], o, Lp);
+                        const bool in = o.count > 0 && r < R[j];
+                        if (!__ballot(in)) continue;
+                        r = in ? r : INFINITY;
+                        const bool lt0 = r < r0[j];
+                        const float tr = lt0 ? r0[j] : r;
+                        const int tn = lt0 ? n0[j] : o.count;
+                        r0[j] = lt0 ? r : r0[j];
+                        n0[j] = lt0 ? o.count : n0[j];
+                        const bool lt1 = tr < r1[j];
+                        r1[j] = lt1 ? tr : r1[j];
+                        n1[j] = lt1 ? tn : n1[j];
+                    } else {
+                        const float lo = box_low2_m<PER>(me[j], o, Lp);
+                        const bool in = o.count > 0 && lo <= R[j];
+                        const uint64_t m = __ballot(in);
+                        if (phase == 2 && in)
+                            list_out[base + cnt[j] + (int)__popcll(m & lanemask_lt())] =
+                                make_int2(x, __float_as_int(lo));
+                        cnt[j] += (int)__popcll(m);
                     }
                 }
-            });
+            }
+            if (phase == 0) radii();
+            if (phase > 0 && single) break;
+            if (first && own == p1 - p0 && nN < FCAP) {
+                first = false;
+                b0 = nN;
+                continue;
+            }
+            first = false;
+            if (own == p1 - p0 && t >= len) break;
+            wave_lds_sync();
+            nN = b0 = 0;
+            single = false;
+        }
     }
 }
 
@@ -1522,7 +1384,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                 d_items.as<int2>(), n_items, cb_of(p), seg_in, list_in, par_spl,
                 t->nodes[p].as<Node>(), k, segs[p].as<int2>(), lists[p].as<int2>(),
                 ctr + (size_t)p * LIST_ARENAS, cap[p] / LIST_ARENAS, ctr + CTR_FLAG,
-                top ? LCAP : walk_cap, top ? 0 : sort_max,
+                top ? INT_MAX : walk_cap, top ? 0 : sort_max,
                 joint ? t->src_cnt[p].as<int>() : nullptr, period,
                 p == 0 ? d_rleaf.as<float>() : nullptr);
         }
