@@ -77,130 +77,156 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_l2p(const Node *__restrict__ l
     for (int i = a.start + 1 + lane; i < a.start + a.count; i += 64) uf[i] = a.start;
 }
 
-// kConnected: within reach but both nodes are whole and already one group
-enum PairCase { kDiscard = 0, kLinked = 1, kDescend = 2, kConnected = 3 };
-
-template <bool PER>
-__device__ __forceinline__ int fof_case(const Node &me, int c, const Node &o, int s, float bb,
-                                        int *whole, int *uf, bool do_link, float &lo, float L) {
-    lo = box_low2_m<PER>(me, o, L);
-    if (lo > bb) return kDiscard;
-    // (flags only ever go from 0 to 1 and groups only merge: values read
-    // through the caches may be older, which only costs a redundant union)
-    if (ld_cached(whole + c) && ld_cached(whole + s) &&
-        uf_find_c(uf, me.start) == uf_find_c(uf, o.start))
-        return box_up2_m<PER>(me, o, L) <= bb ? kLinked : kConnected;
-    if (box_up2_m<PER>(me, o, L) <= bb) {
-        if (do_link) {
-            uf_union_c(uf, me.start, o.start);
-            st_rel(whole + c, 1);
-            st_rel(whole + s, 1);
-        }
-        return kLinked;
-    }
-    return kDescend;
-}
-
-// Node walk step: one wave per receiving parent; its children are spread over
-// the lanes with G = 64 / (children, rounded up to a power of 2) lanes per
-// child, the G lanes of a child splitting the staged source children between
-// them. Pass A links, and counts the pairs that geometry alone sends down
-// (within reach, not wholly within b); pass B re-evaluates them and writes
-// those still to be descended into: the group state only merges, so pass B
-// writes a subset of what pass A counted, whatever either pass read of it.
-// A child's entries are placed through a counter in LDS, so its list is one
-// contiguous run whichever of its lanes found them.
-template <bool PER>
+// Node walk step: one wave per work item, a receiving parent and up to CB of
+// its children (item I: parent I / nsub, its children from CB (I % nsub) on,
+// in strides of CB nsub). The receivers' boxes sit in scalar
+// registers, the source children go through the lanes, 64 node records at a
+// time, their indices expanded into LDS.
+//   phase 0  links (d_up^2 <= b^2: union of the first points, both nodes become
+//            whole), and counts the pairs that geometry alone sends down
+//            (within reach, not wholly within b)
+//   phase 1  writes those still to be descended into (not both whole and
+//            already one group): the group state only merges, so this is a
+//            subset of what was counted, whatever either phase read of it
+// A pair is taken at its lower node. With a wave per parent that went through
+// its list source by source, the top level (a few dozen parents, 32 children
+// each) was one chain of loads per source: 0.34 ms at 10^6 uniform points.
+// CB = 4 or 8 receivers per wave: 4 (and two items per parent) where there are
+// few parents, 8 from FOF_MANY parents on, where the items fill the device
+// anyway and each repeats its parent's stream (leaf level at 2^24 clustered
+// points, 52780 parents: 0.24 ms with 8, 0.35 with 4; 7477 parents: 0.081 and
+// 0.073 ms; a top level of 94: 0.092 and 0.061 ms).
+constexpr int FOF_MANY = 16384;
+constexpr int FOF_CAP = 1024;
+template <bool PER, int CB>
 __global__ __launch_bounds__(64 * WPB) void k_fof_step(
     const int2 *__restrict__ seg_in, const int2 *__restrict__ list_in,
-    const int *__restrict__ par_spl, const Node *__restrict__ nodes, int n_par, float b2,
+    const int *__restrict__ par_spl, const Node *__restrict__ nodes, int n_par, int nsub, float b2,
     const float *__restrict__ b2n, int *__restrict__ whole, int *__restrict__ uf,
     int2 *__restrict__ seg_out, int2 *__restrict__ list_out,
     unsigned long long *__restrict__ ctr, long long cap, unsigned long long *overflow, float L) {
-    __shared__ Node s_tile[WPB][64];
-    __shared__ int s_emit[WPB][64];
+    __shared__ int s_fi[WPB][FOF_CAP];
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
-    const int P = xcd_block(blk_x(), nblk_x()) * WPB + w;
+    const int I = xcd_block(blk_x(), nblk_x()) * WPB + w;
+    const int P = I / nsub;
     if (P >= n_par) return;
     const int2 sg = seg_in[P];
     const int2 *gl = list_in + uni(sg.x);
     const int len = uni(sg.y);
-    const int c0 = uni(par_spl[P]), c1 = uni(par_spl[P + 1]);
-    Node *tile = s_tile[w];
-    int *emit = s_emit[w];
-    for (int cb = c0; cb < c1; cb += 64) {
-        const int nc = min(64, c1 - cb);
-        // G = largest power of two with nc * G <= 64
-        int lg = 0;
-        while ((nc << (lg + 1)) <= 64) ++lg;
-        const int G = 1 << lg;
-        const int ci = lane >> lg, sl = lane & (G - 1);
-        const bool act = ci < nc;
-        const int c = cb + (act ? ci : 0);
-        const Node me = nodes[c];
-        const float bb = b2n ? b2n[c] : b2;
-        int cnt = 0;
-        for (int t = 0; t < len; ++t) {
-            const int S = gl[t].x;
-            const int s0 = par_spl[S], s1 = par_spl[S + 1];
-            for (int sb = s0; sb < s1; sb += 64) {
-                const int ns = min(64, s1 - sb);
-                if (lane < ns) tile[lane] = nodes[sb + lane];
-                wave_lds_sync();
-                for (int j = sl; j < ns; j += G) {
-                    const int s = sb + j;
-                    if (!act || s < c) continue;
-                    float lo;
-                    const int k = fof_case<PER>(me, c, tile[j], s, bb, whole, uf, true, lo, L);
-                    cnt += (k == kDescend || k == kConnected) ? 1 : 0;
+    const int p0 = uni(par_spl[P]), p1 = uni(par_spl[P + 1]);
+    int *FI = s_fi[w];
+    for (int c0 = p0 + CB * (I % nsub); c0 < p1; c0 += CB * nsub) {
+        const int nc = min(CB, p1 - c0);
+        Node me[CB];
+        float bb[CB];
+        int cnt[CB];  // (uniform) pairs counted, then entries written
+        int off[CB];  // (uniform) first entry
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const int c = c0 + min(j, nc - 1);
+            me[j] = nodes[c];
+            bb[j] = b2n ? b2n[c] : b2;
+            cnt[j] = off[j] = 0;
+        }
+        long long base = 0;
+        bool single = true;  // the whole stream fits FI
+        int t = 0, skip = 0, nN = 0;
+        for (int phase = 0; phase < 2; ++phase) {
+            if (phase == 1) {
+                int total = 0;
+#pragma unroll
+                for (int j = 0; j < CB; ++j) {
+                    off[j] = total;
+                    total += cnt[j];
+                    cnt[j] = 0;
                 }
-                wave_lds_sync();
+                // segment in arena I % LIST_ARENAS (cap entries each)
+                const int ar = I & (LIST_ARENAS - 1);
+                unsigned long long lb = 0;
+                if (lane == 0) lb = atomicAdd(ctr + ar, (unsigned long long)total);
+                lb = uni(lb);
+                base = (long long)((unsigned long long)ar * (unsigned long long)cap + lb);
+                const bool ok = (long long)lb + total <= cap;
+                // lists below are incomplete: the leaf stage of this attempt exits
+                if (!ok && lane == 0) *overflow = 1;
+                if (!ok || total == 0) {
+                    if (lane < nc) seg_out[c0 + lane] = make_int2(0, 0);
+                    break;
+                }
             }
-        }
-        // reserve: lanes are child-major, so a wave scan gives each child a
-        // contiguous segment
-        const int incl = wave_incl_scan(cnt);
-        const int total = uni(__shfl(incl, 63, 64));
-        // segment in arena P % LIST_ARENAS (cap entries each)
-        const int ar = P & (LIST_ARENAS - 1);
-        unsigned long long lb = 0;
-        if (lane == 0) lb = atomicAdd(ctr + ar, (unsigned long long)total);
-        lb = uni((unsigned long long)__shfl(lb, 0, 64));
-        const unsigned long long base = (unsigned long long)ar * (unsigned long long)cap + lb;
-        const bool ok = (long long)lb + total <= cap;
-        const int gfirst = ci << lg;
-        const int gstart = __shfl(incl - cnt, gfirst & 63, 64);
-        const int gend = __shfl(incl, (gfirst + G - 1) & 63, 64);
-        if (!ok) {
-            // lists below are incomplete: the leaf stage of this attempt exits
-            if (lane == 0) *overflow = 1;
-            if (act && sl == 0) seg_out[c] = make_int2(0, 0);
-            continue;
-        }
-        const long long cpos = (long long)base + gstart;
-        const int room = gend - gstart;
-        emit[lane] = 0;
-        wave_lds_sync();
-        for (int t = 0; t < len; ++t) {
-            const int S = gl[t].x;
-            const int s0 = par_spl[S], s1 = par_spl[S + 1];
-            for (int sb = s0; sb < s1; sb += 64) {
-                const int ns = min(64, s1 - sb);
-                if (lane < ns) tile[lane] = nodes[sb + lane];
+            if (phase == 0 || !single) t = skip = nN = 0;
+            for (;;) {
+                if (phase == 0 || !single)
+                    list_children<FOF_CAP>(gl, len, par_spl, FI, nN, t, skip,
+                                           [](const int2 &, bool valid, bool &) { return valid; });
                 wave_lds_sync();
-                for (int j = sl; j < ns; j += G) {
-                    const int s = sb + j;
-                    if (!act || s < c) continue;
-                    float lo;
-                    if (fof_case<PER>(me, c, tile[j], s, bb, whole, uf, false, lo, L) == kDescend) {
-                        const int k = atomicAdd(emit + ci, 1);
-                        if (k < room) list_out[cpos + k] = make_int2(s, __float_as_int(lo));
+                // node records of positions b + lane, loaded one batch ahead
+                int x = 0, nx = 0;
+                float4 ra = make_float4(0, 0, 0, 0), rb = ra, na = ra, nb = ra;
+                auto load = [&](int b) __attribute__((always_inline)) {
+                    if (b + lane < nN) {
+                        nx = FI[b + lane];
+                        const float4 *rec = reinterpret_cast<const float4 *>(nodes + nx);
+                        na = rec[0];
+                        nb = rec[1];
+                    }
+                };
+                load(0);
+                for (int b = 0; b < nN; b += 64) {
+                    x = b + lane < nN ? nx : -1;
+                    ra = na;
+                    rb = nb;
+                    load(b + 64);
+                    Node o;
+                    o.lo[0] = ra.x; o.lo[1] = ra.y; o.lo[2] = ra.z;
+                    o.hi[0] = rb.x; o.hi[1] = rb.y; o.hi[2] = rb.z;
+                    o.start = __float_as_int(ra.w);
+                    o.count = 0;
+#pragma unroll
+                    for (int j = 0; j < CB; ++j) {
+                        const int c = c0 + j;
+                        const float lo = box_low2_m<PER>(me[j], o, L);
+                        const bool in = j < nc && x >= c && lo <= bb[j];
+                        if (!__ballot(in)) continue;
+                        const bool down = in && !(box_up2_m<PER>(me[j], o, L) <= bb[j]);
+                        // (flags only ever go from 0 to 1 and groups only
+                        // merge: values read through the caches may be older,
+                        // which only costs a redundant union)
+                        const bool wc = ld_cached(whole + c) != 0;
+                        if (phase == 0) {
+                            cnt[j] += (int)__popcll(__ballot(down));
+                            if (in && !down &&
+                                !(wc && ld_cached(whole + x) &&
+                                  uf_find_c(uf, me[j].start) == uf_find_c(uf, o.start))) {
+                                uf_union_c(uf, me[j].start, o.start);
+                                st_rel(whole + c, 1);
+                                st_rel(whole + x, 1);
+                            }
+                        } else {
+                            bool emit = down;
+                            if (emit && wc && ld_cached(whole + x))
+                                emit = uf_find_c(uf, me[j].start) != uf_find_c(uf, o.start);
+                            const uint64_t m = __ballot(emit);
+                            if (emit)
+                                list_out[base + off[j] + cnt[j] + (int)__popcll(m & lanemask_lt())] =
+                                    make_int2(x, __float_as_int(lo));
+                            cnt[j] += (int)__popcll(m);
+                        }
                     }
                 }
+                if (phase > 0 && single) break;
+                if (t >= len) break;
                 wave_lds_sync();
+                nN = 0;
+                single = false;
+            }
+            if (phase == 1) {
+#pragma unroll
+                for (int j = 0; j < CB; ++j)
+                    if (j < nc && lane == 0)
+                        seg_out[c0 + j] = make_int2((int)(base + off[j]), cnt[j]);
             }
         }
-        if (act && sl == 0) seg_out[c] = make_int2((int)cpos, min(emit[ci], room));
         wave_lds_sync();
     }
 }
@@ -643,8 +669,14 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             (per ? k_fof_p2n<true> : k_fof_p2n<false>)<<<blocks_for(n_par, WPB), 64 * WPB, 0, s>>>(
                 par_spl, t->nodes[p].as<Node>(), (int)n_par, whole_par, whole[p].as<int>(),
                 d_uf.as<int>(), b2, bn, L);
-            (per ? k_fof_step<true> : k_fof_step<false>)<<<blocks_for(n_par, WPB), 64 * WPB, 0, s>>>(
-                seg_in, list_in, par_spl, t->nodes[p].as<Node>(), (int)n_par, b2, bn,
+            // a top parent has up to ngr children, others a few: enough items
+            // for one pass over most parents' children
+            const bool many = n_par >= FOF_MANY;
+            const int nsub = many ? 1 : (top ? (t->opts.ngr + 3) / 4 : 2);
+            const auto step = many ? (per ? k_fof_step<true, 8> : k_fof_step<false, 8>)
+                                   : (per ? k_fof_step<true, 4> : k_fof_step<false, 4>);
+            step<<<blocks_for(n_par * nsub, WPB), 64 * WPB, 0, s>>>(
+                seg_in, list_in, par_spl, t->nodes[p].as<Node>(), (int)n_par, nsub, b2, bn,
                 whole[p].as<int>(), d_uf.as<int>(), segs[p].as<int2>(), lists[p].as<int2>(),
                 ctr + (size_t)p * LIST_ARENAS, cap[p] / LIST_ARENAS, ctr + CTR_FLAG, L);
         }

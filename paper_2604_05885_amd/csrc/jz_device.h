@@ -351,6 +351,55 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
+// The children of a receiver's listed sources, for the node walks: appends to
+// FI[nN ...] (LDS, CAP entries) the indices of the children of the entries from
+// position t of the list on that keep(entry, valid, stop) takes, until FI is
+// full or the list ends. Every lane looks at one entry at a time; keep sets the
+// wave-uniform stop where no later entry is to be taken. A source with more
+// children than CAP is taken in parts (skip: those already taken).
+template <int CAP, class KEEP>
+__device__ __forceinline__ void list_children(const int2 *__restrict__ gl, int len,
+                                              const int *__restrict__ par_spl, int *FI, int &nN,
+                                              int &t, int &skip, KEEP &&keep) {
+    const int lane = lane_id();
+    while (t < len && nN < CAP) {
+        int2 e = make_int2(0, 0);
+        const bool valid = t + lane < len;
+        if (valid) e = gl[t + lane];
+        bool stop = false;
+        int s0 = 0, c = 0;
+        if (keep(e, valid, stop)) {
+            s0 = par_spl[e.x];
+            c = par_spl[e.x + 1] - s0;
+            if (lane == 0) {
+                s0 += skip;
+                c -= skip;
+            }
+        }
+        if (stop) {
+            t = len;
+            break;
+        }
+        const int incl = wave_incl_scan(c);
+        const int take = (int)__popcll(__ballot(nN + incl <= CAP));  // a prefix of the lanes
+        if (take == 0) {
+            // more children than there is room for
+            if (nN > 0) break;
+            const int f0 = __builtin_amdgcn_readlane(s0, 0);
+            for (int f = lane; f < CAP; f += 64) FI[f] = f0 + f;
+            nN = CAP;
+            skip += CAP;
+            return;
+        }
+        if (lane < take)
+            for (int q = 0; q < c; ++q) FI[nN + incl - c + q] = s0 + q;
+        nN += __builtin_amdgcn_readlane(incl, take - 1);
+        t += take;
+        skip = 0;
+        if (take < 64) break;
+    }
+}
+
 // Order LDS traffic of one wave: everything written before is visible to the
 // wave's later reads (the wave's lanes run in lockstep; the fence makes the
 // compiler wait for outstanding LDS operations and keeps them in order).

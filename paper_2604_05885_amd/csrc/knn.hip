@@ -184,6 +184,9 @@ __global__ __launch_bounds__(64) void k_walk_items(const int *__restrict__ par_s
 }
 
 constexpr int FCAP = 1024;  // source children listed in LDS at a time
+// Lists longer than this (and up to sort_max) are put in r_low order in HBM
+// before a wave walks them; a shorter one is at most 8 loads per phase.
+constexpr int WALK_PRESORT = 512;
 
 // Level step of the kNN walk: one wave per work item, a receiving parent P and
 // up to WALK_CB of its children. The children's boxes sit in scalar registers;
@@ -203,9 +206,9 @@ constexpr int FCAP = 1024;  // source children listed in LDS at a time
 // through LDS, the level spent its time waiting for a chain of loads and LDS
 // steps per batch of 128, and merging heaps: 0.20 + 0.27 + 0.46 + 2.21 ms from
 // the top to the leaf level at 2^24 clustered points, k = 16, now 0.04 + 0.06 +
-// 0.20 + 1.03 (8 children per item instead of 4: 0.05 + 0.07 + 0.27 + 0.92, and
-// 0.11 ms instead of 0.07 for the one level of 5 10^4 points); 0.37 + 0.27 ms
-// at 10^6 uniform points, now 0.09 + 0.07.
+// 0.19 + 0.96 (8 children per item instead of 4: 0.05 + 0.07 + 0.27 + 0.92 to
+// 1.03, and 0.11 ms instead of 0.07 for the one level of 5 10^4 points); 0.37 +
+// 0.27 ms at 10^6 uniform points, now 0.09 + 0.06.
 template <bool PER>
 __global__ __launch_bounds__(64 * WPB) void k_knn_step(
     const int2 *__restrict__ items, const unsigned long long *__restrict__ n_items, int cb,
@@ -288,42 +291,12 @@ __global__ __launch_bounds__(64 * WPB) void k_knn_step(
         nN += c;
     };
     auto fill_list = [&]() __attribute__((always_inline)) {
-        while (t < len && nN < FCAP) {
-            int2 e = make_int2(0, 0);
-            if (t + lane < len) e = gl[t + lane];
-            const bool in = t + lane < len && __int_as_float(e.y) <= Rw;
-            const bool keep = in && e.x != P;
-            int s0 = 0, c = 0;
-            if (keep) {
-                s0 = par_spl[e.x];
-                c = par_spl[e.x + 1] - s0;
-                if (lane == 0) {
-                    s0 += skip;
-                    c -= skip;
-                }
-            }
-            if (sorted && !__ballot(in)) {
-                t = len;
-                break;
-            }
-            const int incl = wave_incl_scan(c);
-            const int take = (int)__popcll(__ballot(nN + incl <= FCAP));  // a prefix of the lanes
-            if (take == 0) {
-                // more children than there is room for
-                if (nN > 0) break;
-                const int f0 = __builtin_amdgcn_readlane(s0, 0);
-                for (int f = lane; f < FCAP; f += 64) FI[f] = f0 + f;
-                nN = FCAP;
-                skip += FCAP;
-                return;
-            }
-            if (lane < take)
-                for (int q = 0; q < c; ++q) FI[nN + incl - c + q] = s0 + q;
-            nN += __builtin_amdgcn_readlane(incl, take - 1);
-            t += take;
-            skip = 0;
-            if (take < 64 && t < len) break;
-        }
+        list_children<FCAP>(gl, len, par_spl, FI, nN, t, skip,
+                            [&](const int2 &e, bool valid, bool &stop) {
+                                const bool in = valid && __int_as_float(e.y) <= Rw;
+                                stop = sorted && !__ballot(in);
+                                return in && e.x != P;
+                            });
     };
     long long base = 0;
     bool single = true;  // the whole stream fits FI
@@ -1315,11 +1288,10 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
         cap[p] = initial_cap(t, CAP_KNN, k, p);
         JZ_TRY(segs[p].get(ac, t->L[p] * sizeof(int2), s));
     }
-    // Lists longer than a wave sorts in LDS (LCAP entries in the walk, whose
-    // items of one parent share its list, 1024 in the leaf stage), up to
-    // sort_max, are sorted in HBM before their level.
+    // Lists longer than WALK_PRESORT in the walk and LEAF_PRESORT in the leaf
+    // stage, up to sort_max, are sorted in HBM before their level.
     const int sort_max = t->opts.sort_max;
-    const int walk_cap = LCAP, leaf_cap = std::min(sort_max, 1024);
+    const int walk_cap = WALK_PRESORT, leaf_cap = std::min(sort_max, 1024);
     // work items of the walk (at most one per parent plus one per cb
     // children, or per WALK_CB_LONG children of a parent with a long list):
     // WALK_CB children per item at the leaf level, WALK_CB_UP
