@@ -7,12 +7,15 @@
 //     stable radix sort on the label bits gives group order: groups by
 //     ascending label, members of a group as one block of ascending input
 //     indices
-//  2. member counts per label; group starts (a key differing from the one
-//     before); the starts of groups with >= min_members members compacted in
-//     order: group g = (label, first position, count)
-//  3. centre of mass (and of velocity): per-wave sums over the runs of one
-//     group (positions are in group order, so a wave meets few groups), one
-//     binary64 atomic per group, component and wave
+//  2. group starts (a key differing from the one before); a group has at least
+//     min_members members if the key min_members - 1 positions on is still its
+//     own; the starts of those groups compacted in order, their counts found by
+//     a galloping search for the end of their keys: group g = (label, first
+//     position, count)
+//  3. centre of mass (and of velocity): sums over the runs of one group
+//     (positions are in group order, so a wave meets few groups), one binary64
+//     atomic per group, component and wave; a wave whose 1024 positions belong
+//     to one group adds them up per lane first
 //  4. inertia radius: the same over |x - cm|^2, then sqrt(sum / count)
 #include <hip/hip_runtime.h>
 
@@ -27,33 +30,51 @@ namespace {
 
 constexpr int CAT_BLOCK = 1024;  // positions per compaction block
 
+// (counting the members of every label here, with an atomic per point, took
+// 4.2 ms at 2^22 clustered points: a million of them meet in one address)
 __global__ __launch_bounds__(256) void k_cat_keys(const int32_t *__restrict__ label, int64_t n,
                                                   uint64_t *__restrict__ keys,
-                                                  uint32_t *__restrict__ vals,
-                                                  int *__restrict__ count) {
+                                                  uint32_t *__restrict__ vals) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int l = label[i];
-    keys[i] = (uint64_t)(uint32_t)l;
+    keys[i] = (uint64_t)(uint32_t)label[i];
     vals[i] = (uint32_t)i;
-    atomicAdd(count + l, 1);
 }
 
-__device__ __forceinline__ bool cat_start(const uint64_t *keys, const int *count, int64_t j,
+// whether position j starts a group of at least min_members members
+__device__ __forceinline__ bool cat_start(const uint64_t *keys, int64_t n, int64_t j,
                                           int min_members) {
-    return (j == 0 || keys[j] != keys[j - 1]) && count[keys[j]] >= min_members;
+    const int64_t e = j + min_members - 1;
+    return e < n && (j == 0 || keys[j] != keys[j - 1]) && keys[e] == keys[j];
+}
+
+// members of the group that starts at position j
+__device__ __forceinline__ int cat_count(const uint64_t *keys, int64_t n, int64_t j,
+                                         int min_members) {
+    const uint64_t key = keys[j];
+    int64_t good = j + min_members - 1, bad = n, step = min_members;
+    while (bad - good > 1) {
+        const int64_t e = good + step < bad ? good + step : good + (bad - good) / 2;
+        if (keys[e] == key) {
+            good = e;
+            step <<= 1;
+        } else {
+            bad = e;
+        }
+    }
+    return (int)(good - j + 1);
 }
 
 // qualifying group starts per block of CAT_BLOCK positions
 __global__ __launch_bounds__(256) void k_cat_block_counts(const uint64_t *__restrict__ keys,
-                                                          const int *__restrict__ count, int64_t n,
-                                                          int min_members, int *__restrict__ bcnt) {
+                                                          int64_t n, int min_members,
+                                                          int *__restrict__ bcnt) {
     __shared__ int s_c[4];
     const int64_t b0 = (int64_t)blockIdx.x * CAT_BLOCK;
     int c = 0;
     for (int t = threadIdx.x; t < CAT_BLOCK; t += 256) {
         const int64_t j = b0 + t;
-        if (j < n && cat_start(keys, count, j, min_members)) ++c;
+        if (j < n && cat_start(keys, n, j, min_members)) ++c;
     }
     c = wave_sum_i(c);
     if (lane_id() == 0) s_c[threadIdx.x >> 6] = c;
@@ -88,8 +109,8 @@ __global__ __launch_bounds__(1024) void k_cat_scan(const int *__restrict__ bcnt,
 // the qualifying groups in order: label, first position, count; gidx[label]
 // = group number (gidx is -1 elsewhere)
 __global__ __launch_bounds__(256) void k_cat_compact(const uint64_t *__restrict__ keys,
-                                                     const int *__restrict__ count, int64_t n,
-                                                     int min_members, const int *__restrict__ boff,
+                                                     int64_t n, int min_members,
+                                                     const int *__restrict__ boff,
                                                      jz_group *__restrict__ groups,
                                                      int64_t max_groups, int *__restrict__ gidx) {
     __shared__ int s_w[4];
@@ -97,7 +118,7 @@ __global__ __launch_bounds__(256) void k_cat_compact(const uint64_t *__restrict_
     int base = boff[blockIdx.x];
     for (int t0 = 0; t0 < CAT_BLOCK; t0 += 256) {
         const int64_t j = b0 + t0 + threadIdx.x;
-        const bool st = j < n && cat_start(keys, count, j, min_members);
+        const bool st = j < n && cat_start(keys, n, j, min_members);
         const uint64_t m = __ballot(st);
         const int w = threadIdx.x >> 6;
         if (lane_id() == 0) s_w[w] = __popcll(m);
@@ -111,7 +132,7 @@ __global__ __launch_bounds__(256) void k_cat_compact(const uint64_t *__restrict_
             if (g < max_groups) {
                 jz_group gr{};
                 gr.label = l;
-                gr.count = count[l];
+                gr.count = cat_count(keys, n, j, min_members);
                 gr.first = j;
                 groups[g] = gr;
             }
@@ -121,72 +142,97 @@ __global__ __launch_bounds__(256) void k_cat_compact(const uint64_t *__restrict_
     }
 }
 
+// the sum over the wave, in every lane
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = (uint32_t)dpp_i<CTRL>((int)(uint32_t)b);
+    const uint64_t hi = (uint32_t)dpp_i<CTRL>((int)(b >> 32));
+    return __builtin_bit_cast(double, hi << 32 | lo);
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_d<DPP_XOR1>(v);
+    v += dpp_d<DPP_XOR2>(v);
+    v += dpp_d<DPP_HALF_MIRROR>(v);
+    v += dpp_d<DPP_MIRROR>(v);
+    v += swap16_d(v);
+    return v + swap32_d(v);
 }
 
-// Pass 1 (second = false): sums of positions (and velocities) per group.
-// Pass 2 (second = true): sums of |x - cm|^2 per group, cm from pass 1.
+// Pass 1 (SECOND = false): sums of positions (and velocities) per group.
+// Pass 2 (SECOND = true): sums of |x - cm|^2 per group, cm from pass 1.
 // acc[g] holds 8 doubles: sx, sy, sz, svx, svy, svz, sd2, unused.
+// A wave takes CAT_RUN * 64 positions: as one run if they belong to one group,
+// else 64 at a time, one reduction per group met. (With 64 per wave, the
+// reductions through LDS permutes and the atomics on the largest groups took
+// 0.31 ms per pass at 2^22 clustered points.)
+constexpr int CAT_RUN = 16;
+template <bool SECOND>
 __global__ __launch_bounds__(256) void k_cat_sums(const uint64_t *__restrict__ keys,
                                                   const uint32_t *__restrict__ order, int64_t n,
                                                   const int *__restrict__ gidx,
                                                   const float *__restrict__ pts,
-                                                  const float *__restrict__ vel, bool second,
+                                                  const float *__restrict__ vel,
                                                   const jz_group *__restrict__ groups,
                                                   double *__restrict__ acc) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int g = -1;
-    double x = 0, y = 0, z = 0, a = 0, b = 0, c = 0;
-    if (j < n) {
-        g = gidx[keys[j]];
-        if (g >= 0) {
-            const int64_t i = order[j];
-            x = pts[3 * i];
-            y = pts[3 * i + 1];
-            z = pts[3 * i + 2];
-            if (second) {
-                const jz_group &gr = groups[g];
-                const double dx = x - gr.cm[0], dy = y - gr.cm[1], dz = z - gr.cm[2];
-                x = (dx * dx + dy * dy) + dz * dz;
-            } else if (vel) {
-                a = vel[3 * i];
-                b = vel[3 * i + 1];
-                c = vel[3 * i + 2];
-            }
+    const int lane = lane_id();
+    const int64_t w0 =
+        (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * (CAT_RUN * 64);
+    if (w0 >= n) return;
+    const int64_t w1 = w0 + CAT_RUN * 64 < n ? w0 + CAT_RUN * 64 : n;
+    double v[6];  // this lane's x, y, z (SECOND: |x - cm|^2) and velocity
+    auto load = [&](int64_t j, int g) {
+        const int64_t i = order[j];
+        v[0] = pts[3 * i];
+        v[1] = pts[3 * i + 1];
+        v[2] = pts[3 * i + 2];
+        if (SECOND) {
+            const jz_group &gr = groups[g];
+            const double dx = v[0] - gr.cm[0], dy = v[1] - gr.cm[1], dz = v[2] - gr.cm[2];
+            v[0] = (dx * dx + dy * dy) + dz * dz;
+        } else if (vel) {
+            v[3] = vel[3 * i];
+            v[4] = vel[3 * i + 1];
+            v[5] = vel[3 * i + 2];
         }
+    };
+    const int nv = SECOND ? 1 : (vel ? 6 : 3);
+    auto add = [&](const double (&s)[6], int g) {
+        double *dst = acc + (size_t)g * 8;
+#pragma unroll
+        for (int d = 0; d < (SECOND ? 1 : 6); ++d) {
+            if (d >= nv) continue;
+            const double t = wave_sum_d(s[d]);
+            if (lane == 0) atomicAdd(dst + (SECOND ? 6 : d), t);
+        }
+    };
+    if (keys[w0] == keys[w1 - 1]) {
+        const int g = uni(gidx[keys[w0]]);
+        if (g < 0) return;
+        double s[6] = {0, 0, 0, 0, 0, 0};
+        for (int64_t j = w0 + lane; j < w1; j += 64) {
+            load(j, g);
+#pragma unroll
+            for (int d = 0; d < (SECOND ? 1 : 6); ++d)
+                if (d < nv) s[d] += v[d];
+        }
+        add(s, g);
+        return;
     }
-    uint64_t pending = __ballot(g >= 0);
-    while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int g0 = __builtin_amdgcn_readlane(g, leader);
-        const bool mine = g == g0;
-        pending &= ~__ballot(mine);
-        double *dst = acc + (size_t)g0 * 8;
-        if (second) {
-            const double s = wave_sum_d(mine ? x : 0.0);
-            if (lane_id() == leader) atomicAdd(dst + 6, s);
-        } else {
-            const double sx = wave_sum_d(mine ? x : 0.0);
-            const double sy = wave_sum_d(mine ? y : 0.0);
-            const double sz = wave_sum_d(mine ? z : 0.0);
-            if (lane_id() == leader) {
-                atomicAdd(dst + 0, sx);
-                atomicAdd(dst + 1, sy);
-                atomicAdd(dst + 2, sz);
-            }
-            if (vel) {
-                const double sa = wave_sum_d(mine ? a : 0.0);
-                const double sb = wave_sum_d(mine ? b : 0.0);
-                const double sc = wave_sum_d(mine ? c : 0.0);
-                if (lane_id() == leader) {
-                    atomicAdd(dst + 3, sa);
-                    atomicAdd(dst + 4, sb);
-                    atomicAdd(dst + 5, sc);
-                }
-            }
+    for (int64_t j0 = w0; j0 < w1; j0 += 64) {
+        const int64_t j = j0 + lane;
+        const int g = j < w1 ? gidx[keys[j]] : -1;
+        if (g >= 0) load(j, g);
+        uint64_t pending = __ballot(g >= 0);
+        while (pending) {
+            const int g0 = __builtin_amdgcn_readlane(g, __ffsll((unsigned long long)pending) - 1);
+            const bool mine = g == g0;
+            pending &= ~__ballot(mine);
+            double s[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int d = 0; d < (SECOND ? 1 : 6); ++d)
+                if (d < nv && mine) s[d] = v[d];
+            add(s, g0);
         }
     }
 }
@@ -273,15 +319,12 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     JZ_TRY(run_fof(t, &b2, lab, s));
 
     // 1: group order
-    DBuf k0, v0, k1, v1, d_count;
+    DBuf k0, v0, k1, v1;
     JZ_TRY(k0.get(ac, (size_t)n * sizeof(uint64_t), s));
     JZ_TRY(v0.get(ac, (size_t)n * sizeof(uint32_t), s));
     JZ_TRY(k1.get(ac, (size_t)n * sizeof(uint64_t), s));
     JZ_TRY(v1.get(ac, (size_t)n * sizeof(uint32_t), s));
-    JZ_TRY(d_count.get(ac, (size_t)n * sizeof(int), s));
-    k_fill_i32<<<blocks_for(n, 256), 256, 0, s>>>(d_count.as<int>(), n, 0);
-    k_cat_keys<<<blocks_for(n, 256), 256, 0, s>>>(lab, n, k0.as<uint64_t>(), v0.as<uint32_t>(),
-                                                  d_count.as<int>());
+    k_cat_keys<<<blocks_for(n, 256), 256, 0, s>>>(lab, n, k0.as<uint64_t>(), v0.as<uint32_t>());
     JZ_HIP(hipGetLastError());
     int bits = 0;
     while (bits < 31 && ((int64_t)1 << bits) < n) ++bits;
@@ -296,12 +339,11 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     JZ_TRY(d_total.get(ac, sizeof(long long), s));
     JZ_TRY(d_gidx.get(ac, (size_t)n * sizeof(int), s));
     k_fill_i32<<<blocks_for(n, 256), 256, 0, s>>>(d_gidx.as<int>(), n, -1);
-    k_cat_block_counts<<<nb, 256, 0, s>>>(k0.as<uint64_t>(), d_count.as<int>(), n, min_members,
-                                          d_bcnt.as<int>());
+    k_cat_block_counts<<<nb, 256, 0, s>>>(k0.as<uint64_t>(), n, min_members, d_bcnt.as<int>());
     k_cat_scan<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), nb, d_boff.as<int>(),
                                   d_total.as<long long>());
-    k_cat_compact<<<nb, 256, 0, s>>>(k0.as<uint64_t>(), d_count.as<int>(), n, min_members,
-                                     d_boff.as<int>(), groups, max_groups, d_gidx.as<int>());
+    k_cat_compact<<<nb, 256, 0, s>>>(k0.as<uint64_t>(), n, min_members, d_boff.as<int>(), groups,
+                                     max_groups, d_gidx.as<int>());
     JZ_HIP(hipGetLastError());
     long long G = 0;
     JZ_HIP(hipMemcpyAsync(&G, d_total.p, sizeof(G), hipMemcpyDeviceToHost, s));
@@ -319,10 +361,11 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     const float *points = d_xyz.as<float>();
     JZ_TRY(d_acc.get(ac, (size_t)G * 8 * sizeof(double), s));
     JZ_TRY(zero_words(d_acc.as<unsigned long long>(), (size_t)G * 8, s));
+    const unsigned sb = blocks_for(n, 256 * CAT_RUN);
     for (int pass = 0; pass < 2; ++pass) {
-        k_cat_sums<<<blocks_for(n, 256), 256, 0, s>>>(k0.as<uint64_t>(), v0.as<uint32_t>(), n,
-                                                      d_gidx.as<int>(), points, vel, pass == 1,
-                                                      groups, d_acc.as<double>());
+        (pass ? k_cat_sums<true> : k_cat_sums<false>)<<<sb, 256, 0, s>>>(
+            k0.as<uint64_t>(), v0.as<uint32_t>(), n, d_gidx.as<int>(), points, vel, groups,
+            d_acc.as<double>());
         k_cat_finish<<<blocks_for(G, 256), 256, 0, s>>>(groups, G, d_acc.as<double>(), pass == 1);
     }
     JZ_HIP(hipGetLastError());
