@@ -312,7 +312,7 @@ jz_status make_tree_impl(const float *points, const int64_t *offsets, int nsets,
     t->set_bits = sb;
     hipStream_t s = (hipStream_t)stream;
     jz_status st = t->d_set_off.get(&t->ac, (nsets + 1) * sizeof(int64_t), s);
-    if (st == JZ_OK) {
+    if (st == JZ_OK && nsets > 1) {  // (no kernel reads a single set's)
         hipError_t e = hipMemcpyAsync(t->d_set_off.p, t->set_off.data(), (nsets + 1) * sizeof(int64_t),
                                       hipMemcpyHostToDevice, s);
         if (e != hipSuccess) st = jz_hip_fail(e, "hipMemcpyAsync(set offsets)", __FILE__, __LINE__);

@@ -137,20 +137,6 @@ __global__ __launch_bounds__(256) void k_morton(const float *__restrict__ pts, i
         if (s_h[i]) atomicAdd(hist + i, s_h[i]);
 }
 
-// exclusive scan of each pass's 256 digit counts (one block per pass)
-__global__ __launch_bounds__(256) void k_hist_scan(const uint32_t *__restrict__ hist,
-                                                   uint32_t *__restrict__ doff) {
-    __shared__ int s_w[4];
-    const int p = blockIdx.x, t = threadIdx.x;
-    int v = (int)hist[p * 256 + t];
-    int inc = wave_incl_scan(v);
-    if (lane_id() == 63) s_w[t >> 6] = inc;
-    __syncthreads();
-    int add = 0;
-    for (int w = 0; w < (t >> 6); ++w) add += s_w[w];
-    doff[p * 256 + t] = (uint32_t)(inc - v + add);
-}
-
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
 constexpr int RS_ITEMS = 24;  // 6144 keys per tile: two tiles fill a CU's LDS
@@ -170,23 +156,30 @@ __device__ __forceinline__ void st_u64(uint64_t *p, uint64_t v) {
 // id from an atomic counter (so every lower id belongs to a workgroup that has
 // started); each tile ranks its keys per wave with ballots, publishes its digit
 // counts, looks back over earlier tiles for its global offsets, stages the
-// tile in LDS in digit order and writes it out with coalesced runs.
+// tile in LDS in digit order and writes it out with coalesced runs. `hist`: the
+// pass's 256 digit counts over all keys, whose exclusive scan every tile takes
+// for itself (a launch of its own took as long as a small pass).
 __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
-    uint32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ doff,
+    uint32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ hist,
     uint64_t *__restrict__ status, int *__restrict__ tile_ctr) {
     __shared__ uint64_t s_k[RS_TILE];
     __shared__ uint32_t s_v[RS_TILE];
     __shared__ uint32_t s_wh[RS_WAVES][256];
     __shared__ uint32_t s_excl[256];
     __shared__ uint64_t s_gb[256];
-    __shared__ int s_tmp[RS_WAVES];
+    __shared__ int s_tmp[RS_WAVES], s_hist[RS_WAVES];
     __shared__ int s_tile;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid == 0) s_tile = atomicAdd(tile_ctr, 1);
     for (int i = tid; i < RS_WAVES * 256; i += RS_THREADS) (&s_wh[0][0])[i] = 0;
+    const int hv = (int)hist[tid];
+    const int hinc = wave_incl_scan(hv);
+    if (lane == 63) s_hist[w] = hinc;
     __syncthreads();
     const int tile = s_tile;
+    int doff = hinc - hv;  // keys of the lower digits
+    for (int ww = 0; ww < w; ++ww) doff += s_hist[ww];
     const int64_t base = (int64_t)tile * RS_TILE;
     const int tn = (int)((n - base) < RS_TILE ? (n - base) : RS_TILE);
 
@@ -249,7 +242,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
         }
         st_u64(mine, FLAG_INC | (excl + tot));
     }
-    s_gb[tid] = (uint64_t)doff[tid] + excl;
+    s_gb[tid] = (uint64_t)(uint32_t)doff + excl;
     {
         const int vi = (int)tot;
         const int inc = wave_incl_scan(vi);
@@ -338,6 +331,25 @@ constexpr int LF_MAXW = 64;
 // thread takes the same ~2 x 7 steps instead of a scan of up to 2 x nmax0.
 constexpr int LF_SPAN = LF_TILE + 2 * LF_MAXW + 2;
 constexpr int LF_LOG = 7;  // 2^6 = LF_MAXW: levels 0..6
+// whether the gap at position c of the tables (mx(k): the table of the 2^k) is
+// a split, with a window of W gaps on either side
+template <class MX>
+__device__ __forceinline__ bool leaf_split(MX &&mx, int c, int W, int nmax0) {
+    const int lv = mx(0)[c];
+    if (lv >= kBoundaryLevel) return true;
+    // left: move cur down while [cur - 2^k, cur) holds no greater level
+    int cur = c;
+    for (int k = LF_LOG - 1; k >= 0; --k)
+        if (cur - (1 << k) >= c - W && mx(k)[cur - (1 << k)] <= lv) cur -= 1 << k;
+    const int dl = cur - 1 >= c - W ? c - (cur - 1) : 0;
+    if (dl == 0) return true;
+    // right: move cur up while [cur, cur + 2^k) holds no greater level
+    cur = c + 1;
+    for (int k = LF_LOG - 1; k >= 0; --k)
+        if (cur + (1 << k) - 1 <= c + W && mx(k)[cur] <= lv) cur += 1 << k;
+    const int dr = cur <= c + W ? cur - c : 0;
+    return dr == 0 || dl + dr > nmax0;
+}
 __global__ __launch_bounds__(256) void k_leaf_flags(const uint64_t *__restrict__ keys, int64_t n,
                                                     int bits3, int has_sets, int nmax0,
                                                     uint8_t *__restrict__ flags,
@@ -360,27 +372,8 @@ __global__ __launch_bounds__(256) void k_leaf_flags(const uint64_t *__restrict__
     for (int t = threadIdx.x; t < LF_TILE; t += blockDim.x) {
         const int64_t g = g0 + t;
         if (g > n) break;
-        const int c = t + W;  // g's position in the tile
-        const int lv = s_mx[0][c];
-        uint8_t f;
-        if (lv >= kBoundaryLevel) {
-            f = 1;
-        } else {
-            // left: move cur down while [cur - 2^k, cur) holds no greater level
-            int cur = c;
-            for (int k = LF_LOG - 1; k >= 0; --k)
-                if (cur - (1 << k) >= c - W && s_mx[k][cur - (1 << k)] <= lv) cur -= 1 << k;
-            const int dl = cur - 1 >= c - W ? c - (cur - 1) : 0;
-            int dr = 0;
-            if (dl) {
-                // right: move cur up while [cur, cur + 2^k) holds no greater level
-                cur = c + 1;
-                for (int k = LF_LOG - 1; k >= 0; --k)
-                    if (cur + (1 << k) - 1 <= c + W && s_mx[k][cur] <= lv) cur += 1 << k;
-                dr = cur <= c + W ? cur - c : 0;
-            }
-            f = (dl == 0 || dr == 0 || dl + dr > nmax0) ? 1 : 0;
-        }
+        // t + W: g's position in the tile
+        const uint8_t f = leaf_split([&](int k) { return s_mx[k]; }, t + W, W, nmax0) ? 1 : 0;
         flags[g] = f;
         cnt += f;
     }
@@ -415,7 +408,8 @@ __global__ __launch_bounds__(1024) void k_scan_counts(const int *__restrict__ cn
     if (t == 1023) *total = inc + add;
 }
 
-// ordered compaction of flagged items: out[pos] = item, out2[pos] = map[item]
+// ordered compaction of flagged items: out[pos] = item, and, if given,
+// out2[pos] = map[item] (map NULL: item)
 __global__ __launch_bounds__(256) void k_compact(const uint8_t *__restrict__ flags,
                                                  int64_t nitems_max,
                                                  const int *__restrict__ nitems_dev,
@@ -443,7 +437,7 @@ __global__ __launch_bounds__(256) void k_compact(const uint8_t *__restrict__ fla
         if (f) {
             const int pos = run + add + pre;
             out[pos] = (int)item;
-            if (map) out2[pos] = map[item];
+            if (out2) out2[pos] = map ? map[item] : (int)item;
         }
         run += tot;
         __syncthreads();
@@ -511,7 +505,8 @@ __global__ __launch_bounds__(256) void k_split_sizes(const uint64_t *__restrict_
 }
 
 // Plane p flags over the plane p-1 splits: keep the ends and every split
-// whose node size exceeds N_max^(p).
+// whose node size exceeds N_max^(p). lsi_prev: their leaf splits (NULL: the
+// plane below is the leaf plane).
 __global__ __launch_bounds__(256) void k_plane_flags(const int *__restrict__ lsi_prev,
                                                      const int *__restrict__ cnt_prev,
                                                      const int *__restrict__ nsz, int64_t nmax,
@@ -525,7 +520,7 @@ __global__ __launch_bounds__(256) void k_plane_flags(const int *__restrict__ lsi
     for (int t = threadIdx.x; t < LF_TILE; t += blockDim.x) {
         const int64_t j = base + t;
         if (j >= m) break;
-        const int ls = lsi_prev[j];
+        const int ls = lsi_prev ? lsi_prev[j] : (int)j;
         const uint8_t f = (j == 0 || j == m - 1 || (int64_t)nsz[ls] > nmax ||
                            (int)slv[ls] > lvl_max) ? 1 : 0;
         flags[j] = f;
@@ -579,18 +574,8 @@ __global__ __launch_bounds__(256) void k_reg_leaf_flags(const uint64_t *__restri
     if (threadIdx.x == 0) blk_cnt[blockIdx.x] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
 }
 
-__global__ void k_iota(int *__restrict__ a, const int *__restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < *cnt) a[i] = (int)i;
-}
-
 // leaves: one wave per leaf, lanes over its points
-__global__ __launch_bounds__(256) void k_leaf_geom(const float4 *__restrict__ pts,
-                                                   const int *__restrict__ spl, int64_t L,
-                                                   Node *__restrict__ nodes) {
-    const int64_t a = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (a >= L) return;
-    const int s0 = spl[a], s1 = spl[a + 1];
+__device__ __forceinline__ void leaf_box(const float4 *pts, int s0, int s1, Node *node) {
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int i = s0 + lane_id(); i < s1; i += 64) {
         const float4 p = pts[i];
@@ -609,8 +594,16 @@ __global__ __launch_bounds__(256) void k_leaf_geom(const float4 *__restrict__ pt
         nd.hi[0] = hi[0]; nd.hi[1] = hi[1]; nd.hi[2] = hi[2];
         nd.start = s0;
         nd.count = s1 - s0;
-        nodes[a] = nd;
+        *node = nd;
     }
+}
+
+__global__ __launch_bounds__(256) void k_leaf_geom(const float4 *__restrict__ pts,
+                                                   const int *__restrict__ spl, int64_t L,
+                                                   Node *__restrict__ nodes) {
+    const int64_t a = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (a >= L) return;
+    leaf_box(pts, spl[a], spl[a + 1], nodes + a);
 }
 
 // coarser planes: one wave per node, lanes over its children
@@ -647,6 +640,206 @@ __global__ __launch_bounds__(256) void k_node_geom(const Node *__restrict__ chil
     }
 }
 
+// Before a build: bbox empty, the histogram, sort status and counters zero.
+__global__ __launch_bounds__(256) void k_build_init(unsigned long long *__restrict__ zero, size_t n,
+                                                    int *__restrict__ meta) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = i0; i < n; i += (size_t)gridDim.x * blockDim.x) zero[i] = 0;
+    if (i0 < 8) meta[i0] = i0 < 3 ? INT_MAX : (i0 < 6 ? INT_MIN : 0);
+}
+
+// Super nodes of ngr top nodes and their dense lists, for a single set: row i
+// of the kNN list names all S super nodes, row i of the FoF list those from i
+// on (Alg. 1 lines 1-2).
+__global__ __launch_bounds__(256) void k_top_lists(int S, int LT, int ngr, int *__restrict__ spl,
+                                                   int2 *__restrict__ kseg,
+                                                   int2 *__restrict__ klist,
+                                                   int2 *__restrict__ fseg,
+                                                   int2 *__restrict__ flist) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    auto frow = [&](int64_t i) { return i * S - i * (i - 1) / 2; };
+    for (int64_t i = t0; i <= S; i += stride) {
+        spl[i] = i < S ? (int)i * ngr : LT;
+        if (i == S) break;
+        kseg[i] = make_int2((int)(i * S), S);
+        fseg[i] = make_int2((int)frow(i), S - (int)i);
+    }
+    for (int64_t e = t0; e < (int64_t)S * S; e += stride) {
+        const int64_t i = e / S, j = e - i * S;
+        klist[e] = make_int2((int)j, 0);
+        if (j >= i) flist[frow(i) + j - i] = make_int2((int)j, 0);
+    }
+}
+
+// The whole leaf plane of a set of at most SMALL_N points in one workgroup:
+// bounding box, keys, sort, sorted points, splits and leaf boxes, with the
+// definitions of the kernels above (key and input index packed in one word,
+// whose order is that of the stable radix sort). What bounds a set this small
+// is the number of launches: 13 of them and three transfers, 0.25 ms of a build
+// of 1000 points, against one launch of about 0.03 ms.
+// hdr: leaf splits, then bounding box and non-finite flag as k_bbox leaves them.
+constexpr int SMALL_N = 4096;
+constexpr int SMALL_IDX_BITS = 12;  // of the input index in a packed key
+constexpr int SMALL_NT = 1024;
+__global__ __launch_bounds__(SMALL_NT) void k_build_small(const float *__restrict__ pts, int n,
+                                                          int bits, int nmax0,
+                                                          float4 *__restrict__ out,
+                                                          int *__restrict__ spl,
+                                                          Node *__restrict__ nodes,
+                                                          int *__restrict__ hdr) {
+    constexpr int NW = SMALL_NT / 64;
+    constexpr int SPAN = SMALL_N + 1 + 2 * LF_MAXW;
+    __shared__ uint64_t s_key[SMALL_N];  // later the upper tables of s_mx
+    __shared__ uint8_t s_mx0[SPAN];
+    __shared__ int s_spl[SMALL_N + 1];
+    __shared__ float s_box[NW][6];
+    __shared__ int s_w[NW + 1], s_bad;
+    static_assert(sizeof(uint64_t) * SMALL_N >= (size_t)(LF_LOG - 1) * SPAN, "tables fit");
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // 1: bounding box
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    int bad = 0;
+    for (int i = tid; i < n; i += SMALL_NT) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float v = pts[3 * i + a];
+            bad |= !isfinite(v);
+            lo[a] = fminf(lo[a], v);
+            hi[a] = fmaxf(hi[a], v);
+        }
+    }
+    if (tid == 0) s_bad = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = wave_min(lo[a]);
+        hi[a] = wave_max(hi[a]);
+    }
+    if (lane < 3) {
+        s_box[w][lane] = lane == 0 ? lo[0] : (lane == 1 ? lo[1] : lo[2]);
+        s_box[w][3 + lane] = lane == 0 ? hi[0] : (lane == 1 ? hi[1] : hi[2]);
+    }
+    __syncthreads();
+    if (bad) s_bad = 1;
+    float ext = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = s_box[0][a];
+        hi[a] = s_box[0][3 + a];
+        for (int ww = 1; ww < NW; ++ww) {
+            lo[a] = fminf(lo[a], s_box[ww][a]);
+            hi[a] = fmaxf(hi[a], s_box[ww][3 + a]);
+        }
+        ext = fmaxf(ext, hi[a] - lo[a]);
+    }
+    // 2: keys
+    float inv = ext > 0.0f ? (float)(1u << bits) / ext : 0.0f;
+    if (!isfinite(inv)) inv = 0.0f;
+    const uint32_t qmax = (1u << bits) - 1u;
+    int M = 2 * NW;
+    while (M < n) M <<= 1;
+    for (int i = tid; i < M; i += SMALL_NT) {
+        uint64_t key = ~0ull;
+        if (i < n) {
+            uint32_t q[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float t = (pts[3 * i + a] - lo[a]) * inv;
+                const uint32_t u = (t >= 0.0f) ? (uint32_t)fminf(t, 4294967040.0f) : 0u;
+                q[a] = u < qmax ? u : qmax;
+            }
+            key = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+            key = key << SMALL_IDX_BITS | (uint64_t)i;
+        }
+        s_key[i] = key;
+    }
+    __syncthreads();
+    // 3: bitonic sort (pairs at a distance of up to PW lie within one wave's
+    // range of PW pairs: those steps need no workgroup barrier)
+    const int PW = (M >> 1) / NW;
+    for (int k = 2; k <= M; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const bool wide = j > PW;
+            if (wide) __syncthreads();
+            const int i0 = wide ? tid : w * PW + lane;
+            const int i1 = wide ? (M >> 1) : (w + 1) * PW;
+            const int di = wide ? SMALL_NT : 64;
+            for (int i = i0; i < i1; i += di) {
+                const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1));
+                const int b = a + j;
+                const uint64_t x = s_key[a], y = s_key[b];
+                const bool up = (a & k) == 0;
+                if ((x > y) == up) {
+                    s_key[a] = y;
+                    s_key[b] = x;
+                }
+            }
+            if (wide) __syncthreads();
+            else wave_lds_sync();
+        }
+    }
+    __syncthreads();
+    // 4: sorted points; 5: gap levels (s_mx0[W + g] of gap g)
+    const int W = nmax0, span = n + 1 + 2 * W;
+    for (int i = tid; i < n; i += SMALL_NT) {
+        const int j = (int)(s_key[i] & ((1u << SMALL_IDX_BITS) - 1u));
+        out[i] = make_float4(pts[3 * j], pts[3 * j + 1], pts[3 * j + 2], __int_as_float(j));
+    }
+    for (int t = tid; t < span; t += SMALL_NT) {
+        const int g = t - W;
+        int lv = kSentinelLevel;
+        if (g > 0 && g < n) {
+            const uint64_t x = (s_key[g - 1] ^ s_key[g]) >> SMALL_IDX_BITS;
+            lv = x ? 32 + (int)bitlen64(x) : (int)bitlen64((uint64_t)(g - 1) ^ (uint64_t)g);
+        }
+        s_mx0[t] = (uint8_t)lv;
+    }
+    __syncthreads();
+    // 6: range maxima of 2^k levels, split flags, splits in order
+    uint8_t *const s_up = reinterpret_cast<uint8_t *>(s_key);
+    auto mx = [&](int k) { return k == 0 ? s_mx0 : s_up + (k - 1) * SPAN; };
+    for (int k = 1; k < LF_LOG; ++k) {
+        const int h = 1 << (k - 1);
+        const uint8_t *src = mx(k - 1);
+        uint8_t *dst = mx(k);
+        for (int t = tid; t + 2 * h <= span; t += SMALL_NT) dst[t] = max(src[t], src[t + h]);
+        __syncthreads();
+    }
+    const int per = (n + SMALL_NT) / SMALL_NT;  // gaps 0 .. n, `per` in a row per thread
+    unsigned fl = 0;
+    for (int u = 0; u < per; ++u) {
+        const int g = tid * per + u;
+        if (g > n) break;
+        const int c = g + W;
+        fl |= leaf_split(mx, c, W, nmax0) ? 1u << u : 0u;
+    }
+    const int cnt = __popc(fl);
+    const int inc = wave_incl_scan(cnt);
+    if (lane == 63) s_w[w] = inc;
+    __syncthreads();
+    int pos = inc - cnt;
+    for (int ww = 0; ww < w; ++ww) pos += s_w[ww];
+    int m0 = 0;
+    for (int ww = 0; ww < NW; ++ww) m0 += s_w[ww];
+    for (int u = 0; u < per; ++u)
+        if ((fl >> u) & 1u) {
+            spl[pos] = tid * per + u;
+            s_spl[pos++] = tid * per + u;
+        }
+    __syncthreads();
+    // 8: leaf boxes, one wave per leaf
+    for (int l = w; l < m0 - 1; l += NW) leaf_box(out, s_spl[l], s_spl[l + 1], nodes + l);
+    if (tid == 0) {
+        hdr[0] = m0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            hdr[1 + a] = f2o(lo[a]);
+            hdr[4 + a] = f2o(hi[a]);
+        }
+        hdr[7] = s_bad;
+    }
+}
+
 // set of each node (from the key of its first point) and, for leaves, the
 // first input index of that set
 __global__ void k_node_sets(const Node *__restrict__ nodes, int64_t L,
@@ -664,22 +857,35 @@ __global__ void k_node_sets(const Node *__restrict__ nodes, int64_t L,
 
 // ---------------------------------------------------------------------------
 
-// The onesweep passes over the low 8 * npass key bits, with the exclusive
-// digit offsets in doff; (kin, vin) -> sorted pairs, swapping with
-// (kout, vout) after every pass (the result is where the last pass wrote).
-static jz_status onesweep_passes(const AllocCtx *ac, uint64_t *&kin, uint32_t *&vin,
-                                 uint64_t *&kout, uint32_t *&vout, int64_t n, int npass,
-                                 const uint32_t *doff, hipStream_t s) {
-    const int64_t ntiles = (n + RS_TILE - 1) / RS_TILE;
-    DBuf d_status;
-    const size_t per_pass = (size_t)ntiles * 256;
-    JZ_TRY(d_status.get(ac, (per_pass * npass) * sizeof(uint64_t) + 64 * sizeof(int), s));
-    JZ_TRY(zero_words(d_status.as<unsigned long long>(), d_status.bytes / 8, s));
-    int *ctrs = reinterpret_cast<int *>(d_status.as<uint64_t>() + per_pass * npass);
-    for (int p = 0; p < npass; ++p) {
-        k_onesweep<<<(unsigned)ntiles, RS_THREADS, 0, s>>>(
-            kin, vin, kout, vout, n, 8 * p, doff + 256 * p, d_status.as<uint64_t>() + per_pass * p,
-            ctrs + p);
+// Scratch of a radix sort of n keys in npass passes, to be zero before it: the
+// digit counts of all passes, the tiles' status words and the tile counters.
+struct SortScratch {
+    DBuf buf;
+    int64_t ntiles = 0;
+    int npass = 0;
+    static constexpr size_t HIST_WORDS = kMaxPass * 256 / 2, CTR_WORDS = kMaxPass;
+    jz_status get(const AllocCtx *ac, int64_t n, int np, hipStream_t s) {
+        ntiles = (n + RS_TILE - 1) / RS_TILE;
+        npass = np;
+        return buf.get(ac, words() * sizeof(uint64_t), s);
+    }
+    size_t words() const { return HIST_WORDS + CTR_WORDS + (size_t)ntiles * 256 * npass; }
+    uint32_t *hist() const { return buf.as<uint32_t>(); }
+    int *ctr(int p) const { return reinterpret_cast<int *>(buf.as<uint64_t>() + HIST_WORDS) + 2 * p; }
+    uint64_t *status(int p) const {
+        return buf.as<uint64_t>() + HIST_WORDS + CTR_WORDS + (size_t)ntiles * 256 * p;
+    }
+};
+
+// The onesweep passes over the low 8 * npass key bits, with the digit counts in
+// sc; (kin, vin) -> sorted pairs, swapping with (kout, vout) after every pass
+// (the result is where the last pass wrote).
+static jz_status onesweep_passes(const SortScratch &sc, uint64_t *&kin, uint32_t *&vin,
+                                 uint64_t *&kout, uint32_t *&vout, int64_t n, hipStream_t s) {
+    for (int p = 0; p < sc.npass; ++p) {
+        k_onesweep<<<(unsigned)sc.ntiles, RS_THREADS, 0, s>>>(kin, vin, kout, vout, n, 8 * p,
+                                                              sc.hist() + 256 * p, sc.status(p),
+                                                              sc.ctr(p));
         std::swap(kin, kout);
         std::swap(vin, vout);
     }
@@ -690,17 +896,14 @@ static jz_status onesweep_passes(const AllocCtx *ac, uint64_t *&kin, uint32_t *&
 jz_status radix_sort_pairs(const AllocCtx *ac, DBuf &k0, DBuf &v0, DBuf &k1, DBuf &v1, int64_t n,
                            int bits, hipStream_t s) {
     if (n <= 1 || bits <= 0) return JZ_OK;
-    const int npass = std::min(kMaxPass, (bits + 7) / 8);
-    DBuf d_hist, d_doff;
-    JZ_TRY(d_hist.get(ac, kMaxPass * 256 * sizeof(uint32_t), s));
-    JZ_TRY(d_doff.get(ac, kMaxPass * 256 * sizeof(uint32_t), s));
-    JZ_TRY(zero_words(d_hist.as<unsigned long long>(), d_hist.bytes / 8, s));
+    SortScratch sc;
+    JZ_TRY(sc.get(ac, n, std::min(kMaxPass, (bits + 7) / 8), s));
+    JZ_TRY(zero_words(sc.buf.as<unsigned long long>(), sc.words(), s));
     k_digit_hist<<<std::min<unsigned>(blocks_for(n, 256 * 8), 2048), 256, 0, s>>>(
-        k0.as<uint64_t>(), n, npass, d_hist.as<uint32_t>());
-    k_hist_scan<<<npass, 256, 0, s>>>(d_hist.as<uint32_t>(), d_doff.as<uint32_t>());
+        k0.as<uint64_t>(), n, sc.npass, sc.hist());
     uint64_t *kin = k0.as<uint64_t>(), *kout = k1.as<uint64_t>();
     uint32_t *vin = v0.as<uint32_t>(), *vout = v1.as<uint32_t>();
-    JZ_TRY(onesweep_passes(ac, kin, vin, kout, vout, n, npass, d_doff.as<uint32_t>(), s));
+    JZ_TRY(onesweep_passes(sc, kin, vin, kout, vout, n, s));
     if (kin != k0.as<uint64_t>()) {
         std::swap(k0.p, k1.p);
         std::swap(v0.p, v1.p);
@@ -779,119 +982,10 @@ static int plan_planes(int64_t n, const jz_build_opts &o) {
     return P;
 }
 
-jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
-    const int64_t n = t->n;
-    const AllocCtx *ac = &t->ac;
-    const jz_build_opts &o = t->opts;
-    t->P = 0;
-    if (n == 0) return JZ_OK;
-
-    const int has_sets = t->nsets > 1;
-    // automatic key bits: 5 more per dimension than an even split of n
-    // points needs (cells 32 times finer than the mean spacing), raised to
-    // as many as the radix passes those need can hold (a pass sorts 8 key
-    // bits; set bits come first), at most 21
-    int bits = o.key_bits;
-    if (bits == 0) {
-        int lg = 0;
-        while (lg < 62 && ((int64_t)1 << lg) < n) ++lg;
-        const int b0 = std::max(10, (lg + 2) / 3 + 5);
-        const int np = (3 * b0 + t->set_bits + 7) / 8;
-        bits = std::min(21, std::max(b0, (8 * np - t->set_bits) / 3));
-    }
-    const int max_bits = (63 - t->set_bits) / 3;
-    if (bits > max_bits) bits = max_bits;
-    const int bits3 = 3 * bits;
-    const int total_bits = bits3 + t->set_bits;
-    const int npass = (total_bits + 7) / 8;
-
-    // 1-2: bbox, keys, histograms
-    DBuf d_bbox, d_hist, d_doff, k0, k1, v0, v1;
-    JZ_TRY(d_bbox.get(ac, 8 * sizeof(int), s));
-    JZ_TRY(d_hist.get(ac, kMaxPass * 256 * sizeof(uint32_t), s));
-    JZ_TRY(d_doff.get(ac, kMaxPass * 256 * sizeof(uint32_t), s));
-    JZ_TRY(k0.get(ac, n * sizeof(uint64_t), s));
-    JZ_TRY(k1.get(ac, n * sizeof(uint64_t), s));
-    JZ_TRY(v0.get(ac, n * sizeof(uint32_t), s));
-    JZ_TRY(v1.get(ac, n * sizeof(uint32_t), s));
-    {
-        const int init[8] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN, 0, 0};
-        JZ_HIP(hipMemcpyAsync(d_bbox.p, init, sizeof(init), hipMemcpyHostToDevice, s));
-    }
-    JZ_TRY(zero_words(d_hist.as<unsigned long long>(), d_hist.bytes / 8, s));
-    const unsigned gb = std::min<unsigned>(blocks_for(n, 256), 1024);
-    k_bbox<<<gb, 256, 0, s>>>(points, n, d_bbox.as<int>());
-    k_morton<<<std::min<unsigned>(blocks_for(n, 256 * 8), 2048), 256, 0, s>>>(
-        points, n, d_bbox.as<int>(), bits, t->d_set_off.as<int64_t>(), t->nsets, npass,
-        k0.as<uint64_t>(), v0.as<uint32_t>(), d_hist.as<uint32_t>());
-    k_hist_scan<<<npass, 256, 0, s>>>(d_hist.as<uint32_t>(), d_doff.as<uint32_t>());
-    JZ_HIP(hipGetLastError());
-
-    // 3: radix sort
-    {
-        uint64_t *kin = k0.as<uint64_t>(), *kout = k1.as<uint64_t>();
-        uint32_t *vin = v0.as<uint32_t>(), *vout = v1.as<uint32_t>();
-        JZ_TRY(onesweep_passes(ac, kin, vin, kout, vout, n, npass, d_doff.as<uint32_t>(), s));
-        // sorted data is in (kin, vin)
-        if (kin != k0.as<uint64_t>()) {
-            std::swap(k0.p, k1.p);
-            std::swap(v0.p, v1.p);
-        }
-    }
-    const uint64_t *keys = k0.as<uint64_t>();
-    const uint32_t *order = v0.as<uint32_t>();
-
-    // 4: sorted points
-    JZ_TRY(t->pts4.get(ac, n * sizeof(float4), s));
-    k_gather<<<blocks_for(n, 256), 256, 0, s>>>(points, order, n, t->pts4.as<float4>());
-
-    // 5: leaf plane
-    const int64_t ngaps = n + 1;
-    const unsigned nb = blocks_for(ngaps, LF_TILE);
-    DBuf d_flags, d_bcnt, d_boff, d_cnt;
-    JZ_TRY(d_flags.get(ac, ngaps, s));
-    JZ_TRY(d_bcnt.get(ac, (size_t)nb * sizeof(int), s));
-    JZ_TRY(d_boff.get(ac, (size_t)nb * sizeof(int), s));
-    JZ_TRY(d_cnt.get(ac, (JZ_MAX_PLANES + 2) * sizeof(int), s));
-    int *cnts = d_cnt.as<int>();
-    JZ_TRY(t->spl[0].get(ac, ngaps * sizeof(int), s));
-    k_leaf_flags<<<nb, 256, 0, s>>>(keys, n, bits3, has_sets, o.leaf_max, d_flags.as<uint8_t>(),
-                                    d_bcnt.as<int>());
-    k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nb, d_boff.as<int>(), cnts + 0);
-    k_compact<<<nb, 256, 0, s>>>(d_flags.as<uint8_t>(), ngaps, nullptr, d_boff.as<int>(),
-                                 t->spl[0].as<int>(), nullptr, nullptr);
-    JZ_HIP(hipGetLastError());
-    // regularization: the largest level each plane's nodes may have
-    const bool reg = o.reg_fmax > 0.0f;
-    DBuf d_hist2;
-    int lvl_max = 1000;
-    auto plane_level_max = [&](const int *lsi, const int *cnt_dev) -> jz_status {
-        JZ_TRY(zero_words(d_hist2.as<unsigned long long>(), 256, s));
-        k_level_hist<<<blocks_for(ngaps, 256), 256, 0, s>>>(keys, t->spl[0].as<int>(), lsi,
-                                                            cnt_dev, bits3, has_sets,
-                                                            d_hist2.as<unsigned long long>());
-        unsigned long long h[256];
-        JZ_HIP(hipMemcpyAsync(h, d_hist2.p, sizeof(h), hipMemcpyDeviceToHost, s));
-        JZ_HIP(hipStreamSynchronize(s));
-        lvl_max = std::max(lvl_max == 1000 ? 0 : lvl_max, reg_level_max(h, o.reg_fmax));
-        return JZ_OK;
-    };
-    if (reg) {
-        JZ_TRY(d_hist2.get(ac, 256 * sizeof(unsigned long long), s));
-        JZ_TRY(plane_level_max(nullptr, cnts + 0));
-        k_reg_leaf_flags<<<nb, 256, 0, s>>>(keys, n, bits3, has_sets, lvl_max,
-                                            d_flags.as<uint8_t>(), d_bcnt.as<int>());
-        k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nb, d_boff.as<int>(), cnts + 0);
-        k_compact<<<nb, 256, 0, s>>>(d_flags.as<uint8_t>(), ngaps, nullptr, d_boff.as<int>(),
-                                     t->spl[0].as<int>(), nullptr, nullptr);
-        JZ_HIP(hipGetLastError());
-    }
-    int host_hdr[8];
-    JZ_HIP(hipMemcpyAsync(host_hdr, cnts, sizeof(int), hipMemcpyDeviceToHost, s));
-    JZ_HIP(hipMemcpyAsync(host_hdr + 1, d_bbox.as<int>(), 7 * sizeof(int), hipMemcpyDeviceToHost,
-                          s));
-    JZ_HIP(hipStreamSynchronize(s));
-    if (host_hdr[7]) return jz_fail(JZ_E_NONFINITE, "input contains NaN or infinite coordinates");
+// The input's bounding box (ordered ints) and non-finite flag, as k_bbox leaves
+// them, against what a tree takes.
+static jz_status check_box(const int *bbox, const jz_build_opts &o) {
+    if (bbox[6]) return jz_fail(JZ_E_NONFINITE, "input contains NaN or infinite coordinates");
     if (o.period > 0.0f) {
         // the periodic cube is [0, period)^3
         auto of = [](int v) {
@@ -901,71 +995,43 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
             return f;
         };
         for (int a = 0; a < 3; ++a)
-            if (!(of(host_hdr[1 + a]) >= 0.0f) || !(of(host_hdr[4 + a]) < o.period))
+            if (!(of(bbox[a]) >= 0.0f) || !(of(bbox[3 + a]) < o.period))
                 return jz_fail(JZ_E_INVALID, "with period %g every coordinate must lie in "
                                "[0, %g)", (double)o.period, (double)o.period);
     }
-    const int64_t m0 = host_hdr[0];  // L0 + 1
-    t->L[0] = m0 - 1;
+    return JZ_OK;
+}
 
-    // 6-7: node sizes at leaf splits, coarser planes
-    const int P = plan_planes(n, o);
-    DBuf d_nsz, d_slv, lsiA, lsiB;
-    JZ_TRY(d_nsz.get(ac, m0 * sizeof(int), s));
-    JZ_TRY(d_slv.get(ac, m0, s));
-    k_split_sizes<<<blocks_for(m0, 256), 256, 0, s>>>(keys, n, bits3, has_sets, t->spl[0].as<int>(),
-                                                     cnts + 0, o.leaf_max, d_nsz.as<int>(),
-                                                     d_slv.as<uint8_t>());
-    if (P > 1) {
-        JZ_TRY(lsiA.get(ac, m0 * sizeof(int), s));
-        JZ_TRY(lsiB.get(ac, m0 * sizeof(int), s));
-        k_iota<<<blocks_for(m0, 256), 256, 0, s>>>(lsiA.as<int>(), cnts + 0);
-        const unsigned nbp = blocks_for(m0, LF_TILE);
-        int64_t nmax = o.leaf_max;
-        for (int p = 1; p < P; ++p) {
-            nmax *= o.coarsen;
-            JZ_TRY(t->spl[p].get(ac, m0 * sizeof(int), s));
-            // with regularization a plane is selected twice: by counts, then
-            // also splitting the levels above its nodes' lvl_max
-            for (int pass = 0; pass < (reg ? 2 : 1); ++pass) {
-                k_plane_flags<<<nbp, 256, 0, s>>>(lsiA.as<int>(), cnts + p - 1, d_nsz.as<int>(),
-                                                  nmax, d_slv.as<uint8_t>(),
-                                                  pass ? lvl_max : 1000, d_flags.as<uint8_t>(),
-                                                  d_bcnt.as<int>());
-                k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nbp, d_boff.as<int>(),
-                                                 cnts + p);
-                k_compact<<<nbp, 256, 0, s>>>(d_flags.as<uint8_t>(), m0, cnts + p - 1,
-                                              d_boff.as<int>(), t->spl[p].as<int>(),
-                                              lsiA.as<int>(), lsiB.as<int>());
-                if (reg && pass == 0) JZ_TRY(plane_level_max(lsiB.as<int>(), cnts + p));
-            }
-            std::swap(lsiA.p, lsiB.p);
-        }
-        JZ_HIP(hipGetLastError());
-        int hc[JZ_MAX_PLANES];
-        JZ_HIP(hipMemcpyAsync(hc, cnts, P * sizeof(int), hipMemcpyDeviceToHost, s));
-        JZ_HIP(hipStreamSynchronize(s));
-        for (int p = 0; p < P; ++p) t->L[p] = hc[p] - 1;
-    }
-    t->P = P;
+static void set_stats(jz_tree *t) {
+    t->st.n = t->n;
+    t->st.planes = t->P;
+    for (int p = 0; p < JZ_MAX_PLANES; ++p) t->st.nodes[p] = p < t->P ? t->L[p] : 0;
+    t->st.super_nodes = t->S;
+}
 
-    // 8: geometry
-    for (int p = 0; p < P; ++p) {
-        JZ_TRY(t->nodes[p].get(ac, t->L[p] * sizeof(Node), s));
-        if (p == 0)
-            k_leaf_geom<<<blocks_for(t->L[0] * 64, 256), 256, 0, s>>>(
-                t->pts4.as<float4>(), t->spl[0].as<int>(), t->L[0], t->nodes[0].as<Node>());
-        else
-            k_node_geom<<<blocks_for(t->L[p] * 64, 256), 256, 0, s>>>(
-                t->nodes[p - 1].as<Node>(), t->spl[p].as<int>(), t->L[p], t->nodes[p].as<Node>());
-    }
-    JZ_HIP(hipGetLastError());
-
-    // super nodes over the top plane, per set
-    const int T = P - 1;
+// Super nodes over the top plane and their dense lists: made on the device for
+// a single set (no transfer), on the host for a forest, whose rows end at the
+// set boundaries. Waits for the stream where host arrays are read.
+static jz_status top_lists(jz_tree *t, const uint64_t *keys, int bits3, hipStream_t s) {
+    const AllocCtx *ac = &t->ac;
+    const jz_build_opts &o = t->opts;
+    const int P = t->P, T = P - 1;
     const int64_t LT = t->L[T];
+    if (t->nsets == 1) {
+        const int64_t S = t->S = (LT + o.ngr - 1) / o.ngr;
+        JZ_TRY(t->super_spl.get(ac, (S + 1) * sizeof(int), s));
+        JZ_TRY(t->knn_top_seg.get(ac, S * sizeof(int2), s));
+        JZ_TRY(t->knn_top_list.get(ac, S * S * sizeof(int2), s));
+        JZ_TRY(t->fof_top_seg.get(ac, S * sizeof(int2), s));
+        JZ_TRY(t->fof_top_list.get(ac, S * (S + 1) / 2 * sizeof(int2), s));
+        k_top_lists<<<std::min<unsigned>(blocks_for(S * S + 1, 256), 4096), 256, 0, s>>>(
+            (int)S, (int)LT, o.ngr, t->super_spl.as<int>(), t->knn_top_seg.as<int2>(),
+            t->knn_top_list.as<int2>(), t->fof_top_seg.as<int2>(), t->fof_top_list.as<int2>());
+        JZ_HIP(hipGetLastError());
+        return JZ_OK;
+    }
     std::vector<int> top_set(LT, 0);
-    if (has_sets) {
+    {
         JZ_TRY(t->leaf_base.get(ac, t->L[0] * sizeof(int), s));
         for (int p = 0; p < P; ++p) {
             JZ_TRY(t->node_set[p].get(ac, t->L[p] * sizeof(int), s));
@@ -1018,16 +1084,210 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
                           hipMemcpyHostToDevice, s));
     JZ_HIP(hipMemcpyAsync(t->fof_top_list.p, flist.data(), flist.size() * sizeof(int2),
                           hipMemcpyHostToDevice, s));
+    JZ_HIP(hipStreamSynchronize(s));  // (the host arrays end here)
+    return JZ_OK;
+}
+
+// the one-launch build of a small single set
+static jz_status build_small(jz_tree *t, const float *points, int bits, hipStream_t s) {
+    const AllocCtx *ac = &t->ac;
+    const int64_t n = t->n;
+    DBuf d_hdr;
+    JZ_TRY(d_hdr.get(ac, 8 * sizeof(int), s));
+    JZ_TRY(t->pts4.get(ac, n * sizeof(float4), s));
+    JZ_TRY(t->spl[0].get(ac, (n + 1) * sizeof(int), s));
+    JZ_TRY(t->nodes[0].get(ac, n * sizeof(Node), s));  // (a leaf holds a point at least)
+    k_build_small<<<1, SMALL_NT, 0, s>>>(points, (int)n, bits, t->opts.leaf_max,
+                                         t->pts4.as<float4>(), t->spl[0].as<int>(),
+                                         t->nodes[0].as<Node>(), d_hdr.as<int>());
+    JZ_HIP(hipGetLastError());
+    int h[8];
+    JZ_HIP(hipMemcpyAsync(h, d_hdr.p, sizeof(h), hipMemcpyDeviceToHost, s));
+    JZ_HIP(hipStreamSynchronize(s));
+    JZ_TRY(check_box(h + 1, t->opts));
+    t->L[0] = h[0] - 1;
+    t->P = 1;
+    JZ_TRY(top_lists(t, nullptr, 0, s));
+    JZ_HIP(hipStreamSynchronize(s));
+    set_stats(t);
+    return JZ_OK;
+}
+
+jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
+    const int64_t n = t->n;
+    const AllocCtx *ac = &t->ac;
+    const jz_build_opts &o = t->opts;
+    t->P = 0;
+    if (n == 0) return JZ_OK;
+
+    const int has_sets = t->nsets > 1;
+    // automatic key bits: 5 more per dimension than an even split of n
+    // points needs (cells 32 times finer than the mean spacing), raised to
+    // as many as the radix passes those need can hold (a pass sorts 8 key
+    // bits; set bits come first), at most 21
+    int bits = o.key_bits;
+    if (bits == 0) {
+        int lg = 0;
+        while (lg < 62 && ((int64_t)1 << lg) < n) ++lg;
+        const int b0 = std::max(10, (lg + 2) / 3 + 5);
+        const int np = (3 * b0 + t->set_bits + 7) / 8;
+        bits = std::min(21, std::max(b0, (8 * np - t->set_bits) / 3));
+    }
+    const int max_bits = (63 - t->set_bits) / 3;
+    if (bits > max_bits) bits = max_bits;
+    const int bits3 = 3 * bits;
+    const int total_bits = bits3 + t->set_bits;
+    const int npass = (total_bits + 7) / 8;
+
+    const int P = plan_planes(n, o);
+    const bool reg = o.reg_fmax > 0.0f;
+    if (n <= SMALL_N && !has_sets && P == 1 && !reg && !o.keep_keys &&
+        bits3 + SMALL_IDX_BITS <= 64)
+        return build_small(t, points, bits, s);
+
+    // 1-2: bbox, keys, histograms. d_meta: bounding box and non-finite flag
+    // (8 words), then the number of splits of every plane
+    DBuf d_meta, k0, k1, v0, v1;
+    SortScratch sc;
+    JZ_TRY(d_meta.get(ac, (8 + JZ_MAX_PLANES + 2) * sizeof(int), s));
+    int *const bbox = d_meta.as<int>(), *const cnts = bbox + 8;
+    JZ_TRY(sc.get(ac, n, npass, s));
+    JZ_TRY(k0.get(ac, n * sizeof(uint64_t), s));
+    JZ_TRY(k1.get(ac, n * sizeof(uint64_t), s));
+    JZ_TRY(v0.get(ac, n * sizeof(uint32_t), s));
+    JZ_TRY(v1.get(ac, n * sizeof(uint32_t), s));
+    k_build_init<<<std::min<unsigned>(blocks_for((int64_t)sc.words(), 256), 1024), 256, 0, s>>>(
+        sc.buf.as<unsigned long long>(), sc.words(), bbox);
+    const unsigned gb = std::min<unsigned>(blocks_for(n, 256), 1024);
+    k_bbox<<<gb, 256, 0, s>>>(points, n, bbox);
+    k_morton<<<std::min<unsigned>(blocks_for(n, 256 * 8), 2048), 256, 0, s>>>(
+        points, n, bbox, bits, t->d_set_off.as<int64_t>(), t->nsets, npass, k0.as<uint64_t>(),
+        v0.as<uint32_t>(), sc.hist());
+    JZ_HIP(hipGetLastError());
+
+    // 3: radix sort
+    {
+        uint64_t *kin = k0.as<uint64_t>(), *kout = k1.as<uint64_t>();
+        uint32_t *vin = v0.as<uint32_t>(), *vout = v1.as<uint32_t>();
+        JZ_TRY(onesweep_passes(sc, kin, vin, kout, vout, n, s));
+        // sorted data is in (kin, vin)
+        if (kin != k0.as<uint64_t>()) {
+            std::swap(k0.p, k1.p);
+            std::swap(v0.p, v1.p);
+        }
+    }
+    const uint64_t *keys = k0.as<uint64_t>();
+    const uint32_t *order = v0.as<uint32_t>();
+
+    // 4: sorted points
+    JZ_TRY(t->pts4.get(ac, n * sizeof(float4), s));
+    k_gather<<<blocks_for(n, 256), 256, 0, s>>>(points, order, n, t->pts4.as<float4>());
+
+    // 5: leaf plane
+    const int64_t ngaps = n + 1;
+    const unsigned nb = blocks_for(ngaps, LF_TILE);
+    DBuf d_flags, d_bcnt, d_boff;
+    JZ_TRY(d_flags.get(ac, ngaps, s));
+    JZ_TRY(d_bcnt.get(ac, (size_t)nb * sizeof(int), s));
+    JZ_TRY(d_boff.get(ac, (size_t)nb * sizeof(int), s));
+    JZ_TRY(t->spl[0].get(ac, ngaps * sizeof(int), s));
+    k_leaf_flags<<<nb, 256, 0, s>>>(keys, n, bits3, has_sets, o.leaf_max, d_flags.as<uint8_t>(),
+                                    d_bcnt.as<int>());
+    k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nb, d_boff.as<int>(), cnts + 0);
+    k_compact<<<nb, 256, 0, s>>>(d_flags.as<uint8_t>(), ngaps, nullptr, d_boff.as<int>(),
+                                 t->spl[0].as<int>(), nullptr, nullptr);
+    JZ_HIP(hipGetLastError());
+    // regularization: the largest level each plane's nodes may have
+    DBuf d_hist2;
+    int lvl_max = 1000;
+    auto plane_level_max = [&](const int *lsi, const int *cnt_dev) -> jz_status {
+        JZ_TRY(zero_words(d_hist2.as<unsigned long long>(), 256, s));
+        k_level_hist<<<blocks_for(ngaps, 256), 256, 0, s>>>(keys, t->spl[0].as<int>(), lsi,
+                                                            cnt_dev, bits3, has_sets,
+                                                            d_hist2.as<unsigned long long>());
+        unsigned long long h[256];
+        JZ_HIP(hipMemcpyAsync(h, d_hist2.p, sizeof(h), hipMemcpyDeviceToHost, s));
+        JZ_HIP(hipStreamSynchronize(s));
+        lvl_max = std::max(lvl_max == 1000 ? 0 : lvl_max, reg_level_max(h, o.reg_fmax));
+        return JZ_OK;
+    };
+    if (reg) {
+        JZ_TRY(d_hist2.get(ac, 256 * sizeof(unsigned long long), s));
+        JZ_TRY(plane_level_max(nullptr, cnts + 0));
+        k_reg_leaf_flags<<<nb, 256, 0, s>>>(keys, n, bits3, has_sets, lvl_max,
+                                            d_flags.as<uint8_t>(), d_bcnt.as<int>());
+        k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nb, d_boff.as<int>(), cnts + 0);
+        k_compact<<<nb, 256, 0, s>>>(d_flags.as<uint8_t>(), ngaps, nullptr, d_boff.as<int>(),
+                                     t->spl[0].as<int>(), nullptr, nullptr);
+        JZ_HIP(hipGetLastError());
+    }
+    int hm[9];  // bounding box, non-finite flag, leaf splits
+    JZ_HIP(hipMemcpyAsync(hm, bbox, sizeof(hm), hipMemcpyDeviceToHost, s));
+    JZ_HIP(hipStreamSynchronize(s));
+    JZ_TRY(check_box(hm, o));
+    const int64_t m0 = hm[8];  // L0 + 1
+    t->L[0] = m0 - 1;
+
+    // 6-7: node sizes at leaf splits, coarser planes
+    DBuf d_nsz, d_slv, lsiA, lsiB;
+    JZ_TRY(d_nsz.get(ac, m0 * sizeof(int), s));
+    JZ_TRY(d_slv.get(ac, m0, s));
+    k_split_sizes<<<blocks_for(m0, 256), 256, 0, s>>>(keys, n, bits3, has_sets, t->spl[0].as<int>(),
+                                                     cnts + 0, o.leaf_max, d_nsz.as<int>(),
+                                                     d_slv.as<uint8_t>());
+    if (P > 1) {
+        JZ_TRY(lsiA.get(ac, m0 * sizeof(int), s));
+        JZ_TRY(lsiB.get(ac, m0 * sizeof(int), s));
+        const unsigned nbp = blocks_for(m0, LF_TILE);
+        int64_t nmax = o.leaf_max;
+        for (int p = 1; p < P; ++p) {
+            const int *lsi = p == 1 ? nullptr : lsiA.as<int>();
+            nmax *= o.coarsen;
+            JZ_TRY(t->spl[p].get(ac, m0 * sizeof(int), s));
+            // with regularization a plane is selected twice: by counts, then
+            // also splitting the levels above its nodes' lvl_max
+            for (int pass = 0; pass < (reg ? 2 : 1); ++pass) {
+                k_plane_flags<<<nbp, 256, 0, s>>>(lsi, cnts + p - 1, d_nsz.as<int>(),
+                                                  nmax, d_slv.as<uint8_t>(),
+                                                  pass ? lvl_max : 1000, d_flags.as<uint8_t>(),
+                                                  d_bcnt.as<int>());
+                k_scan_counts<<<1, 1024, 0, s>>>(d_bcnt.as<int>(), (int)nbp, d_boff.as<int>(),
+                                                 cnts + p);
+                k_compact<<<nbp, 256, 0, s>>>(d_flags.as<uint8_t>(), m0, cnts + p - 1,
+                                              d_boff.as<int>(), t->spl[p].as<int>(), lsi,
+                                              lsiB.as<int>());
+                if (reg && pass == 0) JZ_TRY(plane_level_max(lsiB.as<int>(), cnts + p));
+            }
+            std::swap(lsiA.p, lsiB.p);
+        }
+        JZ_HIP(hipGetLastError());
+        int hc[JZ_MAX_PLANES];
+        JZ_HIP(hipMemcpyAsync(hc, cnts, P * sizeof(int), hipMemcpyDeviceToHost, s));
+        JZ_HIP(hipStreamSynchronize(s));
+        for (int p = 0; p < P; ++p) t->L[p] = hc[p] - 1;
+    }
+    t->P = P;
+
+    // 8: geometry
+    for (int p = 0; p < P; ++p) {
+        JZ_TRY(t->nodes[p].get(ac, t->L[p] * sizeof(Node), s));
+        if (p == 0)
+            k_leaf_geom<<<blocks_for(t->L[0] * 64, 256), 256, 0, s>>>(
+                t->pts4.as<float4>(), t->spl[0].as<int>(), t->L[0], t->nodes[0].as<Node>());
+        else
+            k_node_geom<<<blocks_for(t->L[p] * 64, 256), 256, 0, s>>>(
+                t->nodes[p - 1].as<Node>(), t->spl[p].as<int>(), t->L[p], t->nodes[p].as<Node>());
+    }
+    JZ_HIP(hipGetLastError());
+
+    // super nodes over the top plane, per set
+    JZ_TRY(top_lists(t, keys, bits3, s));
     if (o.keep_keys) {
         JZ_TRY(t->keys.get(ac, n * sizeof(uint64_t), s));
         JZ_HIP(hipMemcpyAsync(t->keys.p, keys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
     }
     JZ_HIP(hipStreamSynchronize(s));
 
-    // stats
-    t->st.n = n;
-    t->st.planes = P;
-    for (int p = 0; p < JZ_MAX_PLANES; ++p) t->st.nodes[p] = p < P ? t->L[p] : 0;
-    t->st.super_nodes = t->S;
+    set_stats(t);
     return JZ_OK;
 }

@@ -25,17 +25,18 @@
 
 namespace {
 
-__global__ void k_iota_n(int *__restrict__ a, int64_t n) {
+// The start of a call: every point its own root; the smallest input index of
+// every group starts as its root's own (a root is a member; a point that stays
+// a root of itself needs no update at all); the counters zero.
+__global__ __launch_bounds__(256) void k_fof_init(const float4 *__restrict__ pts, int64_t n,
+                                                  int *__restrict__ uf, int *__restrict__ minidx,
+                                                  unsigned long long *__restrict__ ctr, int nctr) {
     const int64_t i = (int64_t)blk_x() * bdim_x() + tid_x();
-    if (i < n) a[i] = (int)i;
-}
-
-// the smallest input index of every group starts as its root's own (a root is
-// a member; a point that stays a root of itself needs no update at all)
-__global__ __launch_bounds__(256) void k_init_min(const float4 *__restrict__ pts, int64_t n,
-                                                  int *__restrict__ minidx) {
-    const int64_t i = (int64_t)blk_x() * bdim_x() + tid_x();
-    if (i < n) minidx[i] = __float_as_int(pts[i].w);
+    if (i < n) {
+        uf[i] = (int)i;
+        minidx[i] = __float_as_int(pts[i].w);
+    }
+    if (i < nctr) ctr[i] = 0;
 }
 
 __global__ void k_node_b2(const int *__restrict__ node_set, int64_t L,
@@ -64,17 +65,6 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_p2n(const int *__restrict__ pa
         whole[c] = wc;
         if (wp && c != c0) uf[me.start] = first;
     }
-}
-
-// whole leaves: every point points at the leaf's first point
-__global__ __launch_bounds__(64 * WPB) void k_fof_l2p(const Node *__restrict__ leaves, int n_leaves,
-                                                 const int *__restrict__ whole,
-                                                 int *__restrict__ uf) {
-    const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
-    const int A = xcd_block(blk_x(), nblk_x()) * WPB + w;
-    if (A >= n_leaves || !whole[A]) return;
-    const Node a = leaves[A];
-    for (int i = a.start + 1 + lane; i < a.start + a.count; i += 64) uf[i] = a.start;
 }
 
 // Node walk step: one wave per work item, a receiving parent and up to CB of
@@ -350,7 +340,8 @@ __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b
 //
 // The leaf's own points come first: their links are a mask per lane, its
 // components are closed in registers, and one union per point joins them; a
-// leaf whose points are all connected becomes "whole" for the other waves too.
+// leaf whose points are all connected becomes "whole" for the other waves too
+// (and one the node walk found whole only has its points joined here).
 // Then source by source (skipped when A and B are both whole and already one
 // group, or when no lane's point reaches the source's box): the next source's
 // points are loaded while the current one is worked on; a matrix filter gives
@@ -396,7 +387,9 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
 
     tile[lane] = me;
     wave_lds_sync();
+    int lead = 0;  // the lane whose point this lane's is joined with
     if (!wA) {
+        lead = lane;
         // the leaf's own links, exactly (both directions, as masks of lanes)
         uint64_t adj = 0;
         for (int f = 0; f < acount; ++f) {
@@ -409,7 +402,6 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
         // components: from the lowest point not yet in one, the links of all
         // its members are added until nothing changes
         uint64_t todo = __ballot((adj & ~(1ull << lane)) != 0);
-        int lead = lane;
         while (todo) {
             const int s = __ffsll((unsigned long long)todo) - 1;
             uint64_t reach = 1ull << s, prev = 0;
@@ -423,11 +415,12 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
             todo &= ~reach;
             if (reach == (acount == 64 ? ~0ull : (1ull << acount) - 1ull)) wA = true;
         }
-        if (act && lead != lane) uf_union_c(uf, astart + lead, my);
         if (acount == 1) wA = true;
-        // (its points' unions are done)
+        // (other waves that see the flag take the leaf for one group, which it
+        // is once this wave has joined its points)
         if (wA && lane == 0) st_rel(whole + A, 1);
     }
+    if (act && lead != lane) uf_union_c(uf, astart + lead, my);
 
     // the filter's query side: lane l holds component l / 16 (x, y, z, 1) of
     // query 16 g + l % 16 in bq[g], and minus that query's t in tg[g]
@@ -654,10 +647,9 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
     // start with larger lists.
     for (;;) {
         for (int p = 0; p < P; ++p) JZ_TRY(lists[p].ensure(ac, cap[p] * sizeof(int2), s));
-        JZ_HIP(hipMemsetAsync(ctr, 0, d_ctr.bytes, s));
         if (ev.on) JZ_HIP(hipEventRecord(ev[0], s));
-        k_iota_n<<<blocks_for(n, 256), 256, 0, s>>>(d_uf.as<int>(), n);
-        k_init_min<<<blocks_for(n, 256), 256, 0, s>>>(t->pts4.as<float4>(), n, d_min.as<int>());
+        k_fof_init<<<blocks_for(std::max<int64_t>(n, (int64_t)nctr), 256), 256, 0, s>>>(
+            t->pts4.as<float4>(), n, d_uf.as<int>(), d_min.as<int>(), ctr, (int)nctr);
         for (int p = P - 1; p >= 0; --p) {
             const bool top = p == P - 1;
             const int2 *seg_in = top ? t->fof_top_seg.as<int2>() : segs[p + 1].as<int2>();
@@ -680,8 +672,6 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
                 whole[p].as<int>(), d_uf.as<int>(), segs[p].as<int2>(), lists[p].as<int2>(),
                 ctr + (size_t)p * LIST_ARENAS, cap[p] / LIST_ARENAS, ctr + CTR_FLAG, L);
         }
-        k_fof_l2p<<<blocks_for(t->L[0], WPB), 64 * WPB, 0, s>>>(t->nodes[0].as<Node>(), (int)t->L[0],
-                                                         whole[0].as<int>(), d_uf.as<int>());
         JZ_HIP(hipGetLastError());
         if (ev.on) JZ_HIP(hipEventRecord(ev[1], s));
         (per ? k_leaf_fof<true> : k_leaf_fof<false>)<<<blocks_for(t->L[0], WPB), 64 * WPB, 0, s>>>(

@@ -1314,7 +1314,8 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
     JZ_TRY(d_first.get(ac, (size_t)t->L[0] * sizeof(int), s));
     auto presort = [&](int2 *list, const int2 *seg, int64_t n, int min_len,
                        unsigned long long *count) {
-        if (sort_max <= min_len) return;
+        // (a list names a node at most once: none is longer than the plane)
+        if (sort_max <= min_len || n <= min_len) return;
         int *ids_a = d_ids.as<int>(), *ids_b = ids_a + t->L[0];
         const int mid = std::max(min_len, std::min(sort_max, SORT_MID));
         k_find_long<<<(unsigned)((n + 63) / 64), 64, 0, s>>>(seg, (int)n, min_len, mid, sort_max,
@@ -1362,12 +1363,15 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
         }
         presort(lists[0].as<int2>(), segs[0].as<int2>(), t->L[0], LEAF_PRESORT,
                 ctr + c_long + 2 * JZ_MAX_PLANES);
-        k_long_first<<<(unsigned)((t->L[0] + 63) / 64), 64, 0, s>>>(
-            segs[0].as<int2>(), (int)t->L[0], leaf_cap, d_first.as<int>(), ctr + c_first);
-        JZ_HIP(hipGetLastError());
         // waves for every leaf plus the first ones (at most one per leaf_cap
         // + 1 list entries)
-        const int64_t n_waves = t->L[0] + std::min<int64_t>(t->L[0], cap[0] / (leaf_cap + 1) + 1);
+        int64_t n_waves = t->L[0];
+        if (t->L[0] > leaf_cap) {
+            k_long_first<<<(unsigned)((t->L[0] + 63) / 64), 64, 0, s>>>(
+                segs[0].as<int2>(), (int)t->L[0], leaf_cap, d_first.as<int>(), ctr + c_first);
+            n_waves += std::min<int64_t>(t->L[0], cap[0] / (leaf_cap + 1) + 1);
+        }
+        JZ_HIP(hipGetLastError());
         if (ev.on) JZ_HIP(hipEventRecord(ev[1], s));
         // k <= 32: one pass; larger k: passes of 32 neighbours, each after
         // the last key of the one before
