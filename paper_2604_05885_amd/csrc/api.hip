@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -75,7 +76,10 @@ int64_t initial_cap(const jz_tree *t, int op, int k, int level) {
 // ---------------------------------------------------------------------------
 // Caching device pool. Freed blocks keep an event recorded on the stream that
 // last used them; a block is handed to a different stream only after that
-// event has completed, so stream order protects every reuse.
+// event has completed, so stream order protects every reuse. A block freed
+// while its stream has no work left (at the end of every call, which has waited
+// for it) needs none: creating, recording and destroying the events of some 25
+// blocks took 50 us of a call of 240.
 
 namespace {
 
@@ -178,7 +182,11 @@ void dev_free(const AllocCtx &a, void *p, size_t bytes, hipStream_t s) {
     }
     Pool &P = pool(a.device);
     hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
+    const hipError_t idle = hipStreamQuery(s);
+    if (idle != hipSuccess) (void)hipGetLastError();
+    if (idle == hipSuccess) {
+        // nothing to wait for
+    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
         if (hipEventRecord(ev, s) != hipSuccess) {
             (void)hipGetLastError();
             (void)hipStreamSynchronize(s);
@@ -195,6 +203,65 @@ void dev_free(const AllocCtx &a, void *p, size_t bytes, hipStream_t s) {
     const size_t real = it != P.live.end() ? it->second : round_size(bytes);
     if (it != P.live.end()) P.live.erase(it);
     P.free.emplace(real, Block{p, real, s, ev});
+}
+
+// ---------------------------------------------------------------------------
+// pinned host blocks
+
+namespace {
+struct HostCache {
+    std::mutex m;
+    void *block[HOST_BLOCKS];
+    int n = 0;
+};
+HostCache &host_cache() {
+    static HostCache c;
+    return c;
+}
+}  // namespace
+
+HostCopy::~HostCopy() {
+    if (!p) return;
+    if (!pinned) {
+        free(p);
+        return;
+    }
+    HostCache &c = host_cache();
+    {
+        std::lock_guard<std::mutex> lk(c.m);
+        if (c.n < HOST_BLOCKS) {
+            c.block[c.n++] = p;
+            return;
+        }
+    }
+    if (hipHostFree(p) != hipSuccess) (void)hipGetLastError();
+}
+
+jz_status HostCopy::read(const void *dev, size_t bytes, hipStream_t s) {
+    if (!p && bytes <= HOST_BLOCK) {
+        HostCache &c = host_cache();
+        {
+            std::lock_guard<std::mutex> lk(c.m);
+            if (c.n > 0) p = c.block[--c.n];
+        }
+        if (!p && hipHostMalloc(&p, HOST_BLOCK, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        pinned = p != nullptr;
+    } else if (p && !(pinned && bytes <= HOST_BLOCK)) {
+        return jz_fail(JZ_E_DEVICE, "a host copy is read again with another size");
+    }
+    if (!p) p = malloc(bytes);
+    if (!p) return jz_fail(JZ_E_OOM, "host allocation of %zu bytes failed", bytes);
+    hipError_t e = hipMemcpyAsync(p, dev, bytes, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        // the copy may still be under way: the block is not reused
+        p = nullptr;
+        return jz_hip_fail(e, "reading device results", __FILE__, __LINE__);
+    }
+    return JZ_OK;
 }
 
 void pool_forget_stream(int device, hipStream_t s) {
@@ -585,8 +652,14 @@ void jz_release_cached(void) {
         return;
     }
     Pool &P = pool(dev);
-    std::lock_guard<std::mutex> lk(P.m);
-    release_all(P);
+    {
+        std::lock_guard<std::mutex> lk(P.m);
+        release_all(P);
+    }
+    HostCache &c = host_cache();
+    std::lock_guard<std::mutex> lk(c.m);
+    while (c.n > 0)
+        if (hipHostFree(c.block[--c.n]) != hipSuccess) (void)hipGetLastError();
 }
 
 const char *jz_last_error(void) { return g_err.c_str(); }

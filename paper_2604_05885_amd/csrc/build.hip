@@ -1101,9 +1101,9 @@ static jz_status build_small(jz_tree *t, const float *points, int bits, hipStrea
                                          t->pts4.as<float4>(), t->spl[0].as<int>(),
                                          t->nodes[0].as<Node>(), d_hdr.as<int>());
     JZ_HIP(hipGetLastError());
-    int h[8];
-    JZ_HIP(hipMemcpyAsync(h, d_hdr.p, sizeof(h), hipMemcpyDeviceToHost, s));
-    JZ_HIP(hipStreamSynchronize(s));
+    HostCopy hdr;
+    JZ_TRY(hdr.read(d_hdr.p, 8 * sizeof(int), s));
+    const int *h = hdr.as<int>();
     JZ_TRY(check_box(h + 1, t->opts));
     t->L[0] = h[0] - 1;
     t->P = 1;
@@ -1221,9 +1221,9 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
                                      t->spl[0].as<int>(), nullptr, nullptr);
         JZ_HIP(hipGetLastError());
     }
-    int hm[9];  // bounding box, non-finite flag, leaf splits
-    JZ_HIP(hipMemcpyAsync(hm, bbox, sizeof(hm), hipMemcpyDeviceToHost, s));
-    JZ_HIP(hipStreamSynchronize(s));
+    HostCopy meta;  // bounding box, non-finite flag, leaf splits
+    JZ_TRY(meta.read(bbox, 9 * sizeof(int), s));
+    const int *hm = meta.as<int>();
     JZ_TRY(check_box(hm, o));
     const int64_t m0 = hm[8];  // L0 + 1
     t->L[0] = m0 - 1;
@@ -1261,10 +1261,8 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
             std::swap(lsiA.p, lsiB.p);
         }
         JZ_HIP(hipGetLastError());
-        int hc[JZ_MAX_PLANES];
-        JZ_HIP(hipMemcpyAsync(hc, cnts, P * sizeof(int), hipMemcpyDeviceToHost, s));
-        JZ_HIP(hipStreamSynchronize(s));
-        for (int p = 0; p < P; ++p) t->L[p] = hc[p] - 1;
+        JZ_TRY(meta.read(cnts, P * sizeof(int), s));
+        for (int p = 0; p < P; ++p) t->L[p] = hm[p] - 1;
     }
     t->P = P;
 

@@ -345,9 +345,9 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     k_cat_compact<<<nb, 256, 0, s>>>(k0.as<uint64_t>(), n, min_members, d_boff.as<int>(), groups,
                                      max_groups, d_gidx.as<int>());
     JZ_HIP(hipGetLastError());
-    long long G = 0;
-    JZ_HIP(hipMemcpyAsync(&G, d_total.p, sizeof(G), hipMemcpyDeviceToHost, s));
-    JZ_HIP(hipStreamSynchronize(s));
+    HostCopy total;
+    JZ_TRY(total.read(d_total.p, sizeof(long long), s));
+    const long long G = *total.as<long long>();
     *ngroups = G;
     if (G > max_groups)
         return jz_fail(JZ_E_CAPACITY, "%lld groups have at least %d members; groups holds %lld",

@@ -642,6 +642,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
         }
     }
     EventSet ev(jz_profiling());
+    HostCopy host;  // the counters
 
     // Groups only ever merge, so an overflowing run is simply rerun from the
     // start with larger lists.
@@ -686,14 +687,12 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
                                                      t->nsets, label);
         JZ_HIP(hipGetLastError());
         if (ev.on) JZ_HIP(hipEventRecord(ev[3], s));
-        std::vector<unsigned long long> hc(nctr);
-        JZ_HIP(hipMemcpyAsync(hc.data(), ctr, nctr * sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, s));
-        JZ_HIP(hipStreamSynchronize(s));
+        JZ_TRY(host.read(ctr, nctr * sizeof(unsigned long long), s));
+        const unsigned long long *hc = host.as<unsigned long long>();
         bool overflow = false;
         double sum[JZ_MAX_PLANES], need[JZ_MAX_PLANES];
         for (int p = 0; p < P; ++p) {
-            arena_need(hc.data(), p, sum[p], need[p]);
+            arena_need(hc, p, sum[p], need[p]);
             if (need[p] <= (double)(cap[p] / LIST_ARENAS * LIST_ARENAS)) continue;
             overflow = true;
             if (need[p] > (double)INT32_MAX)
@@ -713,7 +712,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             cap_learn(CAP_FOF, 0, p, need[p] / (double)std::max<int64_t>(1, t->L[p]));
         }
         st.leaf_pairs = st.list_entries[0];
-        st.evaluations = stat_sum(hc.data(), 0);
+        st.evaluations = stat_sum(hc, 0);
         if (ev.on) {
             float ms = 0;
             JZ_HIP(hipEventElapsedTime(&ms, ev[1], ev[2]));

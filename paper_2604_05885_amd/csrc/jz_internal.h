@@ -90,6 +90,29 @@ struct DBuf {
     }
 };
 
+// A call's host copy of device results: a block of pinned memory from a small
+// cache (blocks of HOST_BLOCK bytes, at most HOST_BLOCKS kept, given back by
+// jz_release_cached), pageable memory where it is larger or none is to be had.
+// A copy to pageable memory went through the runtime's staging: 20 us before
+// and 20 after it, and the wait for the stream on top.
+constexpr size_t HOST_BLOCK = 64 << 10;
+constexpr int HOST_BLOCKS = 64;
+struct HostCopy {
+    void *p = nullptr;
+    bool pinned = false;
+
+    HostCopy() = default;
+    HostCopy(const HostCopy &) = delete;
+    HostCopy &operator=(const HostCopy &) = delete;
+    ~HostCopy();
+    // copy `bytes` from dev and wait for stream s
+    jz_status read(const void *dev, size_t bytes, hipStream_t s);
+    template <class T>
+    const T *as() const {
+        return static_cast<const T *>(p);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // the tree
 

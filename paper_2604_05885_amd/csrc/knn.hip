@@ -1327,6 +1327,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                                                                               count + 1);
     };
     EventSet ev(jz_profiling());
+    HostCopy host;  // the counters
 
     // Level p turns the list of plane p+1 (or of the super nodes) into the
     // list of plane p. On overflow, levels from the highest overflowing one
@@ -1389,13 +1390,11 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
             JZ_HIP(hipGetLastError());
         }
         if (ev.on) JZ_HIP(hipEventRecord(ev[2], s));
-        std::vector<unsigned long long> hc(nctr);
-        JZ_HIP(hipMemcpyAsync(hc.data(), ctr, nctr * sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, s));
-        JZ_HIP(hipStreamSynchronize(s));
+        JZ_TRY(host.read(ctr, nctr * sizeof(unsigned long long), s));
+        const unsigned long long *hc = host.as<unsigned long long>();
         int redo = -1;
         double sum[JZ_MAX_PLANES], need[JZ_MAX_PLANES];
-        for (int p = P - 1; p >= 0; --p) arena_need(hc.data(), p, sum[p], need[p]);
+        for (int p = P - 1; p >= 0; --p) arena_need(hc, p, sum[p], need[p]);
         for (int p = start; p >= 0; --p) {
             if (need[p] <= (double)(cap[p] / LIST_ARENAS * LIST_ARENAS)) continue;
             if (need[p] > (double)INT32_MAX)
@@ -1423,12 +1422,12 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
             cap_learn(CAP_KNN, k, p, need[p] / (double)std::max<int64_t>(1, t->L[p]));
         }
         t->st.leaf_pairs = t->st.list_entries[0];
-        t->st.evaluations = stat_sum(hc.data(), 0);
-        t->st.leaf_pairs_visited = (int64_t)stat_sum(hc.data(), 1);
-        t->st.insert_rounds = (int64_t)stat_sum(hc.data(), 2);
-        t->st.tile_steps = (int64_t)stat_sum(hc.data(), 3);
-        t->st.lists_sorted_long = (int64_t)stat_sum(hc.data(), 4);
-        t->st.lists_unordered = (int64_t)stat_sum(hc.data(), 5);
+        t->st.evaluations = stat_sum(hc, 0);
+        t->st.leaf_pairs_visited = (int64_t)stat_sum(hc, 1);
+        t->st.insert_rounds = (int64_t)stat_sum(hc, 2);
+        t->st.tile_steps = (int64_t)stat_sum(hc, 3);
+        t->st.lists_sorted_long = (int64_t)stat_sum(hc, 4);
+        t->st.lists_unordered = (int64_t)stat_sum(hc, 5);
         for (int p = 0; p <= JZ_MAX_PLANES; ++p)
             for (int j = 0; j < 2; ++j)
                 t->st.lists_presorted[p][j] = (int64_t)hc[c_long + 2 * p + j];
