@@ -139,8 +139,9 @@ __global__ __launch_bounds__(256) void k_morton(const float *__restrict__ pts, i
 
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
-constexpr int RS_ITEMS = 24;  // 6144 keys per tile: two tiles fill a CU's LDS
-constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
+// Keys per thread and tile: 24 (6144 keys: two tiles fill a CU's LDS) for large
+// sorts; fewer where those tiles would leave CUs idle (see rs_items).
+constexpr int RS_ITEMS = 24;
 constexpr uint64_t FLAG_AGG = 1ull << 62;
 constexpr uint64_t FLAG_INC = 2ull << 62;
 constexpr uint64_t VAL_MASK = (1ull << 62) - 1;
@@ -159,10 +160,12 @@ __device__ __forceinline__ void st_u64(uint64_t *p, uint64_t v) {
 // tile in LDS in digit order and writes it out with coalesced runs. `hist`: the
 // pass's 256 digit counts over all keys, whose exclusive scan every tile takes
 // for itself (a launch of its own took as long as a small pass).
+template <int ITEMS>
 __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
     uint32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ hist,
     uint64_t *__restrict__ status, int *__restrict__ tile_ctr) {
+    constexpr int RS_TILE = RS_THREADS * ITEMS;
     __shared__ uint64_t s_k[RS_TILE];
     __shared__ uint32_t s_v[RS_TILE];
     __shared__ uint32_t s_wh[RS_WAVES][256];
@@ -183,20 +186,20 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
     const int64_t base = (int64_t)tile * RS_TILE;
     const int tn = (int)((n - base) < RS_TILE ? (n - base) : RS_TILE);
 
-    uint64_t k[RS_ITEMS];
-    uint32_t v[RS_ITEMS];
-    uint32_t rk[RS_ITEMS];
+    uint64_t k[ITEMS];
+    uint32_t v[ITEMS];
+    uint32_t rk[ITEMS];
 #pragma unroll
-    for (int i = 0; i < RS_ITEMS; ++i) {
-        const int li = w * (RS_ITEMS * 64) + i * 64 + lane;
+    for (int i = 0; i < ITEMS; ++i) {
+        const int li = w * (ITEMS * 64) + i * 64 + lane;
         const bool valid = li < tn;
         k[i] = valid ? kin[base + li] : 0ull;
         v[i] = valid ? vin[base + li] : 0u;
     }
     const uint64_t ltm = lanemask_lt();
 #pragma unroll
-    for (int i = 0; i < RS_ITEMS; ++i) {
-        const int li = w * (RS_ITEMS * 64) + i * 64 + lane;
+    for (int i = 0; i < ITEMS; ++i) {
+        const int li = w * (ITEMS * 64) + i * 64 + lane;
         const bool valid = li < tn;
         const uint32_t d = (uint32_t)(k[i] >> shift) & 255u;
         uint64_t peers = __ballot(valid);
@@ -254,8 +257,8 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < RS_ITEMS; ++i) {
-        const int li = w * (RS_ITEMS * 64) + i * 64 + lane;
+    for (int i = 0; i < ITEMS; ++i) {
+        const int li = w * (ITEMS * 64) + i * 64 + lane;
         if (li < tn) {
             const uint32_t d = rk[i] >> 16;
             const uint32_t pos = s_excl[d] + s_wh[w][d] + (rk[i] & 0xffffu);
@@ -857,15 +860,28 @@ __global__ void k_node_sets(const Node *__restrict__ nodes, int64_t L,
 
 // ---------------------------------------------------------------------------
 
+// Keys per thread of a sort of n keys, from the time of one pass in us:
+//   n         5 10^4   1.5 10^5   3 10^5   6 10^5   10^6    2 10^6   2^24
+//   4            7.1       12.2     17.3     26.7   37.1      62      345
+//   8            8.6       11.0     13.6     19.4   25.4      40      221
+//   12           9.3       11.3     13.8     15.6   23.0      34      188
+//   24          13.9       15.8     17.1     19.4   22.4      30      146
+// (small tiles fill the chip sooner, but each looks back over more tiles)
+static int rs_items(int64_t n) {
+    return n < 100000 ? 4 : (n < 400000 ? 8 : (n < 900000 ? 12 : RS_ITEMS));
+}
+
+
 // Scratch of a radix sort of n keys in npass passes, to be zero before it: the
 // digit counts of all passes, the tiles' status words and the tile counters.
 struct SortScratch {
     DBuf buf;
     int64_t ntiles = 0;
-    int npass = 0;
+    int npass = 0, items = RS_ITEMS;
     static constexpr size_t HIST_WORDS = kMaxPass * 256 / 2, CTR_WORDS = kMaxPass;
     jz_status get(const AllocCtx *ac, int64_t n, int np, hipStream_t s) {
-        ntiles = (n + RS_TILE - 1) / RS_TILE;
+        items = rs_items(n);
+        ntiles = (n + RS_THREADS * items - 1) / (RS_THREADS * items);
         npass = np;
         return buf.get(ac, words() * sizeof(uint64_t), s);
     }
@@ -882,10 +898,12 @@ struct SortScratch {
 // (the result is where the last pass wrote).
 static jz_status onesweep_passes(const SortScratch &sc, uint64_t *&kin, uint32_t *&vin,
                                  uint64_t *&kout, uint32_t *&vout, int64_t n, hipStream_t s) {
+    const auto pass = sc.items == 4   ? k_onesweep<4>
+                      : sc.items == 8 ? k_onesweep<8>
+                                      : (sc.items == 12 ? k_onesweep<12> : k_onesweep<RS_ITEMS>);
     for (int p = 0; p < sc.npass; ++p) {
-        k_onesweep<<<(unsigned)sc.ntiles, RS_THREADS, 0, s>>>(kin, vin, kout, vout, n, 8 * p,
-                                                              sc.hist() + 256 * p, sc.status(p),
-                                                              sc.ctr(p));
+        pass<<<(unsigned)sc.ntiles, RS_THREADS, 0, s>>>(kin, vin, kout, vout, n, 8 * p,
+                                                        sc.hist() + 256 * p, sc.status(p), sc.ctr(p));
         std::swap(kin, kout);
         std::swap(vin, vout);
     }
@@ -1158,8 +1176,11 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
     JZ_TRY(v1.get(ac, n * sizeof(uint32_t), s));
     k_build_init<<<std::min<unsigned>(blocks_for((int64_t)sc.words(), 256), 1024), 256, 0, s>>>(
         sc.buf.as<unsigned long long>(), sc.words(), bbox);
-    const unsigned gb = std::min<unsigned>(blocks_for(n, 256), 1024);
-    k_bbox<<<gb, 256, 0, s>>>(points, n, bbox);
+    // (a block ends in seven atomics on the same words: a block per 1024 points,
+    // up to 1024 blocks, took 27 us at 10^6 points and 31 at 2^22; a block per
+    // 8192, at least 128, takes 13 and 23; all 1024 at 2^24 take 53, 512 take 61)
+    const int64_t bb = std::min<int64_t>(std::max<int64_t>(n / 8192, 128), 1024);
+    k_bbox<<<(unsigned)std::min<int64_t>(blocks_for(n, 256 * 8), bb), 256, 0, s>>>(points, n, bbox);
     k_morton<<<std::min<unsigned>(blocks_for(n, 256 * 8), 2048), 256, 0, s>>>(
         points, n, bbox, bits, t->d_set_off.as<int64_t>(), t->nsets, npass, k0.as<uint64_t>(),
         v0.as<uint32_t>(), sc.hist());
@@ -1229,13 +1250,13 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
     t->L[0] = m0 - 1;
 
     // 6-7: node sizes at leaf splits, coarser planes
-    DBuf d_nsz, d_slv, lsiA, lsiB;
-    JZ_TRY(d_nsz.get(ac, m0 * sizeof(int), s));
-    JZ_TRY(d_slv.get(ac, m0, s));
-    k_split_sizes<<<blocks_for(m0, 256), 256, 0, s>>>(keys, n, bits3, has_sets, t->spl[0].as<int>(),
-                                                     cnts + 0, o.leaf_max, d_nsz.as<int>(),
-                                                     d_slv.as<uint8_t>());
     if (P > 1) {
+        DBuf d_nsz, d_slv, lsiA, lsiB;
+        JZ_TRY(d_nsz.get(ac, m0 * sizeof(int), s));
+        JZ_TRY(d_slv.get(ac, m0, s));
+        k_split_sizes<<<blocks_for(m0, 256), 256, 0, s>>>(
+            keys, n, bits3, has_sets, t->spl[0].as<int>(), cnts + 0, o.leaf_max, d_nsz.as<int>(),
+            d_slv.as<uint8_t>());
         JZ_TRY(lsiA.get(ac, m0 * sizeof(int), s));
         JZ_TRY(lsiB.get(ac, m0 * sizeof(int), s));
         const unsigned nbp = blocks_for(m0, LF_TILE);
