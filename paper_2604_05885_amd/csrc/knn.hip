@@ -550,6 +550,12 @@ constexpr int LEAF_PRESORT = 2048;
 // their leaf done.
 constexpr int LEAF_FIRST = 256;
 constexpr int LEAF_MANY = 1 << 17;
+// Up to this many leaves, four waves share each one's queries: the chip has 1024
+// SIMDs, and a wave's time is a serial chain of drains (leaf stage at 4096
+// clustered points, k = 8: 75 us with one wave, 65 with four; at 20 000, k = 32:
+// 152 and 134; at 50 000, 1356 leaves, 230 with one and more with four, each
+// staging every tile again).
+constexpr int LEAF_FEW = 768;
 constexpr int TILE_PTS = 255; // source points staged per batch (positions fit a byte)
 constexpr int FILLER = 255;   // tile position of a point at infinity with the padding index
 constexpr int HALF = 128;     // tile positions filtered at a time (32 blocks of 4 per lane row)
@@ -795,7 +801,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     int sort_cap, int presorted, int out_stride, int col0, int kw,
     const int *__restrict__ scnt0, int src_hi, int qry_lo, float Lp,
     const float *__restrict__ rleaf, const int *__restrict__ first,
-    const unsigned long long *__restrict__ n_first, int first_len, int row_align) {
+    const unsigned long long *__restrict__ n_first, int first_len, int row_align, int lg_parts) {
     // Lp: period of the cube (PER), Lh its half
     const float Lh = 0.5f * Lp;
     // one block per wave: the staged list (LCAP entries), the point tile
@@ -808,7 +814,9 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     // the first waves take the leaves with lists longer than first_len (in
     // `first`), the others every leaf in order except those
-    const int wv = xcd_block(blk_x(), nblk_x()) * WPB + w;
+    // (2^lg_parts waves share a leaf: part p answers a run of its queries)
+    const int n_blk = nblk_x() >> lg_parts, part = blk_x() / n_blk;
+    const int wv = xcd_block(blk_x() - part * n_blk, n_blk) * WPB + w;
     const int nfirst = (int)uni(*n_first);
     int A;
     if (wv < nfirst) {
@@ -832,13 +840,16 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         const uint64_t qm = __ballot(isq);
         if (isq) reinterpret_cast<uint8_t *>(L + O_Q)[__popcll(qm & lanemask_lt())] = (uint8_t)lane;
         acount = uni((int)__popcll(qm));
-        if (acount == 0) return;
         wave_lds_sync();
     }
+    const int part_q = 64 >> lg_parts, first_q = part * part_q;  // this wave's queries
+    acount = min(acount - first_q, part_q);
+    if (acount <= 0) return;
     const int lgS = acount <= 16 ? 2 : (acount <= 32 ? 1 : 0);  // log2 lanes per query
     const int q = lane & ((64 >> lgS) - 1), h = lane >> (6 - lgS);
     const bool act = q < acount;
-    const int qpos = types ? (int)sel[act ? q : 0] : (act ? q : 0);
+    const int q_leaf = first_q + (act ? q : 0);
+    const int qpos = types ? (int)sel[q_leaf] : q_leaf;
     const float4 me = pts[a.start + qpos];
     const int64_t row = (int64_t)__float_as_int(me.w) - qry_lo;
     const int base = leaf_base ? leaf_base[A] : 0;
@@ -937,7 +948,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     // points meet an empty top-k, where every point is accepted, so they are
     // merged in sorted chunks instead of being queued (lane h of a query's S
     // takes positions h, h + S, ...).
-    int own = acount;
+    int own = uni(a.count);
     if (types) {
         const float4 p = pts[a.start + min(lane, uni(a.count) - 1)];
         const bool real = lane < a.count && __float_as_int(p.w) < src_hi;
@@ -948,9 +959,10 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             tile[pos] = p;
             tidx[pos] = __float_as_int(p.w);
         }
-    } else if (act && h == 0) {
-        tile[q] = me;
-        tidx[q] = __float_as_int(me.w);
+    } else if (lane < own) {
+        const float4 p = pts[a.start + lane];
+        tile[lane] = p;
+        tidx[lane] = __float_as_int(p.w);
     }
     wave_lds_sync();
     {
@@ -1209,7 +1221,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         atomicAdd(st + 1 * STAT_SLOTS, (unsigned long long)visited);
         atomicAdd(st + 2 * STAT_SLOTS, (unsigned long long)rounds);
         atomicAdd(st + 3 * STAT_SLOTS, (unsigned long long)steps);
-        if (len > LCAP)
+        if (len > LCAP && part == 0)
             atomicAdd(st + (len <= max(sort_cap, presorted) ? 4 : 5) * STAT_SLOTS, 1ull);
     }
 }
@@ -1217,7 +1229,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
 typedef void (*leaf_fn)(const int2 *, const int2 *, const Node *, const float4 *, int, const int *,
                         int32_t *, float *, unsigned long long *, const unsigned long long *, int,
                         int, int, int, int, const int *, int, int, float, const float *,
-                        const int *, const unsigned long long *, int, int);
+                        const int *, const unsigned long long *, int, int, int);
 
 template <int K, bool LO, bool PER>
 leaf_fn leaf_ptr() {
@@ -1394,17 +1406,18 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
         if (ev.on) JZ_HIP(hipEventRecord(ev[1], s));
         // k <= 32: one pass; larger k: passes of 32 neighbours, each after
         // the last key of the one before
+        const int lg_parts = t->L[0] <= LEAF_FEW ? 2 : 0;
         const uintptr_t places = (uintptr_t)idx | (uintptr_t)dist2 | 4 * (uintptr_t)k;
         const int row_align = places & 4 ? 4 : (places & 8 ? 8 : 16);
         for (int col = 0; col < k; col += 32) {
             const leaf_fn fn = leaf_kernel(k, col, per);
-            fn<<<blocks_for(n_waves, WPB), 64 * WPB, 0, s>>>(
+            fn<<<blocks_for(n_waves, WPB) << lg_parts, 64 * WPB, 0, s>>>(
                 segs[0].as<int2>(), lists[0].as<int2>(), t->nodes[0].as<Node>(),
                 t->pts4.as<float4>(), (int)t->L[0], t->nsets > 1 ? t->leaf_base.as<int>() : nullptr,
                 idx, dist2, ctr + CTR_STATS, ctr + CTR_FLAG, leaf_cap, sort_max, k, col,
                 std::min(32, k - col), joint ? t->src_cnt[0].as<int>() : nullptr,
                 joint ? (int)t->n_src : INT_MAX, joint ? (int)t->n_src : 0, period,
-                d_rleaf.as<float>(), d_first.as<int>(), ctr + c_first, first_len, row_align);
+                d_rleaf.as<float>(), d_first.as<int>(), ctr + c_first, first_len, row_align, lg_parts);
             JZ_HIP(hipGetLastError());
         }
         if (ev.on) JZ_HIP(hipEventRecord(ev[2], s));

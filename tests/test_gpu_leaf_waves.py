@@ -1,6 +1,7 @@
-"""GPU parity of the kNN leaf stage where its box tests leave out the queries that
-need none of them and leaves with long lists start first. Bit for bit against
-the oracle."""
+"""GPU parity of the kNN leaf stage where it starts its waves differently: a
+leaf shared by several waves in trees of few leaves, on both sides of the leaf
+count at which that ends, and leaves with long lists started first. Bit for bit
+against the oracle."""
 import numpy as np
 import pytest
 
@@ -9,11 +10,37 @@ from paper_2604_05885_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
+FEW = 768
+
 
 @pytest.fixture(scope="module")
 def jz():
     from paper_2604_05885_amd import api
     return api
+
+
+@pytest.mark.parametrize("n,leaf_max,k", [
+    (15, 64, 7), (16, 64, 16), (17, 64, 17), (33, 64, 33), (49, 64, 8),
+    (FEW, 1, 9), (FEW + 1, 1, 9), (6 * FEW, 7, 20), (24000, 64, 40), (40000, 64, 4)])
+def test_shared_leaves(jz, n, leaf_max, k):
+    import torch
+    for p in (inputs.uniform(n, 500 + n), inputs.clustered(n, max(1, n // 900), 501 + n)):
+        with jz.jz_build(torch.from_numpy(p).cuda(), jz.default_opts(leaf_max=leaf_max)) as t:
+            gi, gd = t.knn(k)
+            gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
+        wi, wd = oracle.knn_kd(p, k)
+        assert np.array_equal(gi, wi) and np.array_equal(gd.view(np.uint32), wd.view(np.uint32))
+
+
+@pytest.mark.parametrize("m,nq,k", [(3000, 1, 5), (900, 17, 33), (20, 3000, 20), (20000, 9000, 12)])
+def test_shared_leaves_point_types(jz, m, nq, k):
+    import torch
+    s, q = inputs.clustered(m, max(1, m // 900), 601), inputs.uniform(nq, 602)
+    with jz.jz_build_joint(torch.from_numpy(s).cuda(), torch.from_numpy(q).cuda()) as t:
+        gi, gd = t.knn_query(k)
+        gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
+    wi, wd = oracle.knn_cross_kd(s, q, k)
+    assert np.array_equal(gi, wi) and np.array_equal(gd.view(np.uint32), wd.view(np.uint32))
 
 
 @pytest.mark.parametrize("n,k", [(3000, 12), (60000, 12)])
