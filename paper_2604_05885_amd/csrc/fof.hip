@@ -355,7 +355,11 @@ __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b
 // With box tests and distances on the vector unit, and every lane walking its
 // own links (a dense source cost a lane up to 64 steps and as many lanes the
 // same compare-and-swap), the kernel took 3.63 ms at 2^24 clustered points and
-// alpha = 0.2, now 2.02; 1.03 ms at 10^6, now 0.34; 0.58 at 3 10^5, now 0.235.
+// alpha = 0.2, now 1.68; 1.03 ms at 10^6, now 0.24; 0.58 at 3 10^5, now 0.16.
+// The chunks of a whole leaf's list grow from one entry: every wave of a dense
+// region starts at the same time, when nothing is joined, and with chunks of 64
+// each worked through all of its first 64 sources (2.0 ms at 2^24, 0.34 at
+// 10^6, 0.23 at 3 10^5, and 5.6 10^9 pairs tested at 2^24 against 4.0).
 template <bool PER>
 __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
     const int2 *__restrict__ seg, const int2 *__restrict__ list, const Node *__restrict__ leaves,
@@ -457,12 +461,14 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
         wave_lds_sync();
     }
 
-    for (int t0 = 0; t0 < len; t0 += 64) {
-        // up to 64 sources, one per lane
+    for (int t0 = 0, lim; t0 < len; t0 = lim) {
+        // up to 64 sources, one per lane; a whole leaf takes 1, 1, 2, 4, ... at
+        // a time, since the first ones join it to most of the others
+        lim = min(t0 + (wA ? min(t0 + 1, 64) : 64), len);
         int e_st = 0, e_ct = 0, e_wh = 0;
         float4 e_lo = make_float4(0, 0, 0, 0), e_hi = e_lo;
         bool keep = false;
-        if (t0 + lane < len) {
+        if (t0 + lane < lim) {
             const int B = gl[t0 + lane].x;
             const float4 *rec = reinterpret_cast<const float4 *>(leaves + B);
             e_lo = rec[0];

@@ -58,3 +58,15 @@ def test_far_queries(jz, n, k):
         x = p + np.float32(1.0 if period else 0.0)
         wi, wd = oracle.knn_kd_periodic(x, period, k) if period else oracle.knn_kd(x, k)
         assert np.array_equal(gi, wi) and np.array_equal(gd.view(np.uint32), wd.view(np.uint32))
+
+
+@pytest.mark.parametrize("leaf_max,alpha", [(64, 0.1), (64, 0.6), (9, 0.4), (1, 0.4)])
+def test_fof_dense_lists(jz, leaf_max, alpha):
+    """Whole leaves with lists around the sizes at which the chunks of sources
+    grow: points of one dense clump, all leaves of which reach each other."""
+    import torch
+    for n in (64 * 4, 65 * 9, 131 * 9, 12000):
+        p = inputs.clustered(n, 1, 700 + n)
+        b = inputs.linking_length(n, alpha)
+        with jz.jz_build(torch.from_numpy(p).cuda(), jz.default_opts(leaf_max=leaf_max)) as t:
+            assert np.array_equal(t.fof(b).cpu().numpy(), oracle.fof_kd(p, b)), n
