@@ -183,24 +183,26 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Work-group and work-item indices read straight from the hardware registers
-// and the dispatch packet. The device library's accessors behind blockIdx,
-// threadIdx, gridDim and blockDim are not inlined into code built with a
-// different IEEE mode (the leaf-stage files): there they become calls, each
+// and the hidden kernel arguments. The device library's accessors behind
+// blockIdx, threadIdx, gridDim and blockDim are not inlined into code built with
+// a different IEEE mode (the leaf-stage files): there they become calls, each
 // with a stack frame, and in the largest kernels the registers live across
 // them spill to scratch memory.
+// Not from the dispatch packet either: it lies in the queue's ring in host
+// memory, and every wave that reads it there waits for that read (a kernel that
+// sets two words per point took 15 us at 5 10^4 points with it, 2.4 us
+// with the arguments; the walk steps of such a set lost 8 to 10 us a level).
 __device__ __forceinline__ unsigned blk_x() { return __builtin_amdgcn_workgroup_id_x(); }
 __device__ __forceinline__ unsigned tid_x() { return __builtin_amdgcn_workitem_id_x(); }
-// dispatch packet: workgroup_size_x (16 bits) at byte 4, grid_size_x (work
-// items, 32 bits) at byte 12
-typedef const __attribute__((address_space(4))) uint16_t dispatch_u16;
-typedef const __attribute__((address_space(4))) uint32_t dispatch_u32;
+// hidden arguments: the number of work-groups (32 bits) at byte 0, their size
+// (16 bits) at byte 12
+typedef const __attribute__((address_space(4))) uint16_t hidden_u16;
+typedef const __attribute__((address_space(4))) uint32_t hidden_u32;
 __device__ __forceinline__ unsigned bdim_x() {
-    return ((dispatch_u16 *)__builtin_amdgcn_dispatch_ptr())[2];
+    return ((hidden_u16 *)__builtin_amdgcn_implicitarg_ptr())[6];
 }
 __device__ __forceinline__ unsigned nblk_x() {
-    const unsigned wg = ((dispatch_u16 *)__builtin_amdgcn_dispatch_ptr())[2];
-    const unsigned gs = ((dispatch_u32 *)__builtin_amdgcn_dispatch_ptr())[3];
-    return (gs + wg - 1) / wg;
+    return ((hidden_u32 *)__builtin_amdgcn_implicitarg_ptr())[0];
 }
 
 // ---------------------------------------------------------------------------
