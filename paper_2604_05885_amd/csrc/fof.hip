@@ -25,18 +25,83 @@
 
 namespace {
 
-// The start of a call: every point its own root; the smallest input index of
+// A leaf's "whole" flag: its points are one group, and (OWN) their roots say so;
+// (WALK) the node walk found it, and the leaf stage joins its points.
+constexpr int WHOLE_WALK = 1, WHOLE_OWN = 2;
+
+// The start of a call, one wave per leaf: its own links as a mask per lane, the
+// components closed in registers, and every point's root the first of its
+// component; a leaf that is one component is whole. The smallest input index of
 // every group starts as its root's own (a root is a member; a point that stays
 // a root of itself needs no update at all); the counters zero.
-__global__ __launch_bounds__(256) void k_fof_init(const float4 *__restrict__ pts, int64_t n,
-                                                  int *__restrict__ uf, int *__restrict__ minidx,
-                                                  unsigned long long *__restrict__ ctr, int nctr) {
-    const int64_t i = (int64_t)blk_x() * bdim_x() + tid_x();
-    if (i < n) {
-        uf[i] = (int)i;
-        minidx[i] = __float_as_int(pts[i].w);
+// Plain stores into a forest that nothing else has touched, from points that
+// have to be read here anyway. With the components found where the pairs of
+// leaves are worked on, no leaf of a dense region was joined when its
+// neighbours' waves began: a source of 64 connected points was 64 groups, joined
+// to the receiving leaf one after another, 2 us each, and the slowest waves set
+// the leaf kernel's length (clustered, alpha = 0.2: 0.14 ms at 5 10^4 points,
+// 0.23 at 10^6, 1.65 at 2^24; now 0.09, 0.15 and 1.28). At 2^24 points this
+// kernel takes 0.33 ms, 64 distances a point on the vector unit; its 0.4 GB of
+// traffic would take 0.09. A search from member to member, which ends early in a
+// dense leaf, took 0.59: a chain of scalar steps per point. Leaving out leaves
+// whose box is within b gains nothing.
+template <bool PER>
+__global__ __launch_bounds__(64 * WPB) void k_fof_init(
+    const Node *__restrict__ leaves, const float4 *__restrict__ pts, int n_leaves, float b2,
+    const float *__restrict__ b2n, int *__restrict__ whole, int *__restrict__ uf,
+    int *__restrict__ minidx, unsigned long long *__restrict__ ctr, int nctr, float L) {
+    const float Lh = 0.5f * L;
+    __shared__ float4 s_tile[WPB][64];
+    for (int i = blk_x() * (64 * WPB) + tid_x(); i < nctr; i += nblk_x() * (64 * WPB)) ctr[i] = 0;
+    const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
+    const int A = xcd_block(blk_x(), nblk_x()) * WPB + w;
+    if (A >= n_leaves) return;
+    const Node a = leaves[A];
+    const int astart = uni(a.start), acount = uni(a.count);
+    const bool act = lane < acount;
+    const int my = astart + (act ? lane : 0);
+    const float4 me = pts[my];
+    const float bb = b2n ? b2n[A] : b2;
+    float4 *tile = s_tile[w];
+    tile[lane] = me;
+    wave_lds_sync();
+    // the leaf's own links, exactly (both directions, as masks of lanes; a
+    // difference's sign is exact, and shifted in with one instruction)
+    unsigned far[2] = {0, 0};
+#pragma unroll
+    for (int hf = 1; hf >= 0; --hf) {
+#pragma unroll 4
+        for (int f = min(acount, 32 * hf + 32) - 1; f >= 32 * hf; --f) {
+            const float4 p = tile[f];
+            const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, L, Lh);
+            far[hf] = __builtin_amdgcn_alignbit(far[hf], __float_as_uint(bb - dd), 31);
+        }
     }
-    if (i < nctr) ctr[i] = 0;
+    uint64_t adj = ~((uint64_t)far[1] << 32 | far[0]) & (~0ull >> (64 - acount));
+    if (!act) adj = 0;
+    // components: from the lowest point not yet in one, the links of all its
+    // members are added until nothing changes
+    int lead = lane;  // the first point of this lane's component
+    bool one = acount == 1;
+    uint64_t todo = __ballot((adj & ~(1ull << lane)) != 0);
+    while (todo) {
+        const int s = __ffsll((unsigned long long)todo) - 1;
+        uint64_t reach = 1ull << s, prev = 0;
+        while (reach != prev) {
+            prev = reach;
+            const uint64_t add = (reach >> lane) & 1ull ? adj : 0ull;
+            reach |= (uint64_t)uni(wave_or((unsigned)(add >> 32))) << 32 |
+                     uni(wave_or((unsigned)add));
+        }
+        if ((reach >> lane) & 1ull) lead = s;
+        todo &= ~reach;
+        one = one || reach == (acount == 64 ? ~0ull : (1ull << acount) - 1ull);
+    }
+    if (act) {
+        uf[my] = astart + lead;
+        minidx[my] = __float_as_int(me.w);
+    }
+    if (lane == 0) whole[A] = one ? WHOLE_OWN : 0;
 }
 
 __global__ void k_node_b2(const int *__restrict__ node_set, int64_t L,
@@ -51,7 +116,8 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_p2n(const int *__restrict__ pa
                                                  const Node *__restrict__ nodes, int n_par,
                                                  const int *__restrict__ whole_par,
                                                  int *__restrict__ whole, int *__restrict__ uf,
-                                                 float b2, const float *__restrict__ b2n, float L) {
+                                                 float b2, const float *__restrict__ b2n, float L,
+                                                 int leaf_level) {
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     const int P = xcd_block(blk_x(), nblk_x()) * WPB + w;
     if (P >= n_par) return;
@@ -61,8 +127,9 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_p2n(const int *__restrict__ pa
     for (int c = c0 + lane; c < c1; c += 64) {
         const Node me = nodes[c];
         const float bb = b2n ? b2n[c] : b2;
-        const int wc = (wp || box_up2_m<PER>(me, me, L) <= bb) ? 1 : 0;
-        whole[c] = wc;
+        const int wc = (wp || box_up2_m<PER>(me, me, L) <= bb) ? WHOLE_WALK : 0;
+        if (!leaf_level) whole[c] = wc;
+        else if (wc && whole[c] == 0) whole[c] = wc;
         if (wp && c != c0) uf[me.start] = first;
     }
 }
@@ -189,8 +256,8 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_step(
                                 !(wc && ld_cached(whole + x) &&
                                   uf_find_c(uf, me[j].start) == uf_find_c(uf, o.start))) {
                                 uf_union_c(uf, me[j].start, o.start);
-                                st_rel(whole + c, 1);
-                                st_rel(whole + x, 1);
+                                if (!wc) st_rel(whole + c, WHOLE_WALK);
+                                if (!ld_cached(whole + x)) st_rel(whole + x, WHOLE_WALK);
                             }
                         } else {
                             bool emit = down;
@@ -262,7 +329,8 @@ __device__ __forceinline__ uint64_t pair_mask(const float *tilef, int c, float a
 template <bool PER>
 __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b0, int my,
                                             const float4 &me, const float4 *tile, int *rootT,
-                                            int *uf, float bb, float L, float Lh, int &ra) {
+                                            int *uf, float bb, float L, float Lh, int &ra,
+                                            int &last) {
     const int lane = lane_id();
     uint64_t linking = __ballot(lm != 0);
     if (!linking) return;
@@ -286,6 +354,35 @@ __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b
         }
         return;
     }
+    if (wA) {
+        // one group on this side: the source's groups are joined to it side by
+        // side, every lane taking another of its links (from its own number on)
+        while (linking) {
+            const uint64_t want = (uint64_t)uni(wave_or((unsigned)(lm >> 32))) << 32 |
+                                  uni(wave_or((unsigned)lm));
+            int rt = -1;
+            if ((want >> lane) & 1ull) rt = uf_find_c(uf, b0 + lane);
+            const int r0 = uf_find_c(uf, __builtin_amdgcn_readfirstlane(my));
+            rootT[lane] = rt;
+            wave_lds_sync();
+            lm &= __ballot(rt >= 0 && rt != r0);
+            const uint64_t up = lm >> lane << lane;
+            const int f = lm ? __ffsll((unsigned long long)(up ? up : lm)) - 1 : 0;
+            const bool ok = lm != 0 && linked(f);
+            lm &= ~(1ull << f);
+            const int rj = ok ? rootT[f] : -1;
+            bool first = false;
+            for (uint64_t left = __ballot(ok); left;) {
+                const int l0 = __ffsll((unsigned long long)left) - 1;
+                left &= ~__ballot(rj == __builtin_amdgcn_readlane(rj, l0));
+                first = first || lane == l0;
+            }
+            if (first) uf_union_c(uf, my, b0 + f);
+            linking = __ballot(lm != 0);
+            wave_lds_sync();
+        }
+        return;
+    }
     // roots of the source's points that some lane links to
     const uint64_t want = (uint64_t)uni(wave_or((unsigned)(lm >> 32))) << 32 |
                           uni(wave_or((unsigned)lm));
@@ -297,7 +394,6 @@ __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b
     const uint64_t eq = __ballot(rt == r0);
     if (lm && ra < 0) ra = uf_find_c(uf, my);
     uint64_t com = ra == r0 ? 0ull : lm & eq, rest = lm & ~eq;
-    int last = -1;  // the last root this lane's group was joined with
     while (__ballot((com | rest) != 0)) {
         // each lane's next link to a group it has not joined
         int f = 0, rj = -1;
@@ -338,33 +434,34 @@ __device__ __forceinline__ void link_source(uint64_t lm, bool wA, bool wB, int b
 // Leaf stage: one wave per receiving leaf A, lanes over its points, sources
 // B >= A (a point links to the later points of a pair only).
 //
-// The leaf's own points come first: their links are a mask per lane, its
-// components are closed in registers, and one union per point joins them; a
-// leaf whose points are all connected becomes "whole" for the other waves too
-// (and one the node walk found whole only has its points joined here).
+// Every leaf's own links are joined already, but for a leaf that only the walk
+// found whole: its points are joined here.
 // Then source by source (skipped when A and B are both whole and already one
-// group, or when no lane's point reaches the source's box): the next source's
-// points are loaded while the current one is worked on; a matrix filter gives
-// each lane the points its own may link to, and only a pair that would join two
-// groups is evaluated with the fixed float32 expression. Two whole leaves need
-// one link. Otherwise the roots of the source's linked points are looked up, in
-// parallel; the points under the first one's root count as one (in a dense
-// region they all are), and of the lanes that would join the same two groups
-// only one does. Groups only ever merge, so equal roots, even looked up at
-// different times, mean already connected.
+// group, or when no lane's point both reaches the source's box and was outside
+// its group): the next source's points are loaded while the current one is
+// worked on; a matrix filter gives each lane the points its own may link to, and
+// only a pair that would join two groups is evaluated with the fixed float32
+// expression. Two whole leaves need one link. A whole A is joined to the
+// source's groups side by side; otherwise the roots of the source's linked
+// points are looked up, in parallel, the points under the first one's root count
+// as one (in a dense region they all are), and of the lanes that would join the
+// same two groups only one does. Groups only ever merge, so equal roots, even
+// looked up at different times, mean already connected.
 // With box tests and distances on the vector unit, and every lane walking its
 // own links (a dense source cost a lane up to 64 steps and as many lanes the
 // same compare-and-swap), the kernel took 3.63 ms at 2^24 clustered points and
-// alpha = 0.2, now 1.68; 1.03 ms at 10^6, now 0.24; 0.58 at 3 10^5, now 0.16.
+// alpha = 0.2, then 2.0; 1.03 ms at 10^6, then 0.34; 0.58 at 3 10^5, then 0.23.
 // The chunks of a whole leaf's list grow from one entry: every wave of a dense
-// region starts at the same time, when nothing is joined, and with chunks of 64
-// each worked through all of its first 64 sources (2.0 ms at 2^24, 0.34 at
-// 10^6, 0.23 at 3 10^5, and 5.6 10^9 pairs tested at 2^24 against 4.0).
+// region starts at the same time, when few leaves are joined, and with chunks of
+// 64 each worked through all of its first 64 sources (2.0 -> 1.65 ms at 2^24,
+// 0.34 -> 0.23 at 10^6; 5.6 -> 3.9 10^9 pairs tested at 2^24). With every leaf's
+// points joined beforehand and a whole leaf joined to several groups at a time:
+// 1.28, 0.15 and, at 3 10^5, 0.08 ms.
 template <bool PER>
 __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
     const int2 *__restrict__ seg, const int2 *__restrict__ list, const Node *__restrict__ leaves,
     const float4 *__restrict__ pts, int n_leaves, float b2, const float *__restrict__ b2n,
-    int *__restrict__ whole, int *__restrict__ uf, unsigned long long *__restrict__ stats,
+    const int *__restrict__ whole, int *__restrict__ uf, unsigned long long *__restrict__ stats,
     const unsigned long long *__restrict__ overflow, float L) {
     const float Lh = 0.5f * L;
     __shared__ float4 s_tile[WPB][64];
@@ -379,52 +476,24 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
     const int my = astart + (act ? lane : 0);
     const float4 me = pts[my];
     const float bb = b2n ? b2n[A] : b2;
-    bool wA = uni(ld_cached(whole + A)) != 0;
+    const int whA = uni(whole[A]);
+    const bool wA = whA != 0;
     const int2 sg = seg[A];
     const int2 *gl = list + uni(sg.x);
     const int len = uni(sg.y);
+    // (found whole by the walk alone: its points are joined here)
+    if (whA == WHOLE_WALK && act && lane > 0) uf_union_c(uf, astart, my);
+    // (the pairs within the leaf, looked at when the call began)
+    unsigned long long evals = (unsigned)acount * (unsigned)acount;
+    if (len == 0) {
+        if (lane == 0) atomicAdd(stats + (A & (STAT_SLOTS - 1)), evals);
+        return;
+    }
     float4 *tile = s_tile[w];
     const float *tilef = reinterpret_cast<const float *>(tile);
     int *rootT = s_root[w];
-    int ra = -1;  // this lane's point's root, as last looked up
-    unsigned long long evals = 0;
-
-    tile[lane] = me;
-    wave_lds_sync();
-    int lead = 0;  // the lane whose point this lane's is joined with
-    if (!wA) {
-        lead = lane;
-        // the leaf's own links, exactly (both directions, as masks of lanes)
-        uint64_t adj = 0;
-        for (int f = 0; f < acount; ++f) {
-            const float4 p = tile[f];
-            const float dd = dist2_m<PER>(me.x, me.y, me.z, p.x, p.y, p.z, L, Lh);
-            adj |= dd <= bb ? 1ull << f : 0ull;
-        }
-        if (!act) adj = 0;
-        evals += (unsigned)acount * (unsigned)acount;
-        // components: from the lowest point not yet in one, the links of all
-        // its members are added until nothing changes
-        uint64_t todo = __ballot((adj & ~(1ull << lane)) != 0);
-        while (todo) {
-            const int s = __ffsll((unsigned long long)todo) - 1;
-            uint64_t reach = 1ull << s, prev = 0;
-            while (reach != prev) {
-                prev = reach;
-                const uint64_t add = (reach >> lane) & 1ull ? adj : 0ull;
-                reach |= (uint64_t)uni(wave_or((unsigned)(add >> 32))) << 32 |
-                         uni(wave_or((unsigned)add));
-            }
-            if ((reach >> lane) & 1ull) lead = s;
-            todo &= ~reach;
-            if (reach == (acount == 64 ? ~0ull : (1ull << acount) - 1ull)) wA = true;
-        }
-        if (acount == 1) wA = true;
-        // (other waves that see the flag take the leaf for one group, which it
-        // is once this wave has joined its points)
-        if (wA && lane == 0) st_rel(whole + A, 1);
-    }
-    if (act && lead != lane) uf_union_c(uf, astart + lead, my);
+    int ra = -1;    // this lane's point's root, as last looked up
+    int last = -1;  // the last root this lane's group was joined with
 
     // the filter's query side: lane l holds component l / 16 (x, y, z, 1) of
     // query 16 g + l % 16 in bq[g], and minus that query's t in tg[g]
@@ -463,9 +532,10 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
 
     for (int t0 = 0, lim; t0 < len; t0 = lim) {
         // up to 64 sources, one per lane; a whole leaf takes 1, 1, 2, 4, ... at
-        // a time, since the first ones join it to most of the others
-        lim = min(t0 + (wA ? min(t0 + 1, 64) : 64), len);
-        int e_st = 0, e_ct = 0, e_wh = 0;
+        // a time, one of many sources 16, 32, 64, ..., since the first ones
+        // join it to most of the others
+        lim = min(t0 + (wA || len > 64 ? min(t0 + (wA ? 1 : 16), 64) : 64), len);
+        int e_st = 0, e_ct = 0, e_wh = 0, e_rt = -2;
         float4 e_lo = make_float4(0, 0, 0, 0), e_hi = e_lo;
         bool keep = false;
         if (t0 + lane < lim) {
@@ -475,8 +545,9 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
             e_hi = rec[1];
             e_st = __float_as_int(e_lo.w);
             e_ct = __float_as_int(e_hi.w);
-            e_wh = ld_cached(whole + B);
-            keep = B != A && !(wA && e_wh && uf_find_c(uf, e_st) == uf_find_c(uf, astart));
+            e_wh = whole[B];
+            if (e_wh) e_rt = uf_find_c(uf, e_st);
+            keep = B != A && !(wA && e_wh && e_rt == uf_find_c(uf, astart));
         }
         uint64_t pend = __ballot(keep);
         const uint64_t wholes = __ballot(e_wh != 0);
@@ -491,9 +562,14 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
                 auto rl = [&](float v) __attribute__((always_inline)) {
                     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), qq));
                 };
-                const bool need = act && point_low2_m<PER>(me.x, me.y, me.z, rl(e_lo.x), rl(e_lo.y),
+                bool need = act && point_low2_m<PER>(me.x, me.y, me.z, rl(e_lo.x), rl(e_lo.y),
                                                            rl(e_lo.z), rl(e_hi.x), rl(e_hi.y),
                                                            rl(e_hi.z), L) <= bb;
+                // (not by a point that is in the group the whole source was in)
+                if (__ballot(need)) {
+                    const int rB = __builtin_amdgcn_readlane(e_rt, qq);
+                    need = need && ra != rB && last != rB;
+                }
                 if (__ballot(need)) {
                     nxt = qq;
                     const int st = __builtin_amdgcn_readlane(e_st, qq);
@@ -518,7 +594,7 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
                 else if (acount > 32) lm = pair_mask<3, PER>(tilef, c, ac, aL, Lh, bq, tg);
                 else if (acount > 16) lm = pair_mask<2, PER>(tilef, c, ac, aL, Lh, bq, tg);
                 else lm = pair_mask<1, PER>(tilef, c, ac, aL, Lh, bq, tg);
-                link_source<PER>(lm, wA, wB, b0, my, me, tile, rootT, uf, bb, L, Lh, ra);
+                link_source<PER>(lm, wA, wB, b0, my, me, tile, rootT, uf, bb, L, Lh, ra, last);
             }
             if (nxt < 0) break;
             wave_lds_sync();
@@ -655,8 +731,10 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
     for (;;) {
         for (int p = 0; p < P; ++p) JZ_TRY(lists[p].ensure(ac, cap[p] * sizeof(int2), s));
         if (ev.on) JZ_HIP(hipEventRecord(ev[0], s));
-        k_fof_init<<<blocks_for(std::max<int64_t>(n, (int64_t)nctr), 256), 256, 0, s>>>(
-            t->pts4.as<float4>(), n, d_uf.as<int>(), d_min.as<int>(), ctr, (int)nctr);
+        (per ? k_fof_init<true> : k_fof_init<false>)<<<blocks_for(t->L[0], WPB), 64 * WPB, 0, s>>>(
+            t->nodes[0].as<Node>(), t->pts4.as<float4>(), (int)t->L[0], b2,
+            sets ? b2n[0].as<float>() : nullptr, whole[0].as<int>(), d_uf.as<int>(),
+            d_min.as<int>(), ctr, (int)nctr, L);
         for (int p = P - 1; p >= 0; --p) {
             const bool top = p == P - 1;
             const int2 *seg_in = top ? t->fof_top_seg.as<int2>() : segs[p + 1].as<int2>();
@@ -667,7 +745,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             const float *bn = sets ? b2n[p].as<float>() : nullptr;
             (per ? k_fof_p2n<true> : k_fof_p2n<false>)<<<blocks_for(n_par, WPB), 64 * WPB, 0, s>>>(
                 par_spl, t->nodes[p].as<Node>(), (int)n_par, whole_par, whole[p].as<int>(),
-                d_uf.as<int>(), b2, bn, L);
+                d_uf.as<int>(), b2, bn, L, p == 0);
             // a top parent has up to ngr children, others a few: enough items
             // for one pass over most parents' children
             const bool many = n_par >= FOF_MANY;
