@@ -139,9 +139,10 @@ __global__ __launch_bounds__(256) void k_morton(const float *__restrict__ pts, i
 
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
-// Keys per thread and tile: 24 (6144 keys: two tiles fill a CU's LDS) for large
-// sorts; fewer where those tiles would leave CUs idle (see rs_items).
-constexpr int RS_ITEMS = 24;
+// Keys per thread and tile: 32 for large sorts (8192 keys: two tiles are what a
+// CU's LDS and registers hold); fewer where those tiles would leave CUs idle
+// (see rs_items).
+constexpr int RS_ITEMS = 32;
 constexpr uint64_t FLAG_AGG = 1ull << 62;
 constexpr uint64_t FLAG_INC = 2ull << 62;
 constexpr uint64_t VAL_MASK = (1ull << 62) - 1;
@@ -157,25 +158,30 @@ __device__ __forceinline__ void st_u64(uint64_t *p, uint64_t v) {
 // id from an atomic counter (so every lower id belongs to a workgroup that has
 // started); each tile ranks its keys per wave with ballots, publishes its digit
 // counts, looks back over earlier tiles for its global offsets, stages the
-// tile in LDS in digit order and writes it out with coalesced runs. `hist`: the
+// tile in LDS in digit order and writes it out with coalesced runs, keys first
+// and then values through the same LDS. What bounds it is the writes, a run of
+// tile / 256 keys per digit that begins and ends within a line another tile
+// writes too: longer tiles are faster though fewer fit (2^24 keys: 147 us with
+// 6144 keys, staged at once, 140 with 8192, 149 with 5120, three per CU; the 0.4
+// GB of a pass would take 85 at the rate of a copy). `hist`: the
 // pass's 256 digit counts over all keys, whose exclusive scan every tile takes
 // for itself (a launch of its own took as long as a small pass).
 template <int ITEMS>
-__global__ __launch_bounds__(RS_THREADS) void k_onesweep(
+__global__ __launch_bounds__(RS_THREADS, ITEMS <= 20 ? 3 : 2) void k_onesweep(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
     uint32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ hist,
     uint64_t *__restrict__ status, int *__restrict__ tile_ctr) {
     constexpr int RS_TILE = RS_THREADS * ITEMS;
     __shared__ uint64_t s_k[RS_TILE];
-    __shared__ uint32_t s_v[RS_TILE];
-    __shared__ uint32_t s_wh[RS_WAVES][256];
-    __shared__ uint32_t s_excl[256];
-    __shared__ uint64_t s_gb[256];
+    __shared__ uint16_t s_wh[RS_WAVES][256];
+    __shared__ uint32_t s_gb[256];  // a digit's first place, less its first in the tile
+    uint32_t *s_v = reinterpret_cast<uint32_t *>(s_k);
     __shared__ int s_tmp[RS_WAVES], s_hist[RS_WAVES];
     __shared__ int s_tile;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid == 0) s_tile = atomicAdd(tile_ctr, 1);
-    for (int i = tid; i < RS_WAVES * 256; i += RS_THREADS) (&s_wh[0][0])[i] = 0;
+    for (int i = tid; i < RS_WAVES * 128; i += RS_THREADS)
+        reinterpret_cast<uint32_t *>(s_wh)[i] = 0;
     const int hv = (int)hist[tid];
     const int hinc = wave_incl_scan(hv);
     if (lane == 63) s_hist[w] = hinc;
@@ -213,7 +219,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
         rk[i] = (d << 16) | (before + (uint32_t)__popcll(peers & ltm));
         const bool leader = valid && ((peers & ltm) == 0ull);
         wave_lds_sync();
-        if (leader) s_wh[w][d] = before + (uint32_t)__popcll(peers);
+        if (leader) s_wh[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
         wave_lds_sync();
     }
     __syncthreads();
@@ -221,10 +227,19 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
     // per digit: wave prefix, tile total, look-back over earlier tiles
     const uint32_t c0 = s_wh[0][tid], c1 = s_wh[1][tid], c2 = s_wh[2][tid], c3 = s_wh[3][tid];
     const uint32_t tot = c0 + c1 + c2 + c3;
-    s_wh[0][tid] = 0;
-    s_wh[1][tid] = c0;
-    s_wh[2][tid] = c0 + c1;
-    s_wh[3][tid] = c0 + c1 + c2;
+    // (s_wh becomes the wave's first place of the digit in the tile)
+    uint32_t texcl;
+    {
+        const int inc = wave_incl_scan((int)tot);
+        if (lane == 63) s_tmp[w] = inc;
+        __syncthreads();
+        texcl = (uint32_t)inc - tot;
+        for (int ww = 0; ww < w; ++ww) texcl += (uint32_t)s_tmp[ww];
+    }
+    s_wh[0][tid] = (uint16_t)texcl;
+    s_wh[1][tid] = (uint16_t)(texcl + c0);
+    s_wh[2][tid] = (uint16_t)(texcl + c0 + c1);
+    s_wh[3][tid] = (uint16_t)(texcl + c0 + c1 + c2);
     uint64_t *mine = status + (size_t)tile * 256 + tid;
     uint64_t excl = 0;
     if (tile == 0) {
@@ -245,34 +260,37 @@ __global__ __launch_bounds__(RS_THREADS) void k_onesweep(
         }
         st_u64(mine, FLAG_INC | (excl + tot));
     }
-    s_gb[tid] = (uint64_t)(uint32_t)doff + excl;
-    {
-        const int vi = (int)tot;
-        const int inc = wave_incl_scan(vi);
-        if (lane == 63) s_tmp[w] = inc;
-        __syncthreads();
-        int add = 0;
-        for (int ww = 0; ww < w; ++ww) add += s_tmp[ww];
-        s_excl[tid] = (uint32_t)(inc - vi + add);
+    s_gb[tid] = (uint32_t)doff + (uint32_t)excl - texcl;
+    __syncthreads();
+    // keys, then values through the same LDS
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int li = w * (ITEMS * 64) + i * 64 + lane;
+        rk[i] = (uint32_t)s_wh[w][rk[i] >> 16] + (rk[i] & 0xffffu);
+        if (li < tn) s_k[rk[i]] = k[i];
+    }
+    __syncthreads();
+    uint32_t dest[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int e = i * RS_THREADS + tid;
+        if (e < tn) {
+            const uint64_t key = s_k[e];
+            dest[i] = s_gb[(uint32_t)(key >> shift) & 255u] + (uint32_t)e;
+            kout[dest[i]] = key;
+        }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int li = w * (ITEMS * 64) + i * 64 + lane;
-        if (li < tn) {
-            const uint32_t d = rk[i] >> 16;
-            const uint32_t pos = s_excl[d] + s_wh[w][d] + (rk[i] & 0xffffu);
-            s_k[pos] = k[i];
-            s_v[pos] = v[i];
-        }
+        if (li < tn) s_v[rk[i]] = v[i];
     }
     __syncthreads();
-    for (int e = tid; e < tn; e += RS_THREADS) {
-        const uint64_t key = s_k[e];
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
-        const uint64_t dest = s_gb[d] + (uint64_t)(e - (int)s_excl[d]);
-        kout[dest] = key;
-        vout[dest] = s_v[e];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int e = i * RS_THREADS + tid;
+        if (e < tn) vout[dest[i]] = s_v[e];
     }
 }
 
@@ -861,14 +879,15 @@ __global__ void k_node_sets(const Node *__restrict__ nodes, int64_t L,
 // ---------------------------------------------------------------------------
 
 // Keys per thread of a sort of n keys, from the time of one pass in us:
-//   n         5 10^4   1.5 10^5   3 10^5   6 10^5   10^6    2 10^6   2^24
-//   4            7.1       12.2     17.3     26.7   37.1      62      345
-//   8            8.6       11.0     13.6     19.4   25.4      40      221
-//   12           9.3       11.3     13.8     15.6   23.0      34      188
-//   24          13.9       15.8     17.1     19.4   22.4      30      146
+//   n         5 10^4   1.5 10^5   3 10^5   6 10^5   10^6    2 10^6   4 10^6   2^24
+//   4            7.1       12.2     17.3     26.7   37.1      62               345
+//   8            8.6       11.0     13.6     19.4   25.4      40               221
+//   12           9.3       11.3     13.8     15.6   23.0      34               188
+//   20                                              22.1      30.3     46.4    147
+//   32                                              25.2      29.2     42.6    138
 // (small tiles fill the chip sooner, but each looks back over more tiles)
 static int rs_items(int64_t n) {
-    return n < 100000 ? 4 : (n < 400000 ? 8 : (n < 900000 ? 12 : RS_ITEMS));
+    return n < 100000 ? 4 : n < 400000 ? 8 : n < 900000 ? 12 : n < 3000000 ? 20 : RS_ITEMS;
 }
 
 
@@ -898,9 +917,11 @@ struct SortScratch {
 // (the result is where the last pass wrote).
 static jz_status onesweep_passes(const SortScratch &sc, uint64_t *&kin, uint32_t *&vin,
                                  uint64_t *&kout, uint32_t *&vout, int64_t n, hipStream_t s) {
-    const auto pass = sc.items == 4   ? k_onesweep<4>
-                      : sc.items == 8 ? k_onesweep<8>
-                                      : (sc.items == 12 ? k_onesweep<12> : k_onesweep<RS_ITEMS>);
+    const auto pass = sc.items == 4    ? k_onesweep<4>
+                      : sc.items == 8  ? k_onesweep<8>
+                      : sc.items == 12 ? k_onesweep<12>
+                      : sc.items == 20 ? k_onesweep<20>
+                                       : k_onesweep<RS_ITEMS>;
     for (int p = 0; p < sc.npass; ++p) {
         pass<<<(unsigned)sc.ntiles, RS_THREADS, 0, s>>>(kin, vin, kout, vout, n, 8 * p,
                                                         sc.hist() + 256 * p, sc.status(p), sc.ctr(p));

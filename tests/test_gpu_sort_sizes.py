@@ -23,3 +23,8 @@ def test_sorted_order(n):
     by_input = np.empty(n, np.uint64)
     by_input[order] = keys
     assert np.array_equal(order, np.argsort(by_input, kind="stable"))
+
+
+@pytest.mark.parametrize("n", [1003520, 1003521, 2999999, 3000000, 3006463, 3006465])
+def test_sorted_order_large_tiles(n):
+    test_sorted_order(n)
