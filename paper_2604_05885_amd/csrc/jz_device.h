@@ -272,17 +272,6 @@ __device__ __forceinline__ double swap32_d(double v) {
 }
 __device__ __forceinline__ float swap32_f(float v) { return __int_as_float(swap32_i(__float_as_int(v))); }
 
-// reduction over each group of 8 lanes (lanes 8g .. 8g + 7)
-__device__ __forceinline__ float group8_min(float v) {
-    v = fminf(v, dpp_f<DPP_XOR1>(v));
-    v = fminf(v, dpp_f<DPP_XOR2>(v));
-    return fminf(v, dpp_f<DPP_HALF_MIRROR>(v));
-}
-__device__ __forceinline__ float group8_max(float v) {
-    v = fmaxf(v, dpp_f<DPP_XOR1>(v));
-    v = fmaxf(v, dpp_f<DPP_XOR2>(v));
-    return fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
-}
 // wave-wide reductions (result in every lane)
 __device__ __forceinline__ int wave_max_i(int v) {
     v = max(v, dpp_i<DPP_XOR1>(v));
@@ -299,14 +288,6 @@ __device__ __forceinline__ float wave_max_f(float v) {
     v = fmaxf(v, dpp_f<DPP_MIRROR>(v));
     v = fmaxf(v, swap16_f(v));
     return fmaxf(v, swap32_f(v));
-}
-__device__ __forceinline__ int wave_min_i(int v) {
-    v = min(v, dpp_i<DPP_XOR1>(v));
-    v = min(v, dpp_i<DPP_XOR2>(v));
-    v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
-    v = min(v, dpp_i<DPP_MIRROR>(v));
-    v = min(v, swap16_i(v));
-    return min(v, swap32_i(v));
 }
 // minimum over each aligned group of G lanes (G a power of 2, wave-uniform)
 __device__ __forceinline__ float group_min_f(float v, int G) {
@@ -339,7 +320,6 @@ __device__ __forceinline__ int wave_sum_i(int v) {
 
 __device__ __forceinline__ float wave_max(float v) { return wave_max_f(v); }
 __device__ __forceinline__ float wave_min(float v) { return group_min_f(v, 64); }
-__device__ __forceinline__ int wave_max_int(int v) { return wave_max_i(v); }
 __device__ __forceinline__ int wave_sum(int v) { return wave_sum_i(v); }
 
 // inclusive prefix sum over the 64 lanes
@@ -412,11 +392,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // ---------------------------------------------------------------------------
-// coherent (L2) loads/stores for data other waves update concurrently
-
-__device__ __forceinline__ int ld_acq(const int *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// coherent stores for data other waves update concurrently
 
 __device__ __forceinline__ void st_rel(int *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -427,36 +403,7 @@ __device__ __forceinline__ void st_rel(int *p, int v) {
 // the higher root to the lower one with compare-and-swap, retry on failure).
 // Invariant: par[x] <= x, so the forest has no cycles and a root is the
 // smallest z-index of its group.
-
-__device__ __forceinline__ int uf_find(int *par, int x) {
-    while (true) {
-        int p = ld_acq(par + x);
-        if (p == x) return x;
-        int gp = ld_acq(par + p);
-        if (gp == p) return p;
-        st_rel(par + x, gp);  // path halving: gp is an ancestor of x
-        x = gp;
-    }
-}
-
-__device__ __forceinline__ void uf_union(int *par, int a, int b) {
-    while (true) {
-        a = uf_find(par, a);
-        b = uf_find(par, b);
-        if (a == b) return;
-        if (a > b) {
-            int t = a;
-            a = b;
-            b = t;
-        }
-        int old = atomicCAS(par + b, b, a);
-        if (old == b) return;
-        b = old;
-    }
-}
-
-// The same operations with parent pointers read through this CU's and this
-// XCD's caches (device-scope reads go past the per-XCD L2 to memory): a read
+// Parent pointers are read through this CU's and this XCD's caches (device-scope reads go past the per-XCD L2 to memory): a read
 // may return an older value, never a wrong one, because a parent only ever
 // moves to an ancestor. An older parent is still an ancestor, an older root
 // is still a member of the group, and equal roots, however old, mean one
@@ -465,7 +412,8 @@ __device__ __forceinline__ void uf_union(int *par, int a, int b) {
 // a node that is not a root, which only the halving itself ever rewrites, and
 // the compare-and-swap on a root fails on a stale guess and returns the
 // current parent, which is smaller, so union's retry loop ends (the larger of
-// its two ids strictly decreases).
+// its two ids strictly decreases). A find halves the path it walks: a parent's
+// parent is an ancestor.
 __device__ __forceinline__ int ld_cached(const int *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -522,4 +470,3 @@ __device__ __forceinline__ int xcd_block(int bid, int nblocks) {
 }
 
 __device__ __forceinline__ unsigned bitlen64(uint64_t v) { return v ? 64u - __clzll(v) : 0u; }
-__device__ __forceinline__ unsigned bitlen32(uint32_t v) { return v ? 32u - __clz(v) : 0u; }

@@ -28,11 +28,6 @@
 namespace {
 
 constexpr int LCAP = 256;  // list entries staged (and sorted) in LDS per wave
-constexpr int prev_pow2(int x) {
-    int m = 1;
-    while (m * 2 <= x) m *= 2;
-    return m;
-}
 constexpr uint64_t PAD_KEY = (0x7f800000ull << 32) | 0xffffffffull;  // (+inf, no index)
 
 __device__ __forceinline__ uint64_t list_key(int2 e) {
@@ -518,25 +513,6 @@ __device__ __forceinline__ void lane_sort(uint64_t *L, int n) {
     if constexpr (NR >= 4) lane_merge<NR, 256, 128>(x, lane);
 #pragma unroll
     for (int r = 0; r < NR; ++r) L[r * 64 + lane] = bits_of(x[r]);
-}
-
-// Insert key into the ascending list b (the largest entry falls off).
-// Inserting the padding key leaves b unchanged, so callers insert
-// unconditionally instead of branching. Each slot computes the carried
-// maximum first and then the slot's minimum in place; the scheduling fence
-// keeps that order, which lets the register allocator update the list in
-// place (with the maxima hoisted, it rotates the list through other
-// registers and pays a copy of every entry per insertion).
-template <int K>
-__device__ __forceinline__ void topk_insert(TopK<K> &b, double key) {
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-        const double e = b.get(i);
-        const double hi = __builtin_fmax(key, e);
-        b.set(i, __builtin_fmin(e, key));
-        key = hi;
-        __builtin_amdgcn_sched_barrier(0);
-    }
 }
 
 // Leaf lists longer than this (and up to sort_max) are put in r_low order in
