@@ -737,7 +737,7 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // query per lane and the entries broadcast in windows of 16, each window waited
 // for its Node records and retested what the tile had no room for, and single
 // waves with 8300 reachable boxes and no needed one took the whole 1.4 ms of
-// the kernel at 10^6 clustered points, k = 8 (now 0.67 ms; 2^24 points, k = 16:
+// the kernel at 10^6 clustered points, k = 8 (then 0.67 ms; 2^24 points, k = 16:
 // 7.48 -> 7.42 ms; 2^21 uniform points, k = 30: 1.69 -> 1.58 ms).
 //
 // Which of the tile's points may belong to a query's list is decided on the
@@ -756,7 +756,9 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // costs one matrix instruction and four shifts per 16 x 16 pairs: at 2^24
 // clustered points and k = 16 the kernel issues 4.3e9 vector instructions
 // instead of 6.1e9 and takes 9.5 ms instead of 10.6; 2^21 uniform points,
-// k = 30: 1.95 ms instead of 2.85.
+// k = 30: 1.95 ms instead of 2.85. (With the own leaf first, the queue, the
+// sorts and the box tests as they are below: 7.0 ms, about 80 % of the vector
+// unit's cycles.)
 // Hits are queued as tile positions and inserted into the register top-k in
 // rounds, so insert time follows the busiest lane rather than every accepted
 // candidate of any lane.
