@@ -77,7 +77,9 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_init(
             far[hf] = __builtin_amdgcn_alignbit(far[hf], __float_as_uint(bb - dd), 31);
         }
     }
-    uint64_t adj = ~((uint64_t)far[1] << 32 | far[0]) & (~0ull >> (64 - acount));
+    // (b^2 beyond the float range: every distance, infinite ones too, is within it)
+    uint64_t adj = bb < INFINITY ? ~((uint64_t)far[1] << 32 | far[0]) : ~0ull;
+    adj &= ~0ull >> (64 - acount);
     if (!act) adj = 0;
     // components: from the lowest point not yet in one, the links of all its
     // members are added until nothing changes

@@ -70,3 +70,15 @@ def test_fof_dense_lists(jz, leaf_max, alpha):
         b = inputs.linking_length(n, alpha)
         with jz.jz_build(torch.from_numpy(p).cuda(), jz.default_opts(leaf_max=leaf_max)) as t:
             assert np.array_equal(t.fof(b).cpu().numpy(), oracle.fof_kd(p, b)), n
+
+
+@pytest.mark.parametrize("b", [1e18, 3e19])
+def test_fof_infinite_distances(jz, b):
+    """Pairs at infinite float32 distance inside one leaf, with b^2 finite and
+    beyond the float range."""
+    import torch
+    p = inputs.uniform(40, 800)
+    p[::2, 0] += np.float32(3e38)
+    p[1::2, 0] -= np.float32(3e38)
+    with jz.jz_build(torch.from_numpy(p).cuda()) as t:
+        assert np.array_equal(t.fof(b).cpu().numpy(), oracle.fof_bf(p, b))
