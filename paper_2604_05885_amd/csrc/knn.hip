@@ -37,12 +37,18 @@ __device__ __forceinline__ uint64_t list_key(int2 e) {
 // Lists longer than a wave can sort in its LDS scratch are put in order in
 // HBM before they are walked: k_find_long collects the receivers whose list
 // length lies in (min_len, mid] and in (mid, max_len], and k_sort_lists
-// sorts each such list in place in LDS, one workgroup per list: one wave for
-// lists of at most SORT_MID entries, SORT_WAVES waves for longer ones (up to
-// SORT_MAX).
+// sorts each such list in place in LDS, one workgroup per list: SORT_MID_WAVES
+// waves for lists of at most SORT_MID entries, SORT_WAVES for longer ones (up to
+// SORT_MAX). There are rarely more than a few hundred such lists, so one list's
+// steps are what a launch takes: with one wave (49 us) and eight (81 us) the walk
+// with its sorts took 0.46 ms at 10^6 clustered points, k = 32, now 0.39; 0.80 at
+// 4 10^6 periodic ones, now 0.67; 0.19 at 3 10^5, now 0.16. (Sixteen for both, in
+// one launch, is as fast there but loses 1 % of a call where a forest has
+// thousands of the shorter lists.)
 constexpr int SORT_MID = 1024;
+constexpr int SORT_MID_WAVES = 8;
 constexpr int SORT_MAX = 8192;
-constexpr int SORT_WAVES = 8;
+constexpr int SORT_WAVES = 16;
 
 __global__ __launch_bounds__(64) void k_find_long(const int2 *__restrict__ seg, int n,
                                                   int min_len, int mid, int max_len,
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(64 * NW) void k_sort_lists(int2 *__restrict__ list,
                         s[b] = x;
                     }
                 }
-                if (wide || NW == 1) __syncthreads();
+                if (wide) __syncthreads();
                 else wave_lds_sync();
             }
         }
@@ -1329,7 +1335,8 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
         k_find_long<<<(unsigned)((n + 63) / 64), 64, 0, s>>>(seg, (int)n, min_len, mid, sort_max,
                                                              ids_a, count, ids_b, count + 1);
         if (mid > min_len)
-            k_sort_lists<SORT_MID, 1><<<4096, 64, 0, s>>>(list, seg, ids_a, count);
+            k_sort_lists<SORT_MID, SORT_MID_WAVES><<<1024, 64 * SORT_MID_WAVES, 0, s>>>(list, seg, ids_a,
+                                                                               count);
         if (sort_max > mid)
             k_sort_lists<SORT_MAX, SORT_WAVES><<<512, 64 * SORT_WAVES, 0, s>>>(list, seg, ids_b,
                                                                               count + 1);

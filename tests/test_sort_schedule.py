@@ -58,3 +58,8 @@ def test_schedule_sorts(M):
             s[a] = np.where(swap, y, x)
             s[b] = np.where(swap, x, y)
         assert np.array_equal(s, want)
+
+
+@pytest.mark.parametrize("M", [32, 64, 1024, 2048, 8192])
+def test_wave_local_steps_of_16_waves(M):
+    test_wave_local_steps_stay_in_their_range(M, 16)
