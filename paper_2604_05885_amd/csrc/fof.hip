@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_init(
     int *__restrict__ minidx, unsigned long long *__restrict__ ctr, int nctr, float L) {
     const float Lh = 0.5f * L;
     __shared__ float4 s_tile[WPB][64];
-    for (int i = blk_x() * (64 * WPB) + tid_x(); i < nctr; i += nblk_x() * (64 * WPB)) ctr[i] = 0;
+    grid_stride(blk_x(), 64 * WPB, nblk_x(), tid_x(), nctr, [&](size_t i) { ctr[i] = 0; });
     const int w = WPB == 1 ? 0 : uni((int)(tid_x() >> 6)), lane = tid_x() & 63;
     const int A = xcd_block(blk_x(), nblk_x()) * WPB + w;
     if (A >= n_leaves) return;

@@ -205,6 +205,16 @@ __device__ __forceinline__ unsigned nblk_x() {
     return ((hidden_u32 *)__builtin_amdgcn_implicitarg_ptr())[0];
 }
 
+// What work item `item` of workgroup `blk` (nblk workgroups of `size` items)
+// does of n things dealt out over the grid: f(i) for its i. In 64 bits: a grid
+// of one wave per leaf has 2^31 work items from 2^25 leaves on (leaves of one
+// point), and may have up to 2^32 - 64.
+template <class F>
+__host__ __device__ __forceinline__ void grid_stride(unsigned blk, unsigned size, unsigned nblk,
+                                                     unsigned item, size_t n, F &&f) {
+    for (size_t i = (size_t)blk * size + item; i < n; i += (size_t)nblk * size) f(i);
+}
+
 // ---------------------------------------------------------------------------
 // wave64 primitives
 
