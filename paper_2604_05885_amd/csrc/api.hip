@@ -77,9 +77,7 @@ int64_t initial_cap(const jz_tree *t, int op, int k, int level) {
 // Caching device pool. Freed blocks keep an event recorded on the stream that
 // last used them; a block is handed to a different stream only after that
 // event has completed, so stream order protects every reuse. A block freed
-// while its stream has no work left (at the end of every call, which has waited
-// for it) needs none: creating, recording and destroying the events of some 25
-// blocks took 50 us of a call of 240.
+// after its call has waited for the stream needs none (CallScope).
 
 namespace {
 
@@ -132,6 +130,14 @@ void release_all(Pool &P) {
 
 }  // namespace
 
+static thread_local CallScope *g_scope = nullptr;
+
+CallScope::CallScope(jz_tree *tree) : outer(g_scope), t(tree) { g_scope = this; }
+CallScope::~CallScope() {
+    g_scope = outer;
+    if (t && !settled) t->unsettled = true;
+}
+
 void *dev_alloc(const AllocCtx &a, size_t bytes, hipStream_t s) {
     if (a.user) return a.ua.alloc(a.ua.ctx, bytes, (void *)s);
     Pool &P = pool(a.device);
@@ -182,9 +188,7 @@ void dev_free(const AllocCtx &a, void *p, size_t bytes, hipStream_t s) {
     }
     Pool &P = pool(a.device);
     hipEvent_t ev = nullptr;
-    const hipError_t idle = hipStreamQuery(s);
-    if (idle != hipSuccess) (void)hipGetLastError();
-    if (idle == hipSuccess) {
+    if (g_scope && g_scope->settled) {
         // nothing to wait for
     } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
         if (hipEventRecord(ev, s) != hipSuccess) {
@@ -338,6 +342,14 @@ jz_status check_opts(const jz_build_opts &o) {
     return JZ_OK;
 }
 
+// (every call on the tree has waited for its work, unless one failed)
+void tree_delete(jz_tree *t) {
+    if (!t) return;
+    CallScope scope;
+    if (!t->unsettled) (void)scope.done();
+    delete t;
+}
+
 jz_status tree_create(const float *points, const int64_t *offsets, int nsets, hipStream_t s,
                       const jz_build_opts *opts, const jz_allocator *alloc, jz_tree **out) {
     return make_tree_impl(points, offsets, nsets, offsets[nsets], (void *)s, opts, alloc, out);
@@ -387,7 +399,7 @@ jz_status make_tree_impl(const float *points, const int64_t *offsets, int nsets,
     if (st == JZ_OK) st = build_tree(t, points, s);
     if (st != JZ_OK) {
         (void)hipStreamSynchronize(s);
-        delete t;
+        tree_delete(t);
         return st;
     }
     t->st.n = n;
@@ -456,6 +468,7 @@ jz_status jz_build_joint(const float *sources, int64_t n_src, const float *queri
         ac.user = true;
         ac.ua = *alloc;
     }
+    CallScope scope;
     // one array over both types: sources first, then queries
     DBuf cat;
     JZ_TRY(cat.get(&ac, (size_t)n * 3 * sizeof(float), s));
@@ -475,10 +488,12 @@ jz_status jz_build_joint(const float *sources, int64_t n_src, const float *queri
         if (e != hipSuccess) st = jz_hip_fail(e, "hipStreamSynchronize", __FILE__, __LINE__);
     }
     if (st != JZ_OK) {
-        delete t;
+        t->unsettled = true;
+        tree_delete(t);
         *out = nullptr;
+        return st;
     }
-    return st;
+    return scope.done();
 }
 
 jz_status jz_knn_query(jz_tree *t, int k, int32_t *idx, float *dist2, void *stream) {
@@ -601,7 +616,7 @@ jz_status jz_forest_fof(jz_tree *t, const float *b, int32_t *label, void *stream
 void jz_tree_free(jz_tree *t) {
     if (!t) return;
     DeviceGuard g(t->ac.device);
-    delete t;
+    tree_delete(t);
 }
 
 int64_t jz_tree_size(const jz_tree *t) {

@@ -1131,6 +1131,7 @@ static jz_status top_lists(jz_tree *t, const uint64_t *keys, int bits3, hipStrea
 static jz_status build_small(jz_tree *t, const float *points, int bits, hipStream_t s) {
     const AllocCtx *ac = &t->ac;
     const int64_t n = t->n;
+    CallScope scope;
     DBuf d_hdr;
     JZ_TRY(d_hdr.get(ac, 8 * sizeof(int), s));
     JZ_TRY(t->pts4.get(ac, n * sizeof(float4), s));
@@ -1149,7 +1150,7 @@ static jz_status build_small(jz_tree *t, const float *points, int bits, hipStrea
     JZ_TRY(top_lists(t, nullptr, 0, s));
     JZ_HIP(hipStreamSynchronize(s));
     set_stats(t);
-    return JZ_OK;
+    return scope.done();
 }
 
 jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
@@ -1186,6 +1187,7 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
 
     // 1-2: bbox, keys, histograms. d_meta: bounding box and non-finite flag
     // (8 words), then the number of splits of every plane
+    CallScope scope;
     DBuf d_meta, k0, k1, v0, v1;
     SortScratch sc;
     JZ_TRY(d_meta.get(ac, (8 + JZ_MAX_PLANES + 2) * sizeof(int), s));
@@ -1272,6 +1274,7 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
 
     // 6-7: node sizes at leaf splits, coarser planes
     if (P > 1) {
+        CallScope planes;
         DBuf d_nsz, d_slv, lsiA, lsiB;
         JZ_TRY(d_nsz.get(ac, m0 * sizeof(int), s));
         JZ_TRY(d_slv.get(ac, m0, s));
@@ -1305,6 +1308,7 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
         JZ_HIP(hipGetLastError());
         JZ_TRY(meta.read(cnts, P * sizeof(int), s));
         for (int p = 0; p < P; ++p) t->L[p] = hm[p] - 1;
+        (void)planes.done();  // (the read has waited for them)
     }
     t->P = P;
 
@@ -1329,5 +1333,5 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
     JZ_HIP(hipStreamSynchronize(s));
 
     set_stats(t);
-    return JZ_OK;
+    return scope.done();
 }

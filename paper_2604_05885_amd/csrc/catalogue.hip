@@ -307,6 +307,7 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     } restore{prev, t->ac.device};
     if (prev != t->ac.device) JZ_HIP(hipSetDevice(t->ac.device));
     const AllocCtx *ac = &t->ac;
+    CallScope scope(t);
 
     // group labels (input order)
     DBuf d_label;
@@ -349,6 +350,7 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     JZ_TRY(total.read(d_total.p, sizeof(long long), s));
     const long long G = *total.as<long long>();
     *ngroups = G;
+    if (G > max_groups || G == 0) (void)scope.done();
     if (G > max_groups)
         return jz_fail(JZ_E_CAPACITY, "%lld groups have at least %d members; groups holds %lld",
                        G, min_members, (long long)max_groups);
@@ -370,5 +372,5 @@ extern "C" JZ_API jz_status jz_fof_catalogue(jz_tree *t, float b, int min_member
     }
     JZ_HIP(hipGetLastError());
     JZ_HIP(hipStreamSynchronize(s));
-    return JZ_OK;
+    return scope.done();
 }

@@ -681,6 +681,7 @@ __global__ void k_labels(const int *__restrict__ uf, const float4 *__restrict__ 
 
 jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStream_t s,
                   jz_stats *st_out) {
+    CallScope scope(t);
     jz_stats &st = st_out ? *st_out : t->st;
     const AllocCtx *ac = &t->ac;
     const int P = t->P;
@@ -693,7 +694,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
     st.insert_rounds = st.tile_steps = 0;
     st.lists_sorted_long = st.lists_unordered = 0;
     for (int p = 0; p <= JZ_MAX_PLANES; ++p) st.lists_presorted[p][0] = st.lists_presorted[p][1] = 0;
-    if (n == 0) return JZ_OK;
+    if (n == 0) return scope.done();
 
     const bool sets = t->nsets > 1;
     const float b2 = b2_set_host[0];
@@ -806,6 +807,6 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             JZ_HIP(hipEventElapsedTime(&ms, ev[0], ev[3]));
             st.total_ms = ms;
         }
-        return JZ_OK;
+        return scope.done();
     }
 }

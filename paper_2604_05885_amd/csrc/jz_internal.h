@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -45,6 +46,29 @@ void dev_free(const AllocCtx &a, void *p, size_t bytes, hipStream_t s);
 // and drop their events (an event last recorded on a destroyed stream must
 // not be waited on).
 void pool_forget_stream(int device, hipStream_t s);
+
+struct jz_tree;
+
+// A stretch of a call on this thread, declared before the buffers it frees.
+// After done(), which follows a wait for the stream, the blocks freed until the
+// stretch ends have no work left on them and go to the pool without an event:
+// creating, recording and destroying those of some 25 blocks took 50 us of a
+// call of 240. (Asking the runtime with hipStreamQuery instead ends a capture:
+// one of the stream itself, and any in global mode.) A stretch that ends
+// without done() may leave work on `t`, which the tree remembers.
+struct CallScope {
+    CallScope *const outer;
+    jz_tree *const t;
+    bool settled = false;
+    explicit CallScope(jz_tree *tree = nullptr);
+    CallScope(const CallScope &) = delete;
+    CallScope &operator=(const CallScope &) = delete;
+    ~CallScope();
+    jz_status done() {
+        settled = true;
+        return JZ_OK;
+    }
+};
 
 // A device buffer owned by a tree or by one call.
 struct DBuf {
@@ -151,12 +175,17 @@ struct jz_tree {
     int64_t n_src = -1;
     DBuf src_cnt[JZ_MAX_PLANES];
 
+    std::atomic<bool> unsettled{false};  // a call failed with work perhaps under way
+
     jz_stats st{};
 };
 
 // create a tree over nsets sets (offsets: host, nsets + 1); on error *out is NULL
 jz_status tree_create(const float *points, const int64_t *offsets, int nsets, hipStream_t s,
                       const jz_build_opts *opts, const jz_allocator *alloc, jz_tree **out);
+
+// free a tree (NULL is ignored) and its device memory
+void tree_delete(jz_tree *t);
 
 // pipelines (build.hip / knn.hip / fof.hip)
 jz_status build_tree(jz_tree *t, const float *points, hipStream_t s);

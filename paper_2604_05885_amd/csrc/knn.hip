@@ -1266,6 +1266,7 @@ jz_status zero_words(unsigned long long *p, size_t n, hipStream_t s) {
 
 jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                   const AllocCtx *scratch) {
+    CallScope scope(t);
     const AllocCtx *ac = scratch ? scratch : &t->ac;
     const int P = t->P;
     // a joint tree of source and query points: rows are the query points
@@ -1281,7 +1282,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
     t->st.insert_rounds = t->st.tile_steps = 0;
     t->st.lists_sorted_long = t->st.lists_unordered = 0;
     for (int p = 0; p <= JZ_MAX_PLANES; ++p) t->st.lists_presorted[p][0] = t->st.lists_presorted[p][1] = 0;
-    if (t->n == 0) return JZ_OK;
+    if (t->n == 0) return scope.done();
 
     // counters: four leaf statistics (evaluations, sources visited, insert
     // rounds, tile steps)
@@ -1454,6 +1455,6 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
             JZ_HIP(hipEventElapsedTime(&ms, ev[0], ev[2]));
             t->st.total_ms = ms;
         }
-        return JZ_OK;
+        return scope.done();
     }
 }

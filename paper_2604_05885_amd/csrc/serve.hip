@@ -99,6 +99,7 @@ namespace {
 
 // Solve one batch on stream s. All requests have the same op (and k).
 jz_status run_batch(jz_server *S, const std::vector<Req *> &batch, hipStream_t s) {
+    CallScope scope;
     const int nsets = (int)batch.size();
     const jz_request &h = batch[0]->r;
     AllocCtx ac;
@@ -175,7 +176,8 @@ jz_status run_batch(jz_server *S, const std::vector<Req *> &batch, hipStream_t s
     } else {
         (void)hipStreamSynchronize(s);
     }
-    delete t;
+    tree_delete(t);
+    if (st == JZ_OK) (void)scope.done();
     return st;
 }
 

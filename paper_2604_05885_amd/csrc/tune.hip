@@ -102,7 +102,7 @@ jz_status time_once(const float *points, const std::vector<int64_t> &off, int k,
     if (st == JZ_OK) st = tree_create(points, off.data(), (int)off.size() - 1, s, &o, nullptr, &t);
     if (st == JZ_OK && k > 0) st = run_knn(t, k, idx, d2, s);
     if (st == JZ_OK && !b2.empty()) st = run_fof(t, b2.data(), lab, s);
-    delete t;
+    tree_delete(t);
     if (st == JZ_OK && hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess) {
         float f = 0;
         (void)hipEventElapsedTime(&f, e0, e1);
