@@ -224,24 +224,28 @@ HostCache &host_cache() {
 }
 }  // namespace
 
-HostCopy::~HostCopy() {
-    if (!p) return;
+void HostCopy::release() {
+    void *const b = p;
+    p = nullptr;
+    cap = 0;
+    if (!b) return;
     if (!pinned) {
-        free(p);
+        free(b);
         return;
     }
     HostCache &c = host_cache();
     {
         std::lock_guard<std::mutex> lk(c.m);
         if (c.n < HOST_BLOCKS) {
-            c.block[c.n++] = p;
+            c.block[c.n++] = b;
             return;
         }
     }
-    if (hipHostFree(p) != hipSuccess) (void)hipGetLastError();
+    if (hipHostFree(b) != hipSuccess) (void)hipGetLastError();
 }
 
 jz_status HostCopy::read(const void *dev, size_t bytes, hipStream_t s) {
+    if (bytes > cap) release();
     if (!p && bytes <= HOST_BLOCK) {
         HostCache &c = host_cache();
         {
@@ -253,16 +257,20 @@ jz_status HostCopy::read(const void *dev, size_t bytes, hipStream_t s) {
             p = nullptr;
         }
         pinned = p != nullptr;
-    } else if (p && !(pinned && bytes <= HOST_BLOCK)) {
-        return jz_fail(JZ_E_DEVICE, "a host copy is read again with another size");
+        if (p) cap = HOST_BLOCK;
     }
-    if (!p) p = malloc(bytes);
-    if (!p) return jz_fail(JZ_E_OOM, "host allocation of %zu bytes failed", bytes);
+    if (!p) {
+        pinned = false;
+        p = malloc(bytes);
+        if (!p) return jz_fail(JZ_E_OOM, "host allocation of %zu bytes failed", bytes);
+        cap = bytes;
+    }
     hipError_t e = hipMemcpyAsync(p, dev, bytes, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         // the copy may still be under way: the block is not reused
         p = nullptr;
+        cap = 0;
         return jz_hip_fail(e, "reading device results", __FILE__, __LINE__);
     }
     return JZ_OK;

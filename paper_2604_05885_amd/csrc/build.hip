@@ -1307,6 +1307,7 @@ jz_status build_tree(jz_tree *t, const float *points, hipStream_t s) {
         }
         JZ_HIP(hipGetLastError());
         JZ_TRY(meta.read(cnts, P * sizeof(int), s));
+        hm = meta.as<int>();
         for (int p = 0; p < P; ++p) t->L[p] = hm[p] - 1;
         (void)planes.done();  // (the read has waited for them)
     }

@@ -117,18 +117,21 @@ struct DBuf {
 // A call's host copy of device results: a block of pinned memory from a small
 // cache (blocks of HOST_BLOCK bytes, at most HOST_BLOCKS kept, given back by
 // jz_release_cached), pageable memory where it is larger or none is to be had.
+// It may be read again, with any size (the copy's address may change then).
 // A copy to pageable memory went through the runtime's staging: 20 us before
 // and 20 after it, and the wait for the stream on top.
 constexpr size_t HOST_BLOCK = 64 << 10;
 constexpr int HOST_BLOCKS = 64;
 struct HostCopy {
     void *p = nullptr;
+    size_t cap = 0;
     bool pinned = false;
 
     HostCopy() = default;
     HostCopy(const HostCopy &) = delete;
     HostCopy &operator=(const HostCopy &) = delete;
-    ~HostCopy();
+    ~HostCopy() { release(); }
+    void release();
     // copy `bytes` from dev and wait for stream s
     jz_status read(const void *dev, size_t bytes, hipStream_t s);
     template <class T>
