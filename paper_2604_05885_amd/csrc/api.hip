@@ -252,7 +252,8 @@ jz_status HostCopy::read(const void *dev, size_t bytes, hipStream_t s) {
             std::lock_guard<std::mutex> lk(c.m);
             if (c.n > 0) p = c.block[--c.n];
         }
-        if (!p && hipHostMalloc(&p, HOST_BLOCK, hipHostMallocPortable) != hipSuccess) {
+        if (!p && fresh_pinned &&
+            hipHostMalloc(&p, HOST_BLOCK, hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             p = nullptr;
         }

@@ -118,6 +118,8 @@ struct DBuf {
 // cache (blocks of HOST_BLOCK bytes, at most HOST_BLOCKS kept, given back by
 // jz_release_cached), pageable memory where it is larger or none is to be had.
 // It may be read again, with any size (the copy's address may change then).
+// fresh_pinned = false, for a call that promises to allocate nothing: it takes a
+// block of the cache (the tree's build leaves one there) or pageable memory.
 // A copy to pageable memory went through the runtime's staging: 20 us before
 // and 20 after it, and the wait for the stream on top.
 constexpr size_t HOST_BLOCK = 64 << 10;
@@ -126,8 +128,9 @@ struct HostCopy {
     void *p = nullptr;
     size_t cap = 0;
     bool pinned = false;
+    const bool fresh_pinned;
 
-    HostCopy() = default;
+    explicit HostCopy(bool fresh = true) : fresh_pinned(fresh) {}
     HostCopy(const HostCopy &) = delete;
     HostCopy &operator=(const HostCopy &) = delete;
     ~HostCopy() { release(); }

@@ -1343,7 +1343,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
                                                                               count + 1);
     };
     EventSet ev(jz_profiling());
-    HostCopy host;  // the counters
+    HostCopy host(!scratch);  // the counters
 
     // Level p turns the list of plane p+1 (or of the super nodes) into the
     // list of plane p. On overflow, levels from the highest overflowing one
