@@ -353,7 +353,9 @@ typedef struct jz_stats {
     /* last jz_knn / jz_fof call on this tree */
     int64_t list_entries[JZ_MAX_PLANES + 1]; /* list entries produced per level (index p = plane p, P = super) */
     int64_t leaf_pairs;              /* leaf-leaf interactions in the leaf list */
-    int64_t leaf_pairs_visited;      /* of those, visited before the early exit */
+    int64_t leaf_pairs_visited;      /* of those, visited before the early exit (k > 32: in each pass;
+                                        in trees of up to 768 leaves, whose leaves several waves
+                                        share: by the first of them) */
     double evaluations;              /* point pairs whose distance the leaf stage tested (kNN: the
                                         pairs its matrix filter looked at) */
     double leaf_ms;                  /* leaf-stage kernel time (ms), when profiling is on */

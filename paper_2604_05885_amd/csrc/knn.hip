@@ -1202,7 +1202,8 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     if (lane == 0) {
         unsigned long long *st = stats + (A & (STAT_SLOTS - 1));
         atomicAdd(st + 0 * STAT_SLOTS, evals);
-        atomicAdd(st + 1 * STAT_SLOTS, (unsigned long long)visited);
+        // (a leaf that several waves share counts its pairs in the first)
+        if (part == 0) atomicAdd(st + 1 * STAT_SLOTS, (unsigned long long)visited);
         atomicAdd(st + 2 * STAT_SLOTS, (unsigned long long)rounds);
         atomicAdd(st + 3 * STAT_SLOTS, (unsigned long long)steps);
         if (len > LCAP && part == 0)
