@@ -49,7 +49,8 @@ typedef enum jz_status {
     JZ_E_INVALID = 1,      /* bad argument (null pointer, n out of range, k < 1, b < 0 or NaN) */
     JZ_E_NONFINITE = 2,    /* an input coordinate is NaN or infinite */
     JZ_E_UNSUPPORTED = 3,  /* k > JZ_MAX_K */
-    JZ_E_CAPACITY = 4,     /* interaction list overflow with auto_regrow = 0 */
+    JZ_E_CAPACITY = 4,     /* interaction list overflow with auto_regrow = 0, or a list of more
+                              than 2^31-1 entries */
     JZ_E_OOM = 5,          /* device allocation failed (jz_knn_fof: also host memory) */
     JZ_E_DEVICE = 6        /* a HIP runtime error */
 } jz_status;

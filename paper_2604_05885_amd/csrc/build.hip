@@ -1048,6 +1048,12 @@ static void set_stats(jz_tree *t) {
     t->st.super_nodes = t->S;
 }
 
+jz_status check_top(int64_t last) {
+    if (last <= INT32_MAX) return JZ_OK;
+    return jz_fail(JZ_E_CAPACITY, "the list of super node pairs has more than 2^31-1 entries; "
+                   "raise ngr or lower n_target");
+}
+
 // Super nodes over the top plane and their dense lists: made on the device for
 // a single set (no transfer), on the host for a forest, whose rows end at the
 // set boundaries. Waits for the stream where host arrays are read.
@@ -1058,6 +1064,8 @@ static jz_status top_lists(jz_tree *t, const uint64_t *keys, int bits3, hipStrea
     const int64_t LT = t->L[T];
     if (t->nsets == 1) {
         const int64_t S = t->S = (LT + o.ngr - 1) / o.ngr;
+        t->knn_top_last = S * (S - 1);
+        t->fof_top_last = (S - 1) * (S + 2) / 2;
         JZ_TRY(t->super_spl.get(ac, (S + 1) * sizeof(int), s));
         JZ_TRY(t->knn_top_seg.get(ac, S * sizeof(int2), s));
         JZ_TRY(t->knn_top_list.get(ac, S * S * sizeof(int2), s));
@@ -1101,6 +1109,8 @@ static jz_status top_lists(jz_tree *t, const uint64_t *keys, int bits3, hipStrea
         int64_t b = a;
         while (b < t->S && t->super_set[b] == t->super_set[a]) ++b;
         for (int64_t i = a; i < b; ++i) {
+            t->knn_top_last = (int64_t)klist.size();
+            t->fof_top_last = (int64_t)flist.size();
             kseg[i] = make_int2((int)klist.size(), (int)(b - a));
             for (int64_t j = a; j < b; ++j) klist.push_back(make_int2((int)j, 0));
             fseg[i] = make_int2((int)flist.size(), (int)(b - i));

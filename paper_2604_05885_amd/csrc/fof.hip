@@ -695,6 +695,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
     st.lists_sorted_long = st.lists_unordered = 0;
     for (int p = 0; p <= JZ_MAX_PLANES; ++p) st.lists_presorted[p][0] = st.lists_presorted[p][1] = 0;
     if (n == 0) return scope.done();
+    JZ_TRY(check_top(t->fof_top_last));
 
     const bool sets = t->nsets > 1;
     const float b2 = b2_set_host[0];

@@ -174,6 +174,9 @@ struct jz_tree {
     std::vector<int> super_set;      // host: set of each super node
     DBuf knn_top_seg, knn_top_list;  // dense super-node list (all pairs within a set)
     DBuf fof_top_seg, fof_top_list;  // dense super-node list (pairs s <= t within a set)
+    // where the last row of each list begins (a call needs it to fit the 32
+    // bits of a segment; the lists grow with the square of S)
+    int64_t knn_top_last = 0, fof_top_last = 0;
 
     // separate point types (jz_build_joint): points [0, n_src) are sources,
     // [n_src, n) queries; n_src = -1 otherwise. src_cnt[p][i]: source points
@@ -205,6 +208,8 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
 // run_fof writes its call statistics to `st_out` when given (else to t->st)
 jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStream_t s,
                   jz_stats *st_out = nullptr);
+// JZ_E_CAPACITY for a super-node list whose rows begin beyond 2^31 - 1
+jz_status check_top(int64_t last);
 // the ranges jz_build_opts documents (JZ_E_INVALID with a message otherwise)
 jz_status check_opts(const jz_build_opts &o);
 

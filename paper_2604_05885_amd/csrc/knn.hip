@@ -1284,6 +1284,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
     t->st.lists_sorted_long = t->st.lists_unordered = 0;
     for (int p = 0; p <= JZ_MAX_PLANES; ++p) t->st.lists_presorted[p][0] = t->st.lists_presorted[p][1] = 0;
     if (t->n == 0) return scope.done();
+    JZ_TRY(check_top(t->knn_top_last));
 
     // counters: four leaf statistics (evaluations, sources visited, insert
     // rounds, tile steps)
