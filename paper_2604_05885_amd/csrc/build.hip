@@ -173,7 +173,8 @@ __global__ __launch_bounds__(RS_THREADS, ITEMS <= 20 ? 3 : 2) void k_onesweep(
     uint64_t *__restrict__ status, int *__restrict__ tile_ctr) {
     constexpr int RS_TILE = RS_THREADS * ITEMS;
     __shared__ uint64_t s_k[RS_TILE];
-    __shared__ uint16_t s_wh[RS_WAVES][256];
+    __shared__ __align__(4) uint16_t s_wh[RS_WAVES][256];
+    static_assert(__alignof__(s_wh) >= alignof(uint32_t), "cleared in words of 32 bits");
     __shared__ uint32_t s_gb[256];  // a digit's first place, less its first in the tile
     uint32_t *s_v = reinterpret_cast<uint32_t *>(s_k);
     __shared__ int s_tmp[RS_WAVES], s_hist[RS_WAVES];
