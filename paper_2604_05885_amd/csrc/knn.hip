@@ -782,7 +782,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const int *__restrict__ leaf_base,
     int32_t *__restrict__ out_idx, float *__restrict__ out_d2,
     unsigned long long *__restrict__ stats, const unsigned long long *__restrict__ overflow,
-    int sort_cap, int presorted, int out_stride, int col0, int kw,
+    int presorted, int out_stride, int col0, int kw,
     const int *__restrict__ scnt0, int src_hi, int qry_lo, float Lp,
     const float *__restrict__ rleaf, const int *__restrict__ first,
     const unsigned long long *__restrict__ n_first, int first_len, int row_align, int lg_parts) {
@@ -1207,13 +1207,13 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
         atomicAdd(st + 2 * STAT_SLOTS, (unsigned long long)rounds);
         atomicAdd(st + 3 * STAT_SLOTS, (unsigned long long)steps);
         if (len > LCAP && part == 0)
-            atomicAdd(st + (len <= max(sort_cap, presorted) ? 4 : 5) * STAT_SLOTS, 1ull);
+            atomicAdd(st + (len <= presorted ? 4 : 5) * STAT_SLOTS, 1ull);
     }
 }
 
 typedef void (*leaf_fn)(const int2 *, const int2 *, const Node *, const float4 *, int, const int *,
                         int32_t *, float *, unsigned long long *, const unsigned long long *, int,
-                        int, int, int, int, const int *, int, int, float, const float *,
+                        int, int, int, const int *, int, int, float, const float *,
                         const int *, const unsigned long long *, int, int, int);
 
 template <int K, bool LO, bool PER>
@@ -1307,8 +1307,8 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
     // Lists longer than WALK_PRESORT in the walk and LEAF_PRESORT in the leaf
     // stage, up to sort_max, are sorted in HBM before their level.
     const int sort_max = t->opts.sort_max;
-    const int walk_cap = WALK_PRESORT, leaf_cap = std::min(sort_max, 1024);
-    const int first_len = t->L[0] > LEAF_MANY ? leaf_cap : LEAF_FIRST;
+    const int walk_cap = WALK_PRESORT;
+    const int first_len = t->L[0] > LEAF_MANY ? std::min(sort_max, 1024) : LEAF_FIRST;
     // work items of the walk (at most one per parent plus one per cb
     // children, or per WALK_CB_LONG children of a parent with a long list):
     // WALK_CB children per item at the leaf level, WALK_CB_UP
@@ -1402,7 +1402,7 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
             fn<<<blocks_for(n_waves, WPB) << lg_parts, 64 * WPB, 0, s>>>(
                 segs[0].as<int2>(), lists[0].as<int2>(), t->nodes[0].as<Node>(),
                 t->pts4.as<float4>(), (int)t->L[0], t->nsets > 1 ? t->leaf_base.as<int>() : nullptr,
-                idx, dist2, ctr + CTR_STATS, ctr + CTR_FLAG, leaf_cap, sort_max, k, col,
+                idx, dist2, ctr + CTR_STATS, ctr + CTR_FLAG, sort_max, k, col,
                 std::min(32, k - col), joint ? t->src_cnt[0].as<int>() : nullptr,
                 joint ? (int)t->n_src : INT_MAX, joint ? (int)t->n_src : 0, period,
                 d_rleaf.as<float>(), d_first.as<int>(), ctr + c_first, first_len, row_align, lg_parts);
