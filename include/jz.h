@@ -359,7 +359,9 @@ typedef struct jz_stats {
                                         share: by the first of them) */
     double evaluations;              /* point pairs whose distance the leaf stage tested (kNN: the
                                         pairs its matrix filter looked at) */
-    double leaf_ms;                  /* leaf-stage kernel time (ms), when profiling is on */
+    double leaf_ms;                  /* leaf-stage kernel time (ms), when profiling is on (FoF: with
+                                        the kernel that finds the links within leaves, which starts
+                                        the call) */
     double total_ms;                 /* whole call, device time (ms), when profiling is on */
     int reruns;                      /* capacity reruns in the last call */
     int64_t insert_rounds;           /* kNN leaf stage: wave-level top-k insert rounds */

@@ -739,6 +739,7 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             t->nodes[0].as<Node>(), t->pts4.as<float4>(), (int)t->L[0], b2,
             sets ? b2n[0].as<float>() : nullptr, whole[0].as<int>(), d_uf.as<int>(),
             d_min.as<int>(), ctr, (int)nctr, L);
+        if (ev.on) JZ_HIP(hipEventRecord(ev[4], s));
         for (int p = P - 1; p >= 0; --p) {
             const bool top = p == P - 1;
             const int2 *seg_in = top ? t->fof_top_seg.as<int2>() : segs[p + 1].as<int2>();
@@ -805,6 +806,8 @@ jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStrea
             float ms = 0;
             JZ_HIP(hipEventElapsedTime(&ms, ev[1], ev[2]));
             st.leaf_ms = ms;
+            JZ_HIP(hipEventElapsedTime(&ms, ev[0], ev[4]));
+            st.leaf_ms += ms;
             JZ_HIP(hipEventElapsedTime(&ms, ev[0], ev[3]));
             st.total_ms = ms;
         }

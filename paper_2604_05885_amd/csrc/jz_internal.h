@@ -235,7 +235,7 @@ int64_t initial_cap(const jz_tree *t, int op, int k, int level);
 // hipEvents for optional device timing; created only when profiling is on
 struct EventSet {
     bool on = false;
-    hipEvent_t e[4] = {};
+    hipEvent_t e[5] = {};
     explicit EventSet(bool want) {
         if (!want) return;
         on = true;
