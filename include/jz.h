@@ -86,9 +86,12 @@ typedef struct jz_build_opts {
                               list_per_node and return JZ_E_CAPACITY on overflow. */
     int keep_keys;         /* 1: keep the sorted Morton keys for jz_tree_export. Default 0. */
     int sort_max;          /* kNN: longest interaction list put in r_low order before it is
-                              walked (so the walk can stop at the first entry beyond its
-                              radius); longer lists are read unordered. Default 8192, range
-                              [256, 8192]. */
+                              read (lists of more than 512 entries in the walk and of more
+                              than 2048 in the leaf stage), so that its reader can stop at the
+                              first entries beyond its radius. Longer lists are read to their
+                              end; the leaf stage orders each slice of up to 256 entries within
+                              its radius itself, as it does with shorter lists. Default 8192,
+                              range [256, 8192]. */
     float period;          /* > 0: the points lie in the periodic cube [0, period)^3 (coordinates
                               outside it: JZ_E_INVALID) and kNN / FoF use the minimum-image
                               distance: each coordinate difference dx = fl(x_i - x_j) becomes
@@ -352,13 +355,15 @@ typedef struct jz_stats {
     int64_t nodes[JZ_MAX_PLANES];    /* nodes per plane (plane 0 = leaves) */
     int64_t super_nodes;             /* super nodes over the top plane */
     /* last jz_knn / jz_fof call on this tree */
-    int64_t list_entries[JZ_MAX_PLANES + 1]; /* list entries produced per level (index p = plane p, P = super) */
-    int64_t leaf_pairs;              /* leaf-leaf interactions in the leaf list */
+    int64_t list_entries[JZ_MAX_PLANES + 1]; /* list entries reserved per level (index p = plane p, P = super).
+                                        FoF reserves for every pair within reach, and leaves out
+                                        those it finds in one group already */
+    int64_t leaf_pairs;              /* the same at the leaf level: leaf-leaf interactions */
     int64_t leaf_pairs_visited;      /* of those, visited before the early exit (k > 32: in each pass;
                                         in trees of up to 768 leaves, whose leaves several waves
                                         share: by the first of them) */
-    double evaluations;              /* point pairs whose distance the leaf stage tested (kNN: the
-                                        pairs its matrix filter looked at) */
+    double evaluations;              /* point pairs whose distance the leaf stage tested (on the
+                                        matrix unit or exactly, pairs within a leaf included) */
     double leaf_ms;                  /* leaf-stage kernel time (ms), when profiling is on (FoF: with
                                         the kernel that finds the links within leaves, which starts
                                         the call) */
@@ -410,8 +415,10 @@ JZ_API void jz_set_profiling(int on);
 JZ_API jz_status jz_tree_export(const jz_tree *t, int32_t *order, uint64_t *keys, int plane,
                          int32_t *spl);
 
-/* Return the library's cached (currently unused) device memory to the
- * runtime. Trees keep their own memory until jz_tree_free. */
+/* Return the library's cached (currently unused) memory to the runtime: the
+ * current device's blocks, and the pinned host blocks (at most 64 of 64 KiB)
+ * that calls read their counters into. Trees keep their own memory until
+ * jz_tree_free. */
 JZ_API void jz_release_cached(void);
 
 /* Thread-local message of the last error (empty string if none). */

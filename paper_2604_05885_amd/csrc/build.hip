@@ -161,9 +161,10 @@ __device__ __forceinline__ void st_u64(uint64_t *p, uint64_t v) {
 // tile in LDS in digit order and writes it out with coalesced runs, keys first
 // and then values through the same LDS. What bounds it is the writes, a run of
 // tile / 256 keys per digit that begins and ends within a line another tile
-// writes too: longer tiles are faster though fewer fit (2^24 keys: 147 us with
-// 6144 keys, staged at once, 140 with 8192, 149 with 5120, three per CU; the 0.4
-// GB of a pass would take 85 at the rate of a copy). `hist`: the
+// writes too: longer tiles are faster though fewer fit (2^24 keys: 138 us with
+// 8192 keys, 147 with 5120, three per CU; tiles of 6144, keys and values staged
+// at once, took 5 % longer than 8192; the 0.4 GB of a pass would take 85 us at
+// the rate of a copy). `hist`: the
 // pass's 256 digit counts over all keys, whose exclusive scan every tile takes
 // for itself (a launch of its own took as long as a small pass).
 template <int ITEMS>

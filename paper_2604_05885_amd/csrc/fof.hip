@@ -41,8 +41,10 @@ constexpr int WHOLE_WALK = 1, WHOLE_OWN = 2;
 // to the receiving leaf one after another, 2 us each, and the slowest waves set
 // the leaf kernel's length (clustered, alpha = 0.2: 0.14 ms at 5 10^4 points,
 // 0.23 at 10^6, 1.65 at 2^24; now 0.09, 0.15 and 1.28). At 2^24 points this
-// kernel takes 0.33 ms, 64 distances a point on the vector unit; its 0.4 GB of
-// traffic would take 0.09. A search from member to member, which ends early in a
+// kernel takes 0.33 ms, 64 distances a point on the vector unit, most of which
+// the leaf kernel spent before; the whole FoF call went from 0.193 to 0.143 ms,
+// from 0.57 to 0.50 and from 2.58 to 2.47. Its 0.4 GB of traffic would take
+// 0.09. A search from member to member, which ends early in a
 // dense leaf, took 0.59: a chain of scalar steps per point. Leaving out leaves
 // whose box is within b gains nothing.
 template <bool PER>
@@ -138,9 +140,11 @@ __global__ __launch_bounds__(64 * WPB) void k_fof_p2n(const int *__restrict__ pa
 
 // Node walk step: one wave per work item, a receiving parent and up to CB of
 // its children (item I: parent I / nsub, its children from CB (I % nsub) on,
-// in strides of CB nsub). The receivers' boxes sit in scalar
-// registers, the source children go through the lanes, 64 node records at a
-// time, their indices expanded into LDS.
+// in strides of CB nsub). The receivers' boxes are uniform, in scalar registers
+// as far as those go (some 60 words of CB = 4 and 165 of CB = 8 are read back
+// from lanes of vector registers, one instruction each); the source children go
+// through the lanes, 64 node records at a time, their indices expanded into
+// LDS.
 //   phase 0  links (d_up^2 <= b^2: union of the first points, both nodes become
 //            whole), and counts the pairs that geometry alone sends down
 //            (within reach, not wholly within b)
@@ -533,9 +537,9 @@ __global__ __launch_bounds__(64 * WPB, 6) void k_leaf_fof(
     }
 
     for (int t0 = 0, lim; t0 < len; t0 = lim) {
-        // up to 64 sources, one per lane; a whole leaf takes 1, 1, 2, 4, ... at
-        // a time, one of many sources 16, 32, 64, ..., since the first ones
-        // join it to most of the others
+        // up to 64 sources, one per lane; a whole leaf takes 1, 2, 4, ... at a
+        // time, one of more than 64 sources 16, 32, 64, ..., since the first
+        // ones join it to most of the others
         lim = min(t0 + (wA || len > 64 ? min(t0 + (wA ? 1 : 16), 64) : 64), len);
         int e_st = 0, e_ct = 0, e_wh = 0, e_rt = -2;
         float4 e_lo = make_float4(0, 0, 0, 0), e_hi = e_lo;

@@ -413,9 +413,10 @@ __device__ __forceinline__ void st_rel(int *p, int v) {
 // the higher root to the lower one with compare-and-swap, retry on failure).
 // Invariant: par[x] <= x, so the forest has no cycles and a root is the
 // smallest z-index of its group.
-// Parent pointers are read through this CU's and this XCD's caches (device-scope reads go past the per-XCD L2 to memory): a read
-// may return an older value, never a wrong one, because a parent only ever
-// moves to an ancestor. An older parent is still an ancestor, an older root
+// Parent pointers are read through this CU's and this XCD's caches
+// (device-scope reads go past the per-XCD L2 to memory): a read may return an
+// older value, never a wrong one, because a parent only ever moves to an
+// ancestor. An older parent is still an ancestor, an older root
 // is still a member of the group, and equal roots, however old, mean one
 // group (groups only merge). Every write stays device-coherent: the
 // path-halving store puts an ancestor (found from possibly older reads) into

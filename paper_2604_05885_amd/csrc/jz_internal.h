@@ -257,7 +257,7 @@ struct EventSet {
 constexpr int STAT_SLOTS = 256;
 // Interaction-list space of a level is split into LIST_ARENAS arenas, each
 // with its own fill counter: a wave reserves its segment in arena
-// (receiver parent % LIST_ARENAS), which spreads the reservation atomics.
+// (work item % LIST_ARENAS), which spreads the reservation atomics.
 constexpr int LIST_ARENAS = 64;
 constexpr int CTR_FLAG = JZ_MAX_PLANES * LIST_ARENAS;
 constexpr int CTR_STATS = CTR_FLAG + 8;

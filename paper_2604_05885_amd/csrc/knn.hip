@@ -2,7 +2,8 @@
 // Eq. 14-16, and the implementation-details subsection on r_low ordering).
 //
 // Level step (one wave per work item: a receiving parent and up to 4 of its
-// children in scalar registers; lanes = the children of the parent's sources):
+// children, the same for every lane; lanes = the children of the parent's
+// sources):
 //   FindRmax: R = smallest radius whose cumulative count reaches k (Alg. 3)
 //   count children pairs with d_low^2 <= R
 //   insert them (with r_low = d_low^2) into the next list, at an offset
@@ -190,8 +191,10 @@ constexpr int FCAP = 1024;  // source children listed in LDS at a time
 constexpr int WALK_PRESORT = 512;
 
 // Level step of the kNN walk: one wave per work item, a receiving parent P and
-// up to WALK_CB of its children. The children's boxes sit in scalar registers;
-// the source children go through the lanes, 64 node records at a time.
+// up to WALK_CB of its children. The children's boxes are uniform, in scalar
+// registers (38 of these do not fit and are read back from a lane of a vector
+// register, one instruction each); the source children go through the lanes,
+// 64 node records at a time.
 //   phase 0  FindRmax: every lane keeps, per receiving child, the two smallest
 //            (d_up^2, count) it has met; the smallest of them over the wave are
 //            added up until the count reaches k (Alg. 3; leaving any out keeps
@@ -763,8 +766,10 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // clustered points and k = 16 the kernel issues 4.3e9 vector instructions
 // instead of 6.1e9 and takes 9.5 ms instead of 10.6; 2^21 uniform points,
 // k = 30: 1.95 ms instead of 2.85. (With the own leaf first, the queue, the
-// sorts and the box tests as they are below: 7.0 ms, about 80 % of the vector
-// unit's cycles.)
+// sorts and the box tests as they are below: 7.0 ms. Its 3.56e9 vector
+// instructions would take 81 % of that at one per 4 cycles and SIMD, a rate that
+// plain float code exceeds; for a third of their time the waves wait to issue
+// an instruction.)
 // Hits are queued as tile positions and inserted into the register top-k in
 // rounds, so insert time follows the busiest lane rather than every accepted
 // candidate of any lane.
@@ -775,6 +780,22 @@ __device__ __forceinline__ void dense_words(const float4 *tp, int m, int W, int 
 // back from column col0 - 1 of the output row), so that equal distances
 // continue by index. A pass writes columns [col0, col0 + kw) of rows of
 // out_stride entries.
+//
+// Waves per SIMD: 4 up to K = 16, 3 above, at 128 and 168 registers. Towards
+// the upper end of both ranges registers spill (open from K = 13 and 27 on, 9 at
+// K = 16 and 7 at 32; periodic from 9 and 23 on, 34 and 11), but one wave fewer,
+// without spills, is slower or the same, and with no bound most kernels run two
+// (ms of the leaf stage, as it is / one wave fewer / no bound):
+//   2^24 clustered points, k = 16        6.94 / 7.41 / 9.88
+//   2^21 uniform, k = 30                 1.50 / 1.72 / 1.75
+//   10^6 clustered, k = 8                0.39 / 0.42 / 0.43
+//   k = 24                               0.68 / 0.68 / 0.83
+//   k = 32                               0.84 / 0.93 / 0.95
+//   k = 64                               1.99 / 2.20 / 2.22
+//   4 10^6 periodic, k = 16              2.36 / 2.36 / 3.00
+//   10^6 periodic, k = 8                 0.52 / 0.54 / 0.68
+//   k = 32                               1.09 / 1.18 / 1.93
+//   k = 64                               2.53 / 2.76 / 3.61
 template <int K, bool LO, bool PER>
 __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const int2 *__restrict__ seg, const int2 *__restrict__ list,
@@ -790,8 +811,7 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
     const float Lh = 0.5f * Lp;
     // one block per wave: the staged list (LCAP entries), the point tile
     // (x, y, z and the filter's w), the points' indices and the candidate
-    // queues; before the walk the whole block is the scratch in which a
-    // longer list is sorted
+    // queues
     constexpr int O_TILE = LCAP, O_IDX = O_TILE + (FILLER + 1) * 2, O_Q = O_IDX + (FILLER + 1) / 2;
     constexpr int RAW = O_Q + CQ * 64 / 8;
     __shared__ __align__(16) uint64_t s_raw[WPB][RAW];
@@ -1007,147 +1027,150 @@ __global__ __launch_bounds__(64 * WPB, K <= 16 ? 4 : 3) void k_leaf_knn(
             tidx[FILLER] = -1;
         }
         wave_lds_sync();
-    // The slice in chunks of 64 entries, one per lane, each staged in batches
-    // of what fits the tile. The nearest batch runs unseen; before the others,
-    // with the radii it leaves, every lane tests its entry's box against all
-    // queries, and the entries that no query reaches are dropped.
-    for (int c0 = 0; c0 < nl; c0 += 64) {
-        uint64_t pend = nl - c0 >= 64 ? ~0ull : (1ull << (nl - c0)) - 1ull;
-        float4 n_lo = make_float4(0, 0, 0, 0), n_hi = n_lo;  // the entry's Node record
-        float e_rl = INFINITY;
-        int e_sc = 0;
-        if (lane < nl - c0) {
-            const uint64_t e = L[c0 + lane];
-            const int src = (int)(uint32_t)e;
-            e_rl = __uint_as_float((uint32_t)(e >> 32));
-            const float4 *rec = reinterpret_cast<const float4 *>(leaves + src);
-            n_lo = rec[0];
-            n_hi = rec[1];
-            e_sc = types ? scnt0[src] : __float_as_int(n_hi.w);
-        }
-        bool tested = false;
-        while (pend) {
-        float kth = group_kth();
-        pend &= __ballot(e_rl <= uni(wave_max_f(act ? kth : -INFINITY)));
-        if (!fresh && !tested && pend) {
-            // A query whose k-th distance is below every r_low of the chunk
-            // needs none of it: of the thousands of boxes that one far query
-            // brings within the leaf's radius, the others look at none (leaf
-            // stage of 10^6 clustered points, k = 8: 0.57 ms with every query
-            // looking at every box, 0.40 ms).
-            const float rl0 = uni(wave_min((pend >> lane) & 1ull ? e_rl : INFINITY));
-            const uint64_t qm = __ballot(h == 0 && act && kth >= rl0);
-            if ((qm >> lane) & 1ull)
-                tile[__popcll(qm & lanemask_lt())] = make_float4(me.x, me.y, me.z, kth);
-            wave_lds_sync();
-            bool need = false;
-            const int nq_near = (int)__popcll(qm);
+        // The slice in chunks of 64 entries, one per lane, each staged in batches
+        // of what fits the tile. The nearest batch runs unseen; before the others,
+        // with the radii it leaves, every lane tests its entry's box against all
+        // queries, and the entries that no query reaches are dropped.
+        for (int c0 = 0; c0 < nl; c0 += 64) {
+            uint64_t pend = nl - c0 >= 64 ? ~0ull : (1ull << (nl - c0)) - 1ull;
+            float4 n_lo = make_float4(0, 0, 0, 0), n_hi = n_lo;  // the entry's Node record
+            float e_rl = INFINITY;
+            int e_sc = 0;
+            if (lane < nl - c0) {
+                const uint64_t e = L[c0 + lane];
+                const int src = (int)(uint32_t)e;
+                e_rl = __uint_as_float((uint32_t)(e >> 32));
+                const float4 *rec = reinterpret_cast<const float4 *>(leaves + src);
+                n_lo = rec[0];
+                n_hi = rec[1];
+                e_sc = types ? scnt0[src] : __float_as_int(n_hi.w);
+            }
+            bool tested = false;
+            while (pend) {
+                float kth = group_kth();
+                pend &= __ballot(e_rl <= uni(wave_max_f(act ? kth : -INFINITY)));
+                if (!fresh && !tested && pend) {
+                    // A query whose k-th distance is below every r_low of the chunk
+                    // needs none of it: of the thousands of boxes that one far query
+                    // brings within the leaf's radius, the others look at none (leaf
+                    // stage of 10^6 clustered points, k = 8: 0.57 ms with every query
+                    // looking at every box, 0.40 ms).
+                    const float rl0 = uni(wave_min((pend >> lane) & 1ull ? e_rl : INFINITY));
+                    const uint64_t qm = __ballot(h == 0 && act && kth >= rl0);
+                    if ((qm >> lane) & 1ull)
+                        tile[__popcll(qm & lanemask_lt())] = make_float4(me.x, me.y, me.z, kth);
+                    wave_lds_sync();
+                    bool need = false;
+                    const int nq_near = (int)__popcll(qm);
 #pragma unroll 4
-            for (int i = 0; i < nq_near; ++i) {
-                const float4 p = tile[i];
-                need |= point_low2_m<PER>(p.x, p.y, p.z, n_lo.x, n_lo.y, n_lo.z, n_hi.x, n_hi.y,
-                                          n_hi.z, Lp) <= p.w;
-            }
-            pend &= __ballot(need);
-            tested = true;
-            wave_lds_sync();
-        }
-        fresh = false;
-        // take entries in order while their points fit the tile: position f
-        // of the tile is point f + delta, delta changing with the source
-        // (several loads per lane in flight; separate point types need the
-        // packing of each leaf's source points and go source by source)
-        int npts = 0;
-        bool bad = qbad;
-        auto stage = [&](const float4 &p, int pos) __attribute__((always_inline)) {
-            const float dx = wrap_diff<PER>(p.x - cx, Lp, Lh);
-            const float dy = wrap_diff<PER>(p.y - cy, Lp, Lh);
-            const float dz = wrap_diff<PER>(p.z - cz, Lp, Lh);
-            const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
-            tile[pos] = make_float4(p.x, p.y, p.z, pw);
-            tidx[pos] = __float_as_int(p.w);
-            bad = bad || !(pw < FILTER_BIG);
-        };
-        const int e_st = __float_as_int(n_lo.w);
-        int at[4] = {0, 0, 0, 0};
-        while (pend) {
-            const int qq = __ffsll((unsigned long long)pend) - 1;
-            const int c = __builtin_amdgcn_readlane(e_sc, qq);
-            if (npts + c > TILE_PTS) break;
-            pend &= pend - 1ull;
-            ++visited;
-            const int st = __builtin_amdgcn_readlane(e_st, qq);
-            if (types) {
-                if (lane < __builtin_amdgcn_readlane(__float_as_int(n_hi.w), qq)) {
-                    const float4 p = pts[st + lane];
-                    const bool real = __float_as_int(p.w) < src_hi;
-                    const int pos = npts + (int)__popcll(__ballot(real) & lanemask_lt());
-                    if (real) stage(p, pos);
+                    for (int i = 0; i < nq_near; ++i) {
+                        const float4 p = tile[i];
+                        need |= point_low2_m<PER>(p.x, p.y, p.z, n_lo.x, n_lo.y, n_lo.z, n_hi.x,
+                                                  n_hi.y, n_hi.z, Lp) <= p.w;
+                    }
+                    pend &= __ballot(need);
+                    tested = true;
+                    wave_lds_sync();
                 }
-            } else {
+                fresh = false;
+                // take entries in order while their points fit the tile: position f
+                // of the tile is point f + delta, delta changing with the source
+                // (several loads per lane in flight; separate point types need the
+                // packing of each leaf's source points and go source by source)
+                int npts = 0;
+                bool bad = qbad;
+                auto stage = [&](const float4 &p, int pos) __attribute__((always_inline)) {
+                    const float dx = wrap_diff<PER>(p.x - cx, Lp, Lh);
+                    const float dy = wrap_diff<PER>(p.y - cy, Lp, Lh);
+                    const float dz = wrap_diff<PER>(p.z - cz, Lp, Lh);
+                    const float pw = (dx * dx + dy * dy + dz * dz) * (1.0f - FILTER_E);
+                    tile[pos] = make_float4(p.x, p.y, p.z, pw);
+                    tidx[pos] = __float_as_int(p.w);
+                    bad = bad || !(pw < FILTER_BIG);
+                };
+                const int e_st = __float_as_int(n_lo.w);
+                int at[4] = {0, 0, 0, 0};
+                while (pend) {
+                    const int qq = __ffsll((unsigned long long)pend) - 1;
+                    const int c = __builtin_amdgcn_readlane(e_sc, qq);
+                    if (npts + c > TILE_PTS) break;
+                    pend &= pend - 1ull;
+                    ++visited;
+                    const int st = __builtin_amdgcn_readlane(e_st, qq);
+                    if (types) {
+                        if (lane < __builtin_amdgcn_readlane(__float_as_int(n_hi.w), qq)) {
+                            const float4 p = pts[st + lane];
+                            const bool real = __float_as_int(p.w) < src_hi;
+                            const int pos = npts + (int)__popcll(__ballot(real) & lanemask_lt());
+                            if (real) stage(p, pos);
+                        }
+                    } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (u * 64 + lane >= npts) at[u] = st - npts;
-            }
-            npts += c;
-        }
-        if (!types) {
-#pragma unroll
-            for (int v = 0; v < 4; v += 2) {
-                float4 p[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if ((v + u) * 64 + lane < npts) p[u] = pts[at[v + u] + (v + u) * 64 + lane];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if ((v + u) * 64 + lane < npts) stage(p[u], (v + u) * 64 + lane);
-            }
-        }
-        bad = __ballot(bad) != 0;
-        wave_lds_sync();
-        evals += (unsigned)npts * (unsigned)acount;
-        for (int p0 = 0; p0 < npts; p0 += HALF) {
-            const int m = min(HALF, npts - p0);
-            steps += (unsigned)((m + 15) >> 4);
-            unsigned wd[4] = {0, 0, 0, 0};
-            bool dense = bad;
-            float thr = kth;
-            if constexpr (PER) {
-                // the k-th distance raised by 2^-19 L
-                const float rt = __builtin_sqrtf(kth) * (1.0f + 0x1p-20f) + Lp * 0x1p-19f;
-                dense = dense || __ballot(act && !(qfar + rt < Lh * (1.0f - 0x1p-10f)));
-                thr = rt * rt;
-            }
-            // t of this lane's query
-            const float tq = act ? thr * (1.0f + FILTER_E) - nq + FILTER_TINY : -FILTER_BIG;
-            if (dense) dense_words<PER>(tile + p0, m, 4 >> lgS, h, me, act ? kth : -1.0f, Lp, Lh, wd);
-            else if (lgS == 0) filter_words<1, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
-            else if (lgS == 1) filter_words<2, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
-            else filter_words<4, PER>(tilef + 4 * p0 + arow, m, h, ac, aL, Lh, bq, tq, wd);
-            // queue the hits word by word, lowest position first; the queue is
-            // drained before a word that would overflow some lane's, and
-            // after the batch's last word
-            const int W = 4 >> lgS;
-            for (int k = 0; k <= W; ++k) {
-                unsigned M = wd[0];
-                wd[0] = wd[1];
-                wd[1] = wd[2];
-                wd[2] = wd[3];
-                wd[3] = 0;
-                const bool full = __ballot(qp + 64 * __popc(M) > q0 + 64 * CQ) != 0;
-                if (full || (k == W && p0 + HALF >= npts)) drain();
-                const int pb = p0 + W * h + k;
-                while (M) {
-                    *qp = (uint8_t)(pb + ((__ffs((int)M) - 1) << 2));
-                    qp += 64;
-                    M &= M - 1u;
+                        for (int u = 0; u < 4; ++u)
+                            if (u * 64 + lane >= npts) at[u] = st - npts;
+                    }
+                    npts += c;
                 }
+                if (!types) {
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) {
+                        float4 p[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            if ((v + u) * 64 + lane < npts)
+                                p[u] = pts[at[v + u] + (v + u) * 64 + lane];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            if ((v + u) * 64 + lane < npts) stage(p[u], (v + u) * 64 + lane);
+                    }
+                }
+                bad = __ballot(bad) != 0;
+                wave_lds_sync();
+                evals += (unsigned)npts * (unsigned)acount;
+                for (int p0 = 0; p0 < npts; p0 += HALF) {
+                    const int m = min(HALF, npts - p0);
+                    steps += (unsigned)((m + 15) >> 4);
+                    unsigned wd[4] = {0, 0, 0, 0};
+                    bool dense = bad;
+                    float thr = kth;
+                    if constexpr (PER) {
+                        // the k-th distance raised by 2^-19 L
+                        const float rt = __builtin_sqrtf(kth) * (1.0f + 0x1p-20f) + Lp * 0x1p-19f;
+                        dense = dense || __ballot(act && !(qfar + rt < Lh * (1.0f - 0x1p-10f)));
+                        thr = rt * rt;
+                    }
+                    // t of this lane's query
+                    const float tq = act ? thr * (1.0f + FILTER_E) - nq + FILTER_TINY : -FILTER_BIG;
+                    const float *ap = tilef + 4 * p0 + arow;
+                    if (dense)
+                        dense_words<PER>(tile + p0, m, 4 >> lgS, h, me, act ? kth : -1.0f, Lp, Lh, wd);
+                    else if (lgS == 0) filter_words<1, PER>(ap, m, h, ac, aL, Lh, bq, tq, wd);
+                    else if (lgS == 1) filter_words<2, PER>(ap, m, h, ac, aL, Lh, bq, tq, wd);
+                    else filter_words<4, PER>(ap, m, h, ac, aL, Lh, bq, tq, wd);
+                    // queue the hits word by word, lowest position first; the queue is
+                    // drained before a word that would overflow some lane's, and
+                    // after the batch's last word
+                    const int W = 4 >> lgS;
+                    for (int k = 0; k <= W; ++k) {
+                        unsigned M = wd[0];
+                        wd[0] = wd[1];
+                        wd[1] = wd[2];
+                        wd[2] = wd[3];
+                        wd[3] = 0;
+                        const bool full = __ballot(qp + 64 * __popc(M) > q0 + 64 * CQ) != 0;
+                        if (full || (k == W && p0 + HALF >= npts)) drain();
+                        const int pb = p0 + W * h + k;
+                        while (M) {
+                            *qp = (uint8_t)(pb + ((__ffs((int)M) - 1) << 2));
+                            qp += 64;
+                            M &= M - 1u;
+                        }
+                    }
+                    if (p0 + HALF < npts) kth = group_kth();
+                }
+                wave_lds_sync();
             }
-            if (p0 + HALF < npts) kth = group_kth();
         }
-        wave_lds_sync();
-        }
-    }
     }
     // merge the partial lists of a query's lanes
     if (lgS >= 1) {
