@@ -1066,11 +1066,15 @@ static jz_status top_lists(jz_tree *t, const uint64_t *keys, int bits3, hipStrea
     const int64_t LT = t->L[T];
     if (t->nsets == 1) {
         const int64_t S = t->S = (LT + o.ngr - 1) / o.ngr;
+        size_t bytes;
+        if (!top_list_bytes(S, bytes))
+            return jz_fail(JZ_E_OOM, "the list of all pairs of %lld super nodes does not fit; raise "
+                           "ngr or lower n_target", (long long)S);
         t->knn_top_last = S * (S - 1);
         t->fof_top_last = (S - 1) * (S + 2) / 2;
         JZ_TRY(t->super_spl.get(ac, (S + 1) * sizeof(int), s));
         JZ_TRY(t->knn_top_seg.get(ac, S * sizeof(int2), s));
-        JZ_TRY(t->knn_top_list.get(ac, S * S * sizeof(int2), s));
+        JZ_TRY(t->knn_top_list.get(ac, bytes, s));
         JZ_TRY(t->fof_top_seg.get(ac, S * sizeof(int2), s));
         JZ_TRY(t->fof_top_list.get(ac, S * (S + 1) / 2 * sizeof(int2), s));
         k_top_lists<<<std::min<unsigned>(blocks_for(S * S + 1, 256), 4096), 256, 0, s>>>(

@@ -208,6 +208,12 @@ jz_status run_knn(jz_tree *t, int k, int32_t *idx, float *dist2, hipStream_t s,
 // run_fof writes its call statistics to `st_out` when given (else to t->st)
 jz_status run_fof(jz_tree *t, const float *b2_set_host, int32_t *label, hipStream_t s,
                   jz_stats *st_out = nullptr);
+// Bytes of the dense kNN list over S super nodes of one set (the FoF list's are
+// fewer); false if no device could hold it.
+inline bool top_list_bytes(int64_t S, size_t &bytes) {
+    bytes = (size_t)S * (size_t)S * sizeof(int2);  // (wraps from 1518500250 super nodes on)
+    return S <= (int64_t)1 << 28;                  // 2^59 bytes
+}
 // JZ_E_CAPACITY for a super-node list whose rows begin beyond 2^31 - 1
 jz_status check_top(int64_t last);
 // the ranges jz_build_opts documents (JZ_E_INVALID with a message otherwise)
